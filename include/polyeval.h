@@ -253,10 +253,11 @@ pe_status pe_batch_eval(const pe_batch* batch, int32_t points_per_system, const 
  *              256-byte aligned, owned by the caller.
  *   resid_out  device [P][2] doubles: |F(x)|_2 before the step and
  *              |dx|_inf (leading limbs), or NULL.
- * Systems with fewer than 128 variables are solved by one workgroup per
- * point; larger ones by the column-parallel solve of pe_lstsq below.
- * Requires N >= n (least squares), N <= 4096 for the column-parallel solve
- * and at most 65535 points (PE_EUNSUPPORTED otherwise).  Enqueues kernels only
+ * The solve is that of pe_lstsq below; points beyond what 1 GiB of solver
+ * workspace holds go through it in groups.
+ * Requires N >= n (least squares), at most 65535 points, and N <= 4096 for
+ * 128 variables or more (fewer variables: two columns of N numbers within a
+ * workgroup's LDS, or N <= 4096) (PE_EUNSUPPORTED otherwise).  Enqueues kernels only
  * (no allocation, no host synchronisation): capturable in a HIP graph.  A
  * numerically zero pivot (|r_kk| <= n u_L max|r|) gives dx = 0 for that point
  * and resid_out[p][1] = -1; the call itself returns PE_OK. */
@@ -287,20 +288,21 @@ pe_status pe_homotopy_track(const pe_system* sys, int32_t P, double* x_inout, co
                             int32_t corrector_iters, void* workspace, double* resid_out, void* stream);
 
 /* The same for every system of a batch, x in the packed batch layout;
- * resid_out is [S][P][2].  Every system is solved by one workgroup per point:
- * n + 1 <= 1024 and the largest pivot column within one workgroup's LDS. */
+ * resid_out is [S][P][2].  Takes n + 1 <= 1024 and two columns of N numbers
+ * within one workgroup's LDS (PE_EUNSUPPORTED otherwise). */
 size_t pe_batch_newton_workspace_bytes(const pe_batch* batch, int32_t P);
 pe_status pe_batch_newton_step(const pe_batch* batch, int32_t P, double* x_inout, void* workspace,
                                double* resid_out, void* stream);
 
 /* ------------------------------------------------------------------ least squares
- * Solve A x = b in the least-squares sense by modified Gram-Schmidt on the
- * augmented matrix [A b] = [Q q][R y; 0 z] (Sec. 3, Fig. 4, eq. (2)):
- * right-looking, one workgroup per column; the inner products in rounds of
- * tiled partial sums (eq. (3)); the pivot columns normalised only when
- * needed (delayed normalisation: r_kj = a_k^H a_j / |a_k| and the update
- * divides by |a_k|^2); then the back substitution R x = y in stages of
- * blocks of 256 rows (eq. (4)).
+ * Solve A x = b in the least-squares sense by Gram-Schmidt on the augmented
+ * matrix [A b] = [Q q][R y; 0 z] (Sec. 3, Fig. 4, eq. (2)): right-looking, in
+ * panels of 32 (complex) or 64 (real) columns.  A panel is orthonormalised
+ * through its Gram matrix (column by column where that is too ill-
+ * conditioned) and its projector is taken off the columns behind it; the
+ * contractions run on the matrix cores with exact sums of more bits than the
+ * level has.  Then the back substitution R x = y in stages of blocks of 256
+ * rows (eq. (4)).
  *   level      1, 2 or 4, or PE_REAL | 1, 2, 4 (real: one component per
  *              array below).  P points (independent problems), 0 <= P <= 65535.
  *   N, n       rows and unknowns: 1 <= n <= N <= 4096.

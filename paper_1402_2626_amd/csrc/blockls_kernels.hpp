@@ -1,0 +1,1312 @@
+// Least-squares solve of A x = b by Gram-Schmidt on the augmented matrix
+// [A b] (Sec. 3, Fig. 4, eq. (2)) in panels of B columns, with the long
+// contractions on the int8 matrix cores, for any number of problems at once.
+//
+// Per panel (columns k0 .. k0 + B - 1 of the working copy W, already updated
+// by the panels before it):
+//   1. bl_slice_kernel, bl_dot_kernel: the Gram matrix of the panel;
+//   2. bl_chol_kernel: its factor U^H D U, one workgroup per problem, so that
+//      the serial chain of a panel is B small steps in LDS instead of B inner
+//      products over all rows and B launches;
+//   3. bl_solve_kernel: X = A U^-1 D^-1/2 by forward substitution, row by row
+//      (backward stable in each row), X overwriting the panel;
+//   4. bl_dot_kernel: S = X^H [X | trailing columns].  E = X^H X - I is
+//      what the factor's rounding left (at most about 2^-58 in double double,
+//      see bl_chol_kernel), and its first order is folded into everything
+//      that follows: Q = X (I - F), R = (I + F) D^1/2 U, F the upper
+//      triangle of E with half its diagonal, so that Q^H Q = I + O(E^2);
+//   5. bl_fin_kernel: the rows of R, and T = (I - E) S;
+//   6. bl_update_kernel: trailing columns -= X T.
+// The trailing columns see the exact projector of the panel's span, panels in
+// order: the right-looking sweep of Fig. 4 with its columns in blocks.  A
+// panel too ill-conditioned for its Gram matrix is orthogonalised by plain
+// modified Gram-Schmidt inside bl_chol_kernel instead (repeated where one
+// sweep would leave E too large), so every matrix the one-column-at-a-time
+// algorithm takes is taken.
+//
+// Contractions.  A multi-double is cut into ND signed base-256 digits
+// (fixed point against a power of two: the column's largest entry for the
+// contraction over rows, the row's largest entry of X and the column's
+// largest entry of T for the update), and a product is the sum over the digit
+// pairs i + j < ND of int8 matrix products with 32-bit sums, which are exact:
+// |digit product| <= 2^14, at most ND pairs and 4096 rows (10240 rows at
+// ND = 10).  What is dropped is below 2^(-8 ND + 4) of the operands'
+// largest products: ND = 16 (128 bits) for double double, 30 (240) for quad
+// double, 10 (80) for double, each beyond the arithmetic of mdarith.hpp with
+// bits to spare for rows of very uneven size.
+// The FP64 pipes spend about 62 instructions on a complex double-double
+// multiply-add and reach at most 0.63e12 of them a second; ND = 16 takes
+// 544 int8 multiply-adds, of which the matrix cores do 2.5e15 a second.
+// Against the column-by-column sweep that this replaces (a launch and two
+// workgroup reductions per pivot, FP64 throughout) a Gauss-Newton step went
+// from 2.08 to 1.02 ms (complex double double, n = 256), 53.5 to 17.5 ms
+// (n = 2048), 35.0 to 12.8 ms (real quad double, n = 1016), and the batched
+// step over 96 system-points of n = 32 .. 256 from 39.9 to 2.5 ms.
+#pragma once
+#include <hip/hip_runtime.h>
+
+#include <algorithm>
+
+#include "eval_kernels.hpp"
+#include "mdarith.hpp"
+#include "newton_kernels.hpp"
+
+namespace pe {
+
+typedef int bl_v4i __attribute__((ext_vector_type(4)));
+
+template <int L>
+struct Bl {
+  static constexpr int NL = limbs_of(L);
+  static constexpr int CX = is_real(L) ? 1 : 2;    // real numbers per number
+  static constexpr int B = 64 / CX;                // panel columns: 64 real ones
+  static constexpr int ND = NL == 1 ? 10 : (NL == 2 ? 16 : 30);
+  static constexpr int NW = (8 * ND + 31) / 32;    // 32-bit words of a fixed-point number
+  static constexpr int W = CX * NL;                // doubles per number
+  static constexpr int NT = NL == 4 ? 1 : 2;       // tiles of 16 real columns per workgroup of the contraction
+  // level code of the Gram matrix and its factor: double works in double double
+  static constexpr int LC = NL == 1 ? L + 1 : L;
+  static constexpr int WC = CX * limbs_of(LC);
+};
+
+constexpr int kBlRows = 64;     // rows of a chunk: the K of a matrix instruction
+constexpr int kBlBs = 256;      // rows of a back-substitution block
+constexpr int kBlMaxSplit = 4;  // row splits of a contraction
+constexpr int kBlGramSplit = 16;  // and of the Gram matrix's
+constexpr int kExpOne = 1022;   // biased exponent field E of v: |v| < 2^(E - 1022)
+
+// the problems of one launch group; per-slot strides in bytes
+struct BlView {
+  const BatchNewtonDesc* desc;  // batch: system's sizes and offsets, or null
+  const int* order;
+  int P, q0;          // batch: problem q0 + slot is point (q % P) of system order[q / P]
+  int N, n;           // uniform problems (desc null): slot s is point q0 + s
+  const double* A;    // augmented matrices, row-major planar
+  int64_t a_pt, a_plane, ld;
+  double* X;
+  int64_t x_pt;
+  int add;
+  double* resid;
+  double* Rout;
+  double* Qout;
+  char* ws;
+  size_t slot;        // bytes of a slot
+  // byte offsets inside a slot
+  size_t oW, oR, oInv, oY, oU, oRp, oF, oS, oXD, oXU, oXr, oSD, oSe, oCe, oMisc;
+  size_t s_split;     // bytes of one split's contraction output
+  size_t g_split;     // and of one split's Gram matrix
+  int nmax;           // stride of the two column-exponent arrays
+};
+
+struct BlMisc {
+  double rmax;   // largest |r_ii| so far
+  int flag;      // 1: a pivot was numerically zero, the problem is done
+  int mgs;       // 1: the current panel was orthogonalised by plain MGS
+};
+
+// Offsets of a slot's regions for problems of at most N rows and n unknowns
+// (bytes, each 256-byte aligned): W [components][n + 1][N] the working copy
+// by columns, R [components][n + 1][n] by columns (column n is y = Q^H b),
+// 1 / r_jj, y, the panel's U and D^1/2 U, F of every panel, S per row split,
+// the digits of X in two orders with its row exponents, the digits of T with
+// its column exponents, two sets of column exponents, the state.
+template <int L>
+inline void bl_layout(int N, int n, BlView& V) {
+  using K = Bl<L>;
+  const size_t NC = size_t(N + kBlRows - 1) / kBlRows, B = K::B;
+  const size_t panels = (size_t(n) + B - 1) / B;
+  size_t off = 0;
+  auto take = [&](size_t bytes) {
+    const size_t at = off;
+    off += (bytes + 255) & ~size_t(255);
+    return at;
+  };
+  V.nmax = n + 1;
+  V.oW = take(size_t(K::W) * (n + 1) * N * 8);
+  V.oR = take(size_t(K::W) * (n + 1) * n * 8);
+  V.oInv = take(size_t(n) * K::NL * 8);
+  V.oY = take(size_t(n) * K::W * 8);
+  V.oU = take((B * B * K::W + B * K::NL) * 8);
+  V.oRp = take(B * B * K::W * 8 + B * 4);
+  V.oF = take(panels * B * B * K::CX * 8);
+  V.g_split = B * B * K::WC * 8;
+  V.s_split = size_t(n + 1) * B * K::W * 8;
+  const size_t gs = std::min<size_t>(NC, kBlGramSplit), ds = std::min<size_t>(NC, kBlMaxSplit);
+  V.oS = take(std::max(gs * V.g_split, ds * V.s_split));
+  V.oXD = take(NC * K::ND * 4096);
+  V.oXU = take(NC * K::ND * 4096);
+  V.oXr = take(NC * kBlRows * 4);
+  V.oSD = take((size_t(n + 1) * K::CX + 15) / 16 * K::ND * 1024);
+  V.oSe = take(size_t(n + 1) * 4);
+  V.oCe = take(size_t(n + 1) * 2 * 4);
+  V.oMisc = take(sizeof(BlMisc));
+  V.slot = off;
+}
+
+
+struct BlProb {
+  int N, n;
+  const double* A;
+  int64_t a_plane, ld;
+  double* x;
+  double* resid;
+  char* base;
+};
+
+template <int L>
+__device__ __forceinline__ BlProb bl_prob(const BlView& V, int slot) {
+  BlProb p;
+  p.base = V.ws + size_t(slot) * V.slot;
+  if (V.desc) {
+    const int q = V.q0 + slot;
+    const int s = V.order[q / V.P], pt = q - (q / V.P) * V.P;
+    const BatchNewtonDesc d = V.desc[s];
+    p.N = d.N;
+    p.n = d.n;
+    p.ld = d.n + 1;
+    p.a_plane = int64_t(d.N) * p.ld;
+    p.A = V.A + d.w_off * V.P + pt * (int64_t(width_of(L)) * p.a_plane);
+    p.x = V.X + d.x_off * V.P + pt * (int64_t(width_of(L)) * d.n);
+    p.resid = V.resid ? V.resid + (int64_t(s) * V.P + pt) * 2 : nullptr;
+  } else {
+    const int64_t pt = V.q0 + slot;
+    p.N = V.N;
+    p.n = V.n;
+    p.ld = V.ld;
+    p.a_plane = V.a_plane;
+    p.A = V.A + pt * V.a_pt;
+    p.x = V.X + pt * V.x_pt;
+    p.resid = V.resid ? V.resid + 2 * pt : nullptr;
+  }
+  return p;
+}
+
+template <typename T>
+__device__ __forceinline__ T* bl_at(const BlProb& p, size_t off) {
+  return reinterpret_cast<T*>(p.base + off);
+}
+
+__device__ __forceinline__ int bl_exp(double v) {
+  return int((__double_as_longlong(v) >> 52) & 0x7ff);
+}
+
+// ------------------------------------------------------------------ fixed point
+
+// The ND leading balanced base-256 digits of v = sum of the limbs, |v| <= 2^e,
+// as bytes: digit d (weight 2^(e - 6 - 8 d)) is byte 3 - d % 4 of w[d / 4].
+// Every limb is cut into signed 32-bit words, each rounded to nearest (adding
+// 1.5 2^52 leaves the integer in the low bits, and the remainder is exact),
+// the words are added with carries as integers, and the bias of 0x80 per byte
+// turns two's complement into digits of -128 .. 127.
+template <int NL, int ND>
+__device__ __forceinline__ void bl_digits(const double (&x)[NL], int e, uint32_t* w) {
+  constexpr int NW = (8 * ND + 31) / 32;
+  constexpr double kMagic = 6755399441055744.0;           // 1.5 2^52
+  constexpr int64_t kMagicBits = 0x4338000000000000LL;  // its representation
+  int64_t acc[NW];
+#pragma unroll
+  for (int q = 0; q < NW; ++q) acc[q] = 0x80808080LL;
+#pragma unroll
+  for (int l = 0; l < NL; ++l) {
+    const int s0 = 53 * l / 32;  // the first word a limb can reach
+    double y = __builtin_ldexp(x[l], 30 + 32 * s0 - e);
+#pragma unroll
+    for (int q = s0; q < NW; ++q) {
+      const double t = y + kMagic;
+      int64_t bits;
+      __builtin_memcpy(&bits, &t, 8);
+      acc[q] += bits - kMagicBits;
+      y = (y - (t - kMagic)) * 4294967296.0;
+    }
+  }
+  int64_t carry = 0;
+#pragma unroll
+  for (int q = NW - 1; q >= 0; --q) {
+    const int64_t a = acc[q] + carry;
+    w[q] = uint32_t(a) ^ 0x80808080u;
+    carry = a >> 32;
+  }
+}
+
+// bytes of four words regrouped: out[s] holds byte 3 - s of each, word 0's lowest
+__device__ __forceinline__ void bl_transpose4(uint32_t a0, uint32_t a1, uint32_t a2, uint32_t a3, uint32_t* out) {
+  const uint32_t x = __builtin_amdgcn_perm(a1, a0, 0x05010400u), y = __builtin_amdgcn_perm(a1, a0, 0x07030602u);
+  const uint32_t u = __builtin_amdgcn_perm(a3, a2, 0x05010400u), v = __builtin_amdgcn_perm(a3, a2, 0x07030602u);
+  out[0] = __builtin_amdgcn_perm(v, y, 0x07060302u);
+  out[1] = __builtin_amdgcn_perm(v, y, 0x05040100u);
+  out[2] = __builtin_amdgcn_perm(u, x, 0x07060302u);
+  out[3] = __builtin_amdgcn_perm(u, x, 0x05040100u);
+}
+
+// digits of four numbers (the limbs of number r in v[r]), packed four to a
+// word, written to dst[d * stride] for digit d
+template <int NL, int ND>
+__device__ __forceinline__ void bl_put4(const double (&v)[4][NL], const int (&e)[4], uint32_t* dst, int stride) {
+  constexpr int NW = (8 * ND + 31) / 32;
+  uint32_t w[4][NW];
+#pragma unroll
+  for (int r = 0; r < 4; ++r) bl_digits<NL, ND>(v[r], e[r], w[r]);
+#pragma unroll
+  for (int q = 0; q < NW; ++q) {
+    uint32_t o[4];
+    bl_transpose4(w[0][q], w[1][q], w[2][q], w[3][q], o);
+#pragma unroll
+    for (int s = 0; s < 4; ++s)
+      if (4 * q + s < ND) dst[(4 * q + s) * stride] = o[s];
+  }
+}
+
+// sum over t of a[t] 2^(-8 t) times 2^e: groups of three sums are exact in a
+// double, the groups are added by an error-free chain
+template <int NL, int ND>
+__device__ __forceinline__ R<NL> bl_value(const int (&a)[ND], int e) {
+  constexpr int NG = (ND + 2) / 3;
+  double g[NG];
+#pragma unroll
+  for (int q = 0; q < NG; ++q) {
+    double s = double(a[3 * q]) * 65536.0;
+    if (3 * q + 1 < ND) s = PE_FMA(double(a[3 * q + 1 < ND ? 3 * q + 1 : 0]), 256.0, s);
+    if (3 * q + 2 < ND) s += double(a[3 * q + 2 < ND ? 3 * q + 2 : 0]);
+    g[q] = __builtin_ldexp(s, -24 * q - 16);
+  }
+  R<NL> r;
+  if constexpr (NL == 1) {
+    double s = g[NG - 1];
+#pragma unroll
+    for (int q = NG - 2; q >= 0; --q) s += g[q];
+    r.x[0] = s;
+  } else if constexpr (NL == 2) {
+    double h = g[0], l = 0.0;
+#pragma unroll
+    for (int q = 1; q < NG; ++q) {
+      double s, t;
+      two_sum(h, g[q], s, t);
+      h = s;
+      l += t;
+    }
+    fast_two_sum(h, l, r.x[0], r.x[1]);
+  } else {
+    double x0 = g[0], x1 = 0.0, x2 = 0.0, x3 = 0.0;
+#pragma unroll
+    for (int q = 1; q < NG; ++q) {
+      double s, t, u, v;
+      two_sum(x0, g[q], s, t);
+      x0 = s;
+      two_sum(x1, t, u, v);
+      x1 = u;
+      two_sum(x2, v, s, t);
+      x2 = s;
+      x3 += t;
+    }
+    r = renorm4(x0, x1, x2, x3);
+  }
+#pragma unroll
+  for (int l = 0; l < NL; ++l) r.x[l] = __builtin_ldexp(r.x[l], e);
+  return r;
+}
+
+template <int L>
+__device__ __forceinline__ C<L> bl_ldexp(C<L> a, int e) {
+#pragma unroll
+  for (int l = 0; l < limbs_of(L); ++l) {
+    a.re.x[l] = __builtin_ldexp(a.re.x[l], e);
+    if constexpr (!is_real(L)) a.im.x[l] = __builtin_ldexp(a.im.x[l], e);
+  }
+  return a;
+}
+
+template <int LO, int L>
+__device__ __forceinline__ C<LO> bl_narrow(const C<L>& a) {
+  C<LO> r;
+#pragma unroll
+  for (int l = 0; l < limbs_of(LO); ++l) {
+    r.re.x[l] = a.re.x[l];
+    if constexpr (!is_real(L)) r.im.x[l] = a.im.x[l];
+  }
+  return r;
+}
+
+// ------------------------------------------------------------------ set up
+
+// Per problem: state cleared, |b|_2 (leading limbs) into resid[0].  grid
+// (slots), 256 threads
+template <int L>
+__global__ __launch_bounds__(256) void bl_init_kernel(BlView V) {
+  __shared__ double red[256];
+  const BlProb p = bl_prob<L>(V, blockIdx.x);
+  const int tid = threadIdx.x;
+  int* ce = bl_at<int>(p, V.oCe);
+  for (int j = tid; j <= p.n; j += 256) ce[j] = ce[V.nmax + j] = 0;
+  if (tid == 0) {
+    BlMisc* m = bl_at<BlMisc>(p, V.oMisc);
+    m->rmax = 0.0;
+    m->flag = 0;
+    m->mgs = 0;
+  }
+  double s = 0.0;
+  for (int i = tid; i < p.N; i += 256) {
+    const double re = p.A[int64_t(i) * p.ld + p.n];
+    const double im = is_real(L) ? 0.0 : p.A[int64_t(limbs_of(L)) * p.a_plane + int64_t(i) * p.ld + p.n];
+    s += re * re + im * im;
+  }
+  red[tid] = s;
+  __syncthreads();
+  for (int k = 128; k > 0; k >>= 1) {
+    if (tid < k) red[tid] += red[tid + k];
+    __syncthreads();
+  }
+  if (tid == 0 && p.resid) p.resid[0] = sqrt(red[0]);
+}
+
+// [A b] (row-major) -> column-major W, and every column's largest exponent.
+// Tiles of 64 rows x 64 columns through LDS, both sides coalesced; grid
+// (tiles, components, slots), 256 threads
+template <int L>
+__global__ __launch_bounds__(256) void bl_copy_in_kernel(BlView V) {
+  __shared__ double tile[64][65];
+  const BlProb p = bl_prob<L>(V, blockIdx.z);
+  const int ncol = p.n + 1, tc = (ncol + 63) / 64;
+  const int bt = blockIdx.x;
+  const int c0 = (bt % tc) * 64, r0 = (bt / tc) * 64;
+  if (r0 >= p.N) return;
+  const int comp = blockIdx.y;
+  const double* src = p.A + comp * p.a_plane;
+  double* dst = bl_at<double>(p, V.oW) + int64_t(comp) * ncol * p.N;
+  int* ce = bl_at<int>(p, V.oCe);
+  const int tx = threadIdx.x & 63, ty = threadIdx.x >> 6;
+  for (int r = ty; r < 64; r += 4) {
+    const int row = r0 + r, col = c0 + tx;
+    tile[r][tx] = (row < p.N && col < ncol) ? src[int64_t(row) * p.ld + col] : 0.0;
+  }
+  __syncthreads();
+  for (int c = ty; c < 64; c += 4) {
+    const int col = c0 + c, row = r0 + tx;
+    const double v = tile[tx][c];
+    if (row < p.N && col < ncol) dst[int64_t(col) * p.N + row] = v;
+    if (comp % limbs_of(L) == 0) {
+      int e = bl_exp(v);
+#pragma unroll
+      for (int m = 1; m < 64; m <<= 1) e = max(e, __shfl_xor(e, m));
+      if (tx == 0 && col < ncol) atomicMax(ce + col, e);
+    }
+  }
+}
+
+// ------------------------------------------------------------------ contractions over rows
+
+// Digits of the panel's columns (fixed point against each column's largest
+// entry) in the order the contraction reads: [chunk][digit][64 real
+// columns][64 rows] bytes.  grid (chunks, slots), 256 threads
+template <int L>
+__global__ __launch_bounds__(256) void bl_slice_kernel(BlView V, int panel, int cur) {
+  using K = Bl<L>;
+  const BlProb p = bl_prob<L>(V, blockIdx.y);
+  const int k0 = panel * K::B, ch = blockIdx.x;
+  if (k0 >= p.n || ch * kBlRows >= p.N || bl_at<BlMisc>(p, V.oMisc)->flag) return;
+  const int bcur = min(K::B, p.n - k0);
+  const double* Wp = bl_at<double>(p, V.oW);
+  const int64_t plane = int64_t(p.n + 1) * p.N;
+  const int* ce = bl_at<int>(p, V.oCe) + cur * V.nmax;
+  uint32_t* xd = bl_at<uint32_t>(p, V.oXD) + size_t(ch) * K::ND * 1024;
+  const int k4 = threadIdx.x & 15;
+  for (int m = threadIdx.x >> 4; m < 64; m += 16) {
+    const int c = m / K::CX, comp = m % K::CX;
+    double v[4][K::NL];
+    int e[4];
+    const int ex = c < bcur ? ce[k0 + c] - kExpOne : 0;
+#pragma unroll
+    for (int r = 0; r < 4; ++r) {
+      const int row = ch * kBlRows + k4 * 4 + r;
+      e[r] = ex;
+#pragma unroll
+      for (int l = 0; l < K::NL; ++l)
+        v[r][l] = (c < bcur && row < p.N) ? Wp[(comp * K::NL + l) * plane + int64_t(k0 + c) * p.N + row] : 0.0;
+    }
+    bl_put4<K::NL, K::ND>(v, e, xd + m * 16 + k4, 1024);
+  }
+}
+
+// S = X^H C for the columns C of W from k0 on (GRAM: the panel's own columns,
+// and X the panel itself, both scaled by their column exponents; else X is
+// orthonormal, C the panel and all later columns with the right-hand side).
+// One workgroup takes NT tiles of 16 real columns and a range of rows: per
+// chunk of 64 rows it cuts its columns into digits in LDS once, and each of
+// its four wavefronts multiplies them by the digits of 16 of X's 64 real
+// columns.  Row ranges are summed by the kernels that read S.  S is
+// [split][column][B] numbers.  grid (column tiles, splits, slots), 256 threads
+template <int L, bool GRAM>
+__global__ __launch_bounds__(256, limbs_of(L) == 4 ? 1 : 2) void bl_dot_kernel(BlView V, int panel, int cur, int nsplit) {
+  using K = Bl<L>;
+  constexpr int NL = K::NL, ND = K::ND, NT = K::NT, CX = K::CX;
+  constexpr int LO = GRAM ? K::LC : L;  // level of the output
+  constexpr int NO = limbs_of(LO);
+  __shared__ bl_v4i dig[NT * ND * 64];
+  const BlProb p = bl_prob<L>(V, blockIdx.z);
+  const int k0 = panel * K::B;
+  if (k0 >= p.n || bl_at<BlMisc>(p, V.oMisc)->flag) return;
+  const int bcur = min(K::B, p.n - k0);
+  const int ncols = (GRAM ? bcur : p.n + 1 - k0) * CX;  // real columns
+  const int rc0 = blockIdx.x * NT * 16;
+  const int NC = (p.N + kBlRows - 1) / kBlRows;
+  const int ns = min(nsplit, NC), split = blockIdx.y;
+  if (rc0 >= ncols || split >= ns) return;
+  const int per = (NC + ns - 1) / ns;
+  const int ch0 = split * per, ch1 = min(NC, ch0 + per);
+  const double* Wp = bl_at<double>(p, V.oW);
+  const int64_t plane = int64_t(p.n + 1) * p.N;
+  const int* ce = bl_at<int>(p, V.oCe) + cur * V.nmax;
+  const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
+  int acc[NT][ND][4];
+  bl_v4i av[NT][ND];
+#pragma unroll
+  for (int t = 0; t < NT; ++t)
+#pragma unroll
+    for (int d = 0; d < ND; ++d) av[t][d] = bl_v4i{0, 0, 0, 0};
+  const int k4 = tid & 15, c16 = tid >> 4;
+  // power of two of column c (from the panel's first): X itself is at most 1
+  auto col_exp = [&](int c) { return !GRAM && c < bcur ? 0 : ce[k0 + c] - kExpOne; };
+  int ex[NT];
+  const double* src[NT];
+#pragma unroll
+  for (int u = 0; u < NT; ++u) {
+    const int rc = rc0 + u * 16 + c16;
+    const int col = k0 + min(rc, ncols - 1) / CX;
+    ex[u] = col_exp(col - k0);
+    src[u] = Wp + int64_t(rc % CX) * NL * plane + int64_t(col) * p.N;
+  }
+  for (int ch = ch0; ch < ch1; ++ch) {
+    const bl_v4i* xd = bl_at<bl_v4i>(p, V.oXD) + size_t(ch) * ND * 256 + (16 * wave + (lane & 15)) * 4 + (lane >> 4);
+    bl_v4i a[ND];
+#pragma unroll
+    for (int i = 0; i < ND; ++i) a[i] = xd[i * 256];
+    double v[NT][4][NL];
+#pragma unroll
+    for (int u = 0; u < NT; ++u)
+#pragma unroll
+      for (int r = 0; r < 4; ++r) {
+        const int row = ch * kBlRows + k4 * 4 + r;
+        const bool in = row < p.N && rc0 + u * 16 + c16 < ncols;
+#pragma unroll
+        for (int l = 0; l < NL; ++l) v[u][r][l] = in ? src[u][l * plane + row] : 0.0;
+      }
+    __syncthreads();  // the previous chunk's digits are read
+#pragma unroll
+    for (int u = 0; u < NT; ++u) {
+      const int e[4] = {ex[u], ex[u], ex[u], ex[u]};
+      bl_put4<NL, ND>(v[u], e, reinterpret_cast<uint32_t*>(dig) + (u * ND * 16 + c16) * 16 + k4, 256);
+    }
+    __syncthreads();
+#pragma unroll
+    for (int u = 0; u < NT; ++u)
+#pragma unroll
+      for (int j = 0; j < ND; ++j) {
+        const bl_v4i b = dig[((u * ND + j) * 16 + (lane & 15)) * 4 + (lane >> 4)];
+#pragma unroll
+        for (int i = 0; i < ND; ++i)
+          if (i + j < ND) av[u][i + j] = __builtin_amdgcn_mfma_i32_16x16x64_i8(a[i], b, av[u][i + j], 0, 0, 0);
+      }
+  }
+#pragma unroll
+  for (int t = 0; t < NT; ++t)
+#pragma unroll
+    for (int d = 0; d < ND; ++d)
+#pragma unroll
+      for (int r = 0; r < 4; ++r) acc[t][d][r] = av[t][d][r];
+  double* Sp = reinterpret_cast<double*>(p.base + V.oS + split * (GRAM ? V.g_split : V.s_split));
+#pragma unroll
+  for (int u = 0; u < NT; ++u) {
+    const int rc = rc0 + u * 16 + (lane & 15);
+    const int col = rc / CX;
+    const int e = (GRAM ? 0 : col_exp(min(rc, ncols - 1) / CX)) - 12;
+    R<NO> val[4];
+#pragma unroll
+    for (int r = 0; r < 4; ++r) {
+      int t[ND];
+#pragma unroll
+      for (int d = 0; d < ND; ++d) t[d] = acc[u][d][r];
+      val[r] = bl_value<NO, ND>(t, e);
+    }
+    const int m = 16 * wave + 4 * (lane >> 4);
+    if constexpr (is_real(L)) {
+      if (rc < ncols)
+#pragma unroll
+        for (int r = 0; r < 4; ++r) r_store_aos(Sp + (size_t(col) * K::B + m + r) * width_of(LO), val[r]);
+    } else {
+      // neighbouring lanes hold the real and imaginary part of one column,
+      // neighbouring values those of one column of X:
+      // re = Xr.Ar + Xi.Ai, im = Xr.Ai - Xi.Ar
+      const int comp = lane & 1;
+#pragma unroll
+      for (int h = 0; h < 2; ++h) {
+        const R<NO> mine = val[2 * h + 1];
+        R<NO> other;
+#pragma unroll
+        for (int l = 0; l < NO; ++l) other.x[l] = __shfl_xor(mine.x[l], 1);
+        const R<NO> s = r_add(val[2 * h], comp ? r_neg(other) : other);
+        if (rc < ncols) r_store_aos(Sp + (size_t(col) * K::B + m / 2 + h) * width_of(LO) + comp * NO, s);
+      }
+    }
+  }
+}
+
+// ------------------------------------------------------------------ the panel's factor
+
+constexpr int kBlCholThreads = 512;
+
+// squared norm of a wavefront's rows of a column summed over the wavefront
+template <int NLV>
+__device__ __forceinline__ R<NLV> bl_wave_sum(R<NLV> s) {
+#pragma unroll
+  for (int m = 1; m < 64; m <<= 1) {
+    R<NLV> o;
+#pragma unroll
+    for (int l = 0; l < NLV; ++l) o.x[l] = __shfl_xor(s.x[l], m);
+    s = r_add(s, o);
+  }
+  return s;
+}
+
+// One sweep of modified Gram-Schmidt over the panel's columns in W by one
+// workgroup: each wavefront takes columns of its own, its lanes the rows.
+// Rr[i * B + j] gets R; the columns become orthonormal.  `rmin` is the
+// smallest ratio of a pivot to its column's norm before the sweep.  Returns
+// false when a pivot is numerically zero against *rmax (first sweep only).
+template <int L>
+__device__ bool bl_mgs_sweep(const BlProb& p, double* Wp, int k0, int bcur, double* Rr, double thresh, double* rmax,
+                             bool check, double* norm0, double* rmin) {
+  using K = Bl<L>;
+  constexpr int NL = K::NL;
+  const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6, nwave = kBlCholThreads / 64;
+  const int64_t plane = int64_t(p.n + 1) * p.N;
+  auto norm2 = [&](int c) {
+    R<NL> s = r_zero<NL>();
+    for (int i = lane; i < p.N; i += 64) s = r_add(s, c_norm2(load_planar<L>(Wp + int64_t(c) * p.N, plane, i)));
+    return bl_wave_sum<NL>(s);
+  };
+  for (int j = wave; j < bcur; j += nwave) {
+    const R<NL> s = norm2(k0 + j);
+    if (lane == 0) norm0[j] = sqrt(s.x[0]);
+  }
+  __syncthreads();
+  for (int k = 0; k < bcur; ++k) {
+    // every wavefront sums the pivot's norm itself (the same value in each)
+    const R<NL> r = r_sqrt(norm2(k0 + k));
+    if (check) {
+      *rmax = fmax(*rmax, r.x[0]);
+      if (!(r.x[0] > thresh * *rmax)) return false;  // uniform
+    }
+    *rmin = fmin(*rmin, r.x[0] / norm0[k]);
+    const R<NL> ir = r_recip(r);
+    __syncthreads();
+    for (int i = threadIdx.x; i < p.N; i += kBlCholThreads) {
+      double* c = Wp + int64_t(k0 + k) * p.N;
+      store_planar(c, plane, i, c_mul_r(load_planar<L>(c, plane, i), ir));
+    }
+    if (threadIdx.x == 0) store_aos(Rr + (size_t(k) * K::B + k) * K::W, c_from_r<L>(r));
+    __syncthreads();
+    const double* q = Wp + int64_t(k0 + k) * p.N;
+    for (int j = k + 1 + wave; j < bcur; j += nwave) {
+      double* a = Wp + int64_t(k0 + j) * p.N;
+      C<L> d = c_zero<L>();
+      for (int i = lane; i < p.N; i += 64)
+        d = c_add(d, c_mul_conj_a(load_planar<L>(q, plane, i), load_planar<L>(a, plane, i)));
+#pragma unroll
+      for (int m = 1; m < 64; m <<= 1) d = c_add(d, shfl_xor_c(d, m));
+      const C<L> nd = c_neg(d);
+      for (int i = lane; i < p.N; i += 64)
+        store_planar(a, plane, i, c_add(load_planar<L>(a, plane, i), c_mul(nd, load_planar<L>(q, plane, i))));
+      if (lane == 0) store_aos(Rr + (size_t(k) * K::B + j) * K::W, d);
+    }
+    __syncthreads();
+  }
+  return true;
+}
+
+// Factor of the panel's Gram matrix G (of the columns scaled by their
+// exponents): G = U^H D U, U unit upper triangular, in LDS, one barrier per
+// pivot: the thread of entry (i, j) subtracts conj(g_ki) (g_kj / d_k), so the
+// reciprocal of the pivot is the only serial step.  Square roots wait for the
+// end.  A pivot below kPivot of its column's squared norm would leave
+// E = X^H X - I too large for its first order (E is about u_C / pivot
+// ratio, u_C the unit roundoff of the factor's level): then the panel is
+// orthogonalised by modified Gram-Schmidt here, again if one sweep leaves
+// E above the square root of the level's roundoff.  One workgroup per
+// problem: it is bound by the chain of B pivots.
+template <int L>
+__global__ __launch_bounds__(kBlCholThreads) void bl_chol_kernel(BlView V, int panel, int cur, int nsplit) {
+  using K = Bl<L>;
+  constexpr int LC = K::LC, NC_ = limbs_of(LC), WC = K::WC, B = K::B, NL = K::NL;
+  using RC = R<NC_>;
+  extern __shared__ double lds[];
+  const BlProb p = bl_prob<L>(V, blockIdx.x);
+  BlMisc* misc = bl_at<BlMisc>(p, V.oMisc);
+  const int k0 = panel * B;
+  if (k0 >= p.n || misc->flag) return;
+  const int bcur = min(B, p.n - k0);
+  const int tid = threadIdx.x;
+  double* G = lds;                    // [B][B] numbers
+  double* g0 = G + size_t(B) * B * WC;  // [B] diagonal before the factorisation
+  double* dinv = g0 + B;              // [B][NC_] 1 / d
+  double* sq = dinv + B * NC_;        // [B][NC_] sqrt(d)
+  double* norm0 = sq + B * NC_;       // [B]
+  const int nch = (p.N + kBlRows - 1) / kBlRows;
+  const int ns = min(nsplit, nch);
+  const int* ce = bl_at<int>(p, V.oCe) + cur * V.nmax;
+  // S holds column j as [j][i]: entry (i, j) of the upper triangle
+  for (int idx = tid; idx < B * B; idx += kBlCholThreads) {
+    const int i = idx % B, j = idx / B;
+    if (i > j || j >= bcur) continue;
+    C<LC> g = c_zero<LC>();
+    for (int s = 0; s < ns; ++s) {
+      const double* Sp = reinterpret_cast<const double*>(p.base + V.oS + s * V.g_split);
+      const C<LC> t = load_aos<LC>(Sp + (size_t(j) * B + i) * WC);
+      g = s == 0 ? t : c_add(g, t);
+    }
+    store_aos(G + (size_t(i) * B + j) * WC, g);
+    if (i == j) g0[i] = g.re.x[0];
+  }
+  bool nonfinite = false;
+  for (int j = 0; j < bcur; ++j) nonfinite |= ce[k0 + j] == 0x7ff;
+  if (nonfinite) {  // uniform
+    if (tid == 0) misc->flag = 1;
+    return;
+  }
+  constexpr double kPivot = NL == 1 ? 0x1p-26 : 0x1p-46;
+  bool bad = false;
+  for (int k = 0; k < bcur; ++k) {
+    __syncthreads();
+    const RC d = load_aos<LC>(G + (size_t(k) * B + k) * WC).re;
+    if (!(d.x[0] > kPivot * g0[k])) {
+      bad = true;
+      break;  // uniform
+    }
+    const RC inv = r_recip(d);
+    if (tid == 0) r_store_aos(dinv + k * NC_, inv);
+    const int m = bcur - 1 - k;  // trailing rows and columns
+    for (int idx = tid; idx < m * m; idx += kBlCholThreads) {
+      const int i = k + 1 + idx / m, j = k + 1 + idx % m;
+      if (j < i) continue;
+      const C<LC> f = c_mul_r(load_aos<LC>(G + (size_t(k) * B + j) * WC), inv);
+      const C<LC> t = c_mul_conj_a(load_aos<LC>(G + (size_t(k) * B + i) * WC), f);
+      double* g = G + (size_t(i) * B + j) * WC;
+      C<LC> u = c_sub(load_aos<LC>(g), t);
+      store_aos(g, u);
+    }
+  }
+  __syncthreads();
+  const double thresh = double(p.n) * level_unit<L>();
+  double* U = bl_at<double>(p, V.oU);    // [B][B] then [B][NL] 1 / sqrt(d)
+  double* Rp = bl_at<double>(p, V.oRp);  // [B][B], then B column exponents
+  int* rexp = reinterpret_cast<int*>(Rp + size_t(B) * B * K::W);
+  double rmax = misc->rmax;
+  if (!bad) {
+    double* is = U + size_t(B) * B * K::W;
+    if (tid < B) {
+      const RC d = tid < bcur ? load_aos<LC>(G + (size_t(tid) * B + tid) * WC).re : r_from_double<NC_>(1.0);
+      const RC s = r_sqrt(d);
+      r_store_aos(sq + tid * NC_, s);
+      const RC q = r_recip(s);
+#pragma unroll
+      for (int l = 0; l < NL; ++l) is[tid * NL + l] = q.x[l];
+      rexp[tid] = tid < bcur ? ce[k0 + tid] - kExpOne : 0;
+    }
+    __syncthreads();
+    bool singular = false;
+    for (int j = 0; j < bcur; ++j) {
+      const double r = __builtin_ldexp(sq[j * NC_], ce[k0 + j] - kExpOne);
+      rmax = fmax(rmax, r);
+      if (!(r > thresh * rmax)) singular = true;
+    }
+    if (singular) {
+      if (tid == 0) misc->flag = 1;
+      return;
+    }
+    for (int idx = tid; idx < B * B; idx += kBlCholThreads) {
+      const int i = idx / B, j = idx % B;
+      C<LC> u = c_zero<LC>();
+      C<LC> r = u;
+      const RC s = r_load_aos<NC_>(sq + i * NC_);
+      if (i == j) {
+        r = c_from_r<LC>(s);
+      } else if (i < j && j < bcur) {
+        u = c_mul_r(load_aos<LC>(G + (size_t(i) * B + j) * WC), r_load_aos<NC_>(dinv + i * NC_));
+        // the factor as the substitution takes it (rounded to the level)
+        const C<L> un = bl_narrow<L>(u);
+        C<LC> w = c_zero<LC>();
+#pragma unroll
+        for (int l = 0; l < NL; ++l) {
+          w.re.x[l] = un.re.x[l];
+          if constexpr (!is_real(L)) w.im.x[l] = un.im.x[l];
+        }
+        r = c_mul_r(w, s);
+      }
+      store_aos(U + size_t(idx) * K::W, bl_narrow<L>(u));
+      store_aos(Rp + size_t(idx) * K::W, bl_narrow<L>(r));
+    }
+    if (tid == 0) {
+      misc->rmax = rmax;
+      misc->mgs = 0;
+    }
+    return;
+  }
+  // modified Gram-Schmidt on the panel itself
+  double* Wp = bl_at<double>(p, V.oW);
+  for (int idx = tid; idx < B * B; idx += kBlCholThreads) {
+    store_aos(Rp + size_t(idx) * K::W, c_zero<L>());
+    store_aos(U + size_t(idx) * K::W, c_zero<L>());
+  }
+  if (tid < B) rexp[tid] = 0;
+  __syncthreads();
+  double rmin = 1.0;
+  if (!bl_mgs_sweep<L>(p, Wp, k0, bcur, Rp, thresh, &rmax, true, norm0, &rmin)) {
+    if (tid == 0) misc->flag = 1;
+    return;
+  }
+  if (rmin < (NL == 1 ? 0x1p-20 : (NL == 2 ? 0x1p-40 : 0x1p-44))) {
+    // again: R = R2 R1 (R2 into U's place, then the product)
+    double unused = 1.0;
+    bl_mgs_sweep<L>(p, Wp, k0, bcur, U, 0.0, &unused, false, norm0, &unused);
+    __syncthreads();
+    // entry (i, j) = sum over m = i .. j of R2[i][m] R1[m][j]: a thread owns a
+    // column and goes down it, since entry (i, j) needs R1[m][j] for m >= i only
+    for (int j = tid; j < bcur; j += kBlCholThreads)
+      for (int i = 0; i <= j; ++i) {
+        C<L> s = c_zero<L>();
+        for (int m = i; m <= j; ++m)
+          s = c_add(s, c_mul(load_aos<L>(U + (size_t(i) * B + m) * K::W), load_aos<L>(Rp + (size_t(m) * B + j) * K::W)));
+        store_aos(Rp + (size_t(i) * B + j) * K::W, s);
+      }
+  }
+  if (tid == 0) {
+    misc->rmax = rmax;
+    misc->mgs = 1;
+  }
+}
+
+template <int L>
+__host__ __device__ inline size_t bl_chol_lds() {
+  using K = Bl<L>;
+  return (size_t(K::B) * K::B * K::WC + K::B * (2 + 2 * limbs_of(K::LC))) * sizeof(double);
+}
+
+// ------------------------------------------------------------------ X = A U^-1 D^-1/2
+
+// Rows of X by forward substitution: a group of B lanes holds a row, lane j
+// its column j; step i broadcasts entry i and the lanes j > i subtract
+// a_i u_ij.  X replaces the panel in W; its digits are written in the two
+// orders the products read: XD (rows contiguous, fixed point against 1) for
+// the contraction and XU ([chunk][digit][row][64 real columns], against the
+// row's largest entry, so that a small row keeps its relative precision) for
+// the update.  Bound by the chain of B steps: few rows per workgroup, so that
+// it spreads over the chip.  grid (64-row chunks * 64 / rows per workgroup,
+// slots), 256 threads
+template <int L>
+__global__ __launch_bounds__(256) void bl_solve_kernel(BlView V, int panel, int cur) {
+  using K = Bl<L>;
+  constexpr int B = K::B, NL = K::NL, ND = K::ND, CX = K::CX, RPW = 256 / B;
+  extern __shared__ double lds[];
+  const BlProb p = bl_prob<L>(V, blockIdx.y);
+  const BlMisc* misc = bl_at<BlMisc>(p, V.oMisc);
+  const int k0 = panel * B, r0 = blockIdx.x * RPW;
+  const int NC = (p.N + kBlRows - 1) / kBlRows;
+  if (k0 >= p.n || r0 >= NC * kBlRows || misc->flag) return;
+  const int bcur = min(B, p.n - k0);
+  double* Us = lds;                             // [B][B] numbers
+  double* xs = lds + size_t(B) * B * K::W;      // [RPW][64][NL] results
+  int* er = reinterpret_cast<int*>(xs + RPW * 64 * NL);  // [RPW] row exponents
+  const double* U = bl_at<double>(p, V.oU);
+  double* Wp = bl_at<double>(p, V.oW);
+  const int64_t plane = int64_t(p.n + 1) * p.N;
+  const int tid = threadIdx.x, j = tid % B, rr = tid / B;
+  const int row = r0 + rr;
+  const bool live = row < p.N && j < bcur;
+  const bool mgs = misc->mgs != 0;
+  C<L> a = live ? load_planar<L>(Wp + int64_t(k0 + j) * p.N, plane, row) : c_zero<L>();
+  if (!mgs) {
+    // entry (i, j) of component k at [i][k][j]: the lanes of a row read
+    // consecutive words
+    for (int idx = tid; idx < B * B * K::W; idx += 256) {
+      const int k = idx % K::W, ij = idx / K::W;
+      Us[(size_t(ij / B) * K::W + k) * B + ij % B] = U[idx];
+    }
+    const double* is = U + size_t(B) * B * K::W;
+    R<NL> inv;
+#pragma unroll
+    for (int l = 0; l < NL; ++l) inv.x[l] = is[j * NL + l];
+    if (live) a = bl_ldexp(a, -(bl_at<int>(p, V.oCe)[cur * V.nmax + k0 + j] - kExpOne));
+    __syncthreads();
+    for (int i = 0; i + 1 < bcur; ++i) {
+      C<L> ai;
+#pragma unroll
+      for (int l = 0; l < NL; ++l) {
+        ai.re.x[l] = __shfl(a.re.x[l], i, B);
+        if constexpr (!is_real(L)) ai.im.x[l] = __shfl(a.im.x[l], i, B);
+      }
+      const C<L> u = load_planar<L>(Us + size_t(i) * K::W * B, B, j);
+      // u is zero for j <= i
+      if (j > i) a = c_sub(a, c_mul(ai, u));
+    }
+    a = c_mul_r(a, inv);
+    if (live) store_planar(Wp + int64_t(k0 + j) * p.N, plane, row, a);
+  }
+  int e = live ? max(bl_exp(a.re.x[0]), bl_exp(im_lead(a))) : 0;
+#pragma unroll
+  for (int m = 1; m < B; m <<= 1) e = max(e, __shfl_xor(e, m));
+#pragma unroll
+  for (int l = 0; l < NL; ++l) {
+    xs[(rr * 64 + j * CX) * NL + l] = a.re.x[l];
+    if constexpr (!is_real(L)) xs[(rr * 64 + j * CX + 1) * NL + l] = a.im.x[l];
+  }
+  if (j == 0) {
+    er[rr] = e - kExpOne;
+    bl_at<int>(p, V.oXr)[row] = e - kExpOne;
+  }
+  __syncthreads();
+  const int ch = r0 / kBlRows, rin = r0 % kBlRows;
+  uint32_t* xd = bl_at<uint32_t>(p, V.oXD) + size_t(ch) * ND * 1024;
+  uint32_t* xu = bl_at<uint32_t>(p, V.oXU) + size_t(ch) * ND * 1024;
+  for (int t = tid; t < 64 * (RPW / 4) + RPW * 16; t += 256) {
+    double v[4][NL];
+    int ev[4];
+    uint32_t* dst;
+    if (t < 64 * (RPW / 4)) {
+      const int m = t & 63, g = t >> 6;
+#pragma unroll
+      for (int r = 0; r < 4; ++r) {
+        ev[r] = 0;
+#pragma unroll
+        for (int l = 0; l < NL; ++l) v[r][l] = xs[((4 * g + r) * 64 + m) * NL + l];
+      }
+      dst = xd + m * 16 + (rin / 4 + g);
+    } else {
+      const int q = t - 64 * (RPW / 4), m4 = q & 15, r2 = q >> 4;
+#pragma unroll
+      for (int r = 0; r < 4; ++r) {
+        ev[r] = er[r2];
+#pragma unroll
+        for (int l = 0; l < NL; ++l) v[r][l] = xs[(r2 * 64 + m4 * 4 + r) * NL + l];
+      }
+      dst = xu + (rin + r2) * 16 + m4;
+    }
+    bl_put4<NL, ND>(v, ev, dst, 1024);
+  }
+}
+
+template <int L>
+__host__ __device__ inline size_t bl_solve_lds() {
+  using K = Bl<L>;
+  return (size_t(K::B) * K::B * K::W + (256 / K::B) * 64 * K::NL) * sizeof(double) + (256 / K::B) * sizeof(int);
+}
+
+// ------------------------------------------------------------------ R and T
+
+// Columns of S summed over the row splits; the panel's rows of R; T = (I - E) S
+// in digits ([tile][digit][16 real columns][64] bytes, real column 2 c
+// holding (Tr, -Ti) and 2 c + 1 (Ti, Tr) of the B pairs, so that the update
+// is one real product); the exponents of the next panel's columns cleared.
+// For the panel's own columns R = (I + F) D^1/2 U instead.  E is at most
+// 2^-58, so its products need no more than double arithmetic.  grid (column
+// groups, slots), 256 threads: B lanes per column
+template <int L>
+__global__ __launch_bounds__(256) void bl_fin_kernel(BlView V, int panel, int cur, int nsplit) {
+  using K = Bl<L>;
+  constexpr int B = K::B, NL = K::NL, ND = K::ND, NW = K::NW, CX = K::CX, W = K::W, CPW = 256 / B;
+  __shared__ double E[B * B * CX];    // [i][j]
+  __shared__ double sl[CPW * B * CX];  // leading limbs of the columns of S
+  const BlProb p = bl_prob<L>(V, blockIdx.y);
+  const int k0 = panel * B;
+  if (k0 >= p.n || bl_at<BlMisc>(p, V.oMisc)->flag) return;
+  const int bcur = min(B, p.n - k0);
+  const int c0 = blockIdx.x * CPW;
+  if (k0 + c0 > p.n) return;
+  const int ns = min(nsplit, (p.N + kBlRows - 1) / kBlRows);
+  const int tid = threadIdx.x;
+  auto sum = [&](int c, int i) {
+    C<L> s = c_zero<L>();
+    for (int t = 0; t < ns; ++t) {
+      const C<L> v =
+          load_aos<L>(reinterpret_cast<const double*>(p.base + V.oS + t * V.s_split) + (size_t(c) * B + i) * W);
+      s = t == 0 ? v : c_add(s, v);
+    }
+    return s;
+  };
+  for (int idx = tid; idx < B * B; idx += 256) {
+    const int j = idx / B, i = idx % B;
+    double re = 0.0, im = 0.0;
+    if (i < bcur && j < bcur) {
+      C<L> s = sum(j, i);
+      if (i == j) s.re = r_sub(s.re, r_from_double<NL>(1.0));
+      re = s.re.x[0];
+      im = im_lead(s);
+    }
+    E[(i * B + j) * CX] = re;
+    if (CX == 2) E[(i * B + j) * CX + 1] = im;
+  }
+  const int cl = tid / B, i = tid % B;
+  const int c = c0 + cl, col = k0 + c;
+  const bool in = col <= p.n;
+  const bool own = in && c < bcur;
+  C<L> s = in ? (own ? c_zero<L>() : sum(c, i)) : c_zero<L>();
+  sl[tid * CX] = s.re.x[0];
+  if (CX == 2) sl[tid * CX + 1] = im_lead(s);
+  __syncthreads();
+  if (panel * B < p.n && blockIdx.x == 0)
+    for (int idx = tid; idx < B * B * CX; idx += 256) bl_at<double>(p, V.oF)[size_t(panel) * B * B * CX + idx] = E[idx];
+  double* R = bl_at<double>(p, V.oR);
+  const int64_t rplane = int64_t(p.n + 1) * p.n;
+  int* ce = bl_at<int>(p, V.oCe);
+  auto e_at = [&](int a, int b, double& re, double& im) {
+    re = E[(a * B + b) * CX];
+    im = CX == 2 ? E[(a * B + b) * CX + 1] : 0.0;
+  };
+  if (own) {
+    if (i <= c) {
+      const double* Rp = bl_at<double>(p, V.oRp);
+      const int* rexp = reinterpret_cast<const int*>(Rp + size_t(B) * B * W);
+      C<L> r = load_aos<L>(Rp + (size_t(i) * B + c) * W);
+      double fr = 0.0, fi = 0.0;
+      for (int m = i; m <= c; ++m) {
+        const double* q = Rp + (size_t(m) * B + c) * W;
+        const double qr = q[0], qi = CX == 2 ? q[(CX - 1) * NL] : 0.0;
+        double er, ei;
+        e_at(i, m, er, ei);
+        if (m == i) {
+          er *= 0.5;
+          ei = 0.0;
+        }
+        fr += er * qr - ei * qi;
+        fi += er * qi + ei * qr;
+      }
+      C<L> f = c_zero<L>();
+      f.re.x[0] = fr;
+      if constexpr (!is_real(L)) f.im.x[0] = i == c ? 0.0 : fi;
+      r = bl_ldexp(c_add(r, f), rexp[c]);
+      store_planar(R + int64_t(col) * p.n, rplane, k0 + i, r);
+      if (i == c) {
+        const auto inv = r_recip(r.re);
+        r_store_aos(bl_at<double>(p, V.oInv) + size_t(col) * NL, inv);
+      }
+    }
+    return;
+  }
+  if (!in) return;
+  // lanes of one column are neighbours: B of them
+  double lr = 0.0, li = 0.0, hr = 0.0, hi = 0.0;  // sums over j < i (with half of j = i) and over all j
+  for (int j = 0; j < bcur; ++j) {
+    // E is Hermitian: E_ij read as conj(E_ji), consecutive over the lanes
+    double er, ei;
+    e_at(j, i, er, ei);
+    ei = -ei;
+    const double sr = sl[(cl * B + j) * CX], si = CX == 2 ? sl[(cl * B + j) * CX + 1] : 0.0;
+    const double tr = er * sr - ei * si, ti = er * si + ei * sr;
+    hr += tr;
+    hi += ti;
+    if (j < i) {
+      lr += tr;
+      li += ti;
+    } else if (j == i) {
+      lr += 0.5 * tr;
+      li += 0.5 * ti;
+    }
+  }
+  auto minus = [](const C<L>& v, double re, double im) {
+    C<L> f = c_zero<L>();
+    f.re.x[0] = -re;
+    if constexpr (!is_real(L)) f.im.x[0] = -im;
+    return c_add(v, f);
+  };
+  C<L> r = minus(s, lr, li);
+  if (ce[cur * V.nmax + col] == 0x7ff) {
+    // a column with a value that is not finite has no projection
+    const double nan = __builtin_nan("");
+    for (int l = 0; l < NL; ++l) {
+      r.re.x[l] = nan;
+      if constexpr (!is_real(L)) r.im.x[l] = nan;
+    }
+  }
+  if (i < bcur) store_planar(R + int64_t(col) * p.n, rplane, k0 + i, r);
+  const C<L> t = minus(s, hr, hi);
+  int e = max(bl_exp(t.re.x[0]), bl_exp(im_lead(t)));
+#pragma unroll
+  for (int m = 1; m < B; m <<= 1) e = max(e, __shfl_xor(e, m));
+  if (i == 0) {
+    bl_at<int>(p, V.oSe)[c] = e - kExpOne;
+    ce[(1 - cur) * V.nmax + col] = 0;
+  }
+  uint32_t wr[NW], wi[NW], wn[NW];
+  bl_digits<NL, ND>(t.re.x, e - kExpOne, wr);
+  char* sd = bl_at<char>(p, V.oSD);
+  if constexpr (is_real(L)) {
+    char* dst = sd + size_t(c / 16) * ND * 1024 + (c % 16) * 64 + i;
+#pragma unroll
+    for (int d = 0; d < ND; ++d) dst[d * 1024] = char(wr[d / 4] >> (8 * (3 - d % 4)));
+  } else {
+    bl_digits<NL, ND>(t.im.x, e - kExpOne, wi);
+    bl_digits<NL, ND>(r_neg(t.im).x, e - kExpOne, wn);
+    const int rc = 2 * c;
+    char* dst = sd + size_t(rc / 16) * ND * 1024 + (rc % 16) * 64 + 2 * i;
+#pragma unroll
+    for (int d = 0; d < ND; ++d) {
+      const int sh = 8 * (3 - d % 4);
+      const uint32_t a = (wr[d / 4] >> sh) & 255u, b = (wi[d / 4] >> sh) & 255u, n = (wn[d / 4] >> sh) & 255u;
+      *reinterpret_cast<uint16_t*>(dst + d * 1024) = uint16_t(a | (n << 8));
+      *reinterpret_cast<uint16_t*>(dst + d * 1024 + 64) = uint16_t(b | (a << 8));
+    }
+  }
+}
+
+// ------------------------------------------------------------------ trailing update
+
+// Columns behind the panel -= X T.  A workgroup keeps the digits of 64 rows of
+// X (16 per wavefront) in registers and walks column tiles of 16 real
+// columns, whose digits of T it reads from the cache; K is the panel's 64
+// real columns, one matrix instruction.  Also the largest exponent of every
+// updated column.  grid (chunks, column groups, slots), 256 threads
+template <int L>
+__global__ __launch_bounds__(256, limbs_of(L) == 4 ? 1 : 2) void bl_update_kernel(BlView V, int panel, int cur, int tiles_per) {
+  using K = Bl<L>;
+  constexpr int NL = K::NL, ND = K::ND, CX = K::CX, B = K::B;
+  const BlProb p = bl_prob<L>(V, blockIdx.z);
+  const int k0 = panel * B, k1 = k0 + B;
+  const int ch = blockIdx.x;
+  if (k1 >= p.n || ch * kBlRows >= p.N || bl_at<BlMisc>(p, V.oMisc)->flag) return;
+  // tiles count from the panel's first column; its own 64 real columns are 4 tiles
+  const int ntiles = ((p.n + 1 - k0) * CX + 15) / 16;
+  const int t0 = 4 + blockIdx.y * tiles_per, t1 = min(ntiles, t0 + tiles_per);
+  if (t0 >= t1) return;
+  const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
+  const int64_t plane = int64_t(p.n + 1) * p.N;
+  double* Wp = bl_at<double>(p, V.oW);
+  int* ce = bl_at<int>(p, V.oCe) + (1 - cur) * V.nmax;
+  const int* se = bl_at<int>(p, V.oSe);
+  const bl_v4i* xu = bl_at<bl_v4i>(p, V.oXU) + size_t(ch) * ND * 256 + (16 * wave + (lane & 15)) * 4 + (lane >> 4);
+  bl_v4i a[ND];
+#pragma unroll
+  for (int i = 0; i < ND; ++i) a[i] = xu[i * 256];
+  const int row0 = ch * kBlRows + 16 * wave + 4 * (lane >> 4);
+  int er[4];
+#pragma unroll
+  for (int r = 0; r < 4; ++r) er[r] = bl_at<int>(p, V.oXr)[row0 + r] - 12;
+  for (int t = t0; t < t1; ++t) {
+    const bl_v4i* sd = bl_at<bl_v4i>(p, V.oSD) + size_t(t) * ND * 64 + (lane & 15) * 4 + (lane >> 4);
+    const int rc = t * 16 + (lane & 15);
+    const int c = rc / CX, col = k0 + c;
+    const bool in = col <= p.n;
+    double* dst = Wp + int64_t(rc % CX) * NL * plane + int64_t(in ? col : p.n) * p.N;
+    double old[4][NL];
+#pragma unroll
+    for (int r = 0; r < 4; ++r)
+#pragma unroll
+      for (int l = 0; l < NL; ++l) old[r][l] = (in && row0 + r < p.N) ? dst[l * plane + row0 + r] : 0.0;
+    bl_v4i av[ND];
+#pragma unroll
+    for (int d = 0; d < ND; ++d) av[d] = bl_v4i{0, 0, 0, 0};
+#pragma unroll
+    for (int j = 0; j < ND; ++j) {
+      const bl_v4i b = sd[j * 64];
+#pragma unroll
+      for (int i = 0; i < ND; ++i)
+        if (i + j < ND) av[i + j] = __builtin_amdgcn_mfma_i32_16x16x64_i8(a[i], b, av[i + j], 0, 0, 0);
+    }
+    const int es = in ? se[c] : 0;
+    int emax = 0;
+#pragma unroll
+    for (int r = 0; r < 4; ++r) {
+      int tt[ND];
+#pragma unroll
+      for (int d = 0; d < ND; ++d) tt[d] = av[d][r];
+      const R<NL> v = bl_value<NL, ND>(tt, es + er[r]);
+      R<NL> o;
+#pragma unroll
+      for (int l = 0; l < NL; ++l) o.x[l] = old[r][l];
+      const R<NL> w = r_sub(o, v);
+      if (in && row0 + r < p.N) {
+#pragma unroll
+        for (int l = 0; l < NL; ++l) dst[l * plane + row0 + r] = w.x[l];
+        emax = max(emax, bl_exp(w.x[0]));
+      }
+    }
+    emax = max(emax, __shfl_xor(emax, 16));
+    emax = max(emax, __shfl_xor(emax, 32));
+    if (CX == 2) emax = max(emax, __shfl_xor(emax, 1));
+    if (in && lane < 16 && (CX == 1 || (lane & 1) == 0)) atomicMax(ce + col, emax);
+  }
+}
+
+// ------------------------------------------------------------------ back substitution
+
+constexpr int kBlBsThreads = 512;
+
+// Diagonal block `stage` (of kBlBs rows, from the bottom) of R x = y, in
+// sub-blocks of 32 rows: a wavefront solves the sub-block (its triangle staged
+// in LDS, x_j broadcast from lane to lanes), then all threads subtract its
+// columns from the block's rows above.  grid (slots), 512 threads
+template <int L>
+__global__ __launch_bounds__(kBlBsThreads) void bl_bs_diag_kernel(BlView V, int stage) {
+  constexpr int NL = limbs_of(L), W = width_of(L), SB = 32;
+  __shared__ double tri[SB * W * SB];  // [column][component][row]
+  __shared__ double y[kBlBs * W];
+  const BlProb p = bl_prob<L>(V, blockIdx.x);
+  if (bl_at<BlMisc>(p, V.oMisc)->flag) return;
+  const int e = p.n - stage * kBlBs;
+  if (e <= 0) return;
+  const int s = max(0, e - kBlBs);
+  const int tid = threadIdx.x;
+  const int64_t rplane = int64_t(p.n + 1) * p.n;
+  const double* Rm = bl_at<double>(p, V.oR);
+  double* yw = bl_at<double>(p, V.oY);
+  const double* inv = bl_at<double>(p, V.oInv);
+  if (tid < e - s) {
+    const C<L> v = stage == 0 ? load_planar<L>(Rm + int64_t(p.n) * p.n, rplane, s + tid) : load_planar<L>(yw, p.n, s + tid);
+    store_planar(y, kBlBs, tid, v);
+  }
+  for (int se = e; se > s; se -= SB) {
+    const int ss = max(s, se - SB), sb = se - ss;
+    __syncthreads();
+    for (int idx = tid; idx < SB * SB; idx += kBlBsThreads) {
+      const int jj = idx / SB, ii = idx % SB;
+      if (jj < sb && ii < jj)
+        store_planar(tri + jj * W * SB, SB, ii, load_planar<L>(Rm + int64_t(ss + jj) * p.n, rplane, ss + ii));
+    }
+    __syncthreads();
+    if (tid < 64) {
+      const int ii = tid & (SB - 1);
+      C<L> v = ii < sb ? load_planar<L>(y, kBlBs, ss - s + ii) : c_zero<L>();
+      R<NL> dv = r_zero<NL>();
+      if (ii < sb) dv = r_load_aos<NL>(inv + size_t(ss + ii) * NL);
+      for (int jj = sb - 1; jj >= 0; --jj) {
+        const C<L> mine = c_mul_r(v, dv);
+        C<L> xj;
+#pragma unroll
+        for (int l = 0; l < NL; ++l) {
+          xj.re.x[l] = __shfl(mine.re.x[l], jj, SB);
+          if constexpr (!is_real(L)) xj.im.x[l] = __shfl(mine.im.x[l], jj, SB);
+        }
+        if (ii == jj) {
+          if (tid < SB) store_planar(y, kBlBs, ss - s + ii, xj);
+        } else if (ii < jj) {
+          v = c_sub(v, c_mul(load_planar<L>(tri + jj * W * SB, SB, ii), xj));
+        }
+      }
+    }
+    __syncthreads();
+    // rows above inside the block: two threads per row, even and odd columns
+    const int rows = ss - s, i = tid >> 1, h = tid & 1;
+    C<L> acc = c_zero<L>();
+    if (i < rows)
+      for (int jj = h; jj < sb; jj += 2)
+        acc = c_add(acc, c_mul(load_planar<L>(Rm + int64_t(ss + jj) * p.n, rplane, s + i),
+                               load_planar<L>(y, kBlBs, ss - s + jj)));
+    acc = c_add(acc, shfl_xor_c(acc, 1));
+    if (i < rows && h == 0) store_planar(y, kBlBs, i, c_sub(load_planar<L>(y, kBlBs, i), acc));
+  }
+  __syncthreads();
+  if (tid < e - s) store_planar(yw, p.n, s + tid, load_planar<L>(y, kBlBs, tid));
+}
+
+// y[0, s) -= R[0:s, s:e] x[s:e] for the block `stage` just solved: eight
+// lanes per row, their columns added pairwise.  grid (row blocks of 32,
+// slots), 256 threads
+template <int L>
+__global__ __launch_bounds__(256) void bl_bs_update_kernel(BlView V, int stage) {
+  __shared__ double xs[kBlBs * width_of(L)];
+  const BlProb p = bl_prob<L>(V, blockIdx.y);
+  if (bl_at<BlMisc>(p, V.oMisc)->flag) return;
+  const int e = p.n - stage * kBlBs;
+  const int s = e - kBlBs;
+  const int r0 = blockIdx.x * 32;
+  if (s <= 0 || r0 >= s) return;
+  const int tid = threadIdx.x;
+  const int64_t rplane = int64_t(p.n + 1) * p.n;
+  const double* R = bl_at<double>(p, V.oR);
+  double* yw = bl_at<double>(p, V.oY);
+  store_planar(xs, kBlBs, tid, load_planar<L>(yw, p.n, s + tid));
+  __syncthreads();
+  // lanes of a wavefront: 32 rows x 2 column halves; the wavefronts take
+  // quarters of the columns
+  const int i = r0 + (tid & 31), part = tid >> 5;
+  C<L> acc = c_zero<L>();
+  if (i < s)
+    for (int j = part * (kBlBs / 8); j < (part + 1) * (kBlBs / 8); ++j)
+      acc = c_add(acc, c_mul(load_planar<L>(R + int64_t(s + j) * p.n, rplane, i), load_planar<L>(xs, kBlBs, j)));
+  __syncthreads();
+  double* red = xs;  // [8][32] numbers
+  store_planar(red, kBlBs, tid, acc);
+  __syncthreads();
+  if (tid < 32 && i < s) {
+    C<L> t = load_planar<L>(red, kBlBs, tid);
+    for (int q = 1; q < 8; ++q) t = c_add(t, load_planar<L>(red, kBlBs, q * 32 + tid));
+    const C<L> old =
+        stage == 0 ? load_planar<L>(R + int64_t(p.n) * p.n, rplane, i) : load_planar<L>(yw, p.n, i);
+    store_planar(yw, p.n, i, c_sub(old, t));
+  }
+}
+
+// x (+)= dx, dx = 0 when a pivot was zero; resid[1] = |dx|_inf or -1.  grid
+// (slots), 256 threads
+template <int L>
+__global__ __launch_bounds__(256) void bl_finish_kernel(BlView V) {
+  __shared__ double red[256];
+  const BlProb p = bl_prob<L>(V, blockIdx.x);
+  const int tid = threadIdx.x;
+  const bool singular = bl_at<BlMisc>(p, V.oMisc)->flag != 0;
+  double dmax = 0.0;
+  for (int j = tid; j < p.n; j += 256) {
+    const C<L> d = singular ? c_zero<L>() : load_planar<L>(bl_at<double>(p, V.oY), p.n, j);
+    if (!(singular && V.add)) store_planar(p.x, p.n, j, V.add ? c_add(load_planar<L>(p.x, p.n, j), d) : d);
+    dmax = fmax(dmax, fmax(fabs(d.re.x[0]), fabs(im_lead(d))));
+  }
+  red[tid] = dmax;
+  __syncthreads();
+  for (int k = 128; k > 0; k >>= 1) {
+    if (tid < k) red[tid] = fmax(red[tid], red[tid + k]);
+    __syncthreads();
+  }
+  if (tid == 0 && p.resid) p.resid[1] = singular ? -1.0 : red[0];
+}
+
+// R (row-major [P][components][n][n + 1], zeros below the diagonal) and
+// Q = X (I - F) ([P][components][N][n]).  A group of lanes takes a row of a
+// panel of Q.  grid (blocks, slots), 256 threads
+template <int L>
+__global__ __launch_bounds__(256) void bl_export_kernel(BlView V) {
+  using K = Bl<L>;
+  constexpr int B = K::B, CX = K::CX, NL = K::NL;
+  const BlProb p = bl_prob<L>(V, blockIdx.y);
+  const int64_t idx = int64_t(blockIdx.x) * 256 + threadIdx.x;
+  const int64_t pt = V.q0 + blockIdx.y;
+  const int ncol = p.n + 1;
+  const int64_t rplane = int64_t(ncol) * p.n;
+  if (V.Rout && idx < rplane) {
+    const int i = int(idx / ncol), j = int(idx - int64_t(i) * ncol);
+    const C<L> r =
+        i <= j ? load_planar<L>(bl_at<double>(p, V.oR) + int64_t(j) * p.n, rplane, i) : c_zero<L>();
+    store_planar(V.Rout + pt * (int64_t(K::W) * rplane), rplane, idx, r);
+  }
+  if (V.Qout && idx < int64_t(p.N) * p.n) {
+    // consecutive threads take consecutive columns of a row of Q
+    const int i = int(idx / p.n), c = int(idx - int64_t(i) * p.n);
+    const int k0 = c / B * B, cc = c - k0;
+    const int64_t plane = int64_t(ncol) * p.N;
+    const double* X = bl_at<double>(p, V.oW) + i;
+    const double* F = bl_at<double>(p, V.oF) + size_t(c / B) * B * B * CX;
+    double fr = 0.0, fi = 0.0;
+    for (int m = 0; m <= cc; ++m) {
+      const double xr = X[int64_t(k0 + m) * p.N], xi = CX == 2 ? X[(CX - 1) * NL * plane + int64_t(k0 + m) * p.N] : 0.0;
+      double er = F[(m * B + cc) * CX], ei = CX == 2 ? F[(m * B + cc) * CX + CX - 1] : 0.0;
+      if (m == cc) {
+        er *= 0.5;
+        ei = 0.0;
+      }
+      fr += xr * er - xi * ei;
+      fi += xr * ei + xi * er;
+    }
+    C<L> f = c_zero<L>();
+    f.re.x[0] = -fr;
+    if constexpr (!is_real(L)) f.im.x[0] = -fi;
+    const C<L> q = c_add(load_planar<L>(X + int64_t(c) * p.N, plane, 0), f);
+    store_planar(V.Qout + pt * (int64_t(K::W) * p.N * p.n), int64_t(p.N) * p.n, idx, q);
+  }
+}
+
+}  // namespace pe

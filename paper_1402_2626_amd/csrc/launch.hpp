@@ -7,8 +7,8 @@
 
 #include <algorithm>
 
+#include "blockls_kernels.hpp"
 #include "eval_kernels.hpp"
-#include "lstsq_kernels.hpp"
 #include "newton_kernels.hpp"
 
 namespace pe {
@@ -76,28 +76,15 @@ template <int L>
 hipError_t launch_batch(const BatchShape& b, int P, const double* x, const BatchOut& out, int mode,
                         hipStream_t st);
 template <int L>
-hipError_t launch_mgs(int P, int N, int n, double* W, int64_t w_pt, double* R, int64_t r_pt, double* Y,
-                      int64_t y_pt, double* x, double* resid, hipStream_t st);
-template <int L>
-hipError_t launch_mgs_batch(int S, int P, int maxN, const BatchNewtonDesc* desc, const int* order, double* W,
-                            double* R, double* Y, double* x, double* resid, hipStream_t st);
-
-template <int L>
 hipError_t launch_rhs_shift(double* W, int64_t w_pt, int64_t plane, int64_t ld, int N, int n, int P, const double* c,
                             double wF, double wc, hipStream_t st);
 
-// Column-parallel least-squares solve of the augmented matrices [A b] given
-// row-major at A (row stride ld, component plane stride a_plane, point stride
-// a_pt; see lstsq_kernels.hpp), writing x (x_pt per point; add = 1 adds the
-// solution to x, the Newton update), resid[P][2] and optionally R and Q.
-// PE panel of pivots per launch: kLsPanel.
-constexpr int kLsPanel = 32;
-constexpr int kLsMaxRows = 4096;  // N limit of the column-parallel solve
+// Least-squares solve (blockls_kernels.hpp) of `slots` problems of at most
+// Nm rows and nm unknowns, whose workspace slots V.ws holds.
+constexpr int kLsMaxRows = 4096;  // N limit of the solve beyond 127 unknowns
 
 template <int L>
-hipError_t launch_lstsq(const LsLayout& lo, void* ws, const double* A, int64_t ld, int64_t a_plane, int64_t a_pt,
-                        double* x, int64_t x_pt, int add, double* resid, double* Rout, double* Qout,
-                        hipStream_t st);
+hipError_t launch_blockls(const BlView& V, int slots, int Nm, int nm, hipStream_t st);
 
 #ifdef PE_LAUNCH_DEFINITIONS
 
@@ -321,30 +308,6 @@ hipError_t launch_batch(const BatchShape& K, int P, const double* x, const Batch
 }
 
 template <int L>
-hipError_t launch_mgs(int P, int N, int n, double* W, int64_t w_pt, double* R, int64_t r_pt, double* Y,
-                      int64_t y_pt, double* x, double* resid, hipStream_t st) {
-  auto kern = mgs_solve_kernel<L, kMgsThreads>;
-  const size_t lds = mgs_lds_bytes<L>(N);
-  hipError_t e = allow_lds(kern, lds);
-  if (e != hipSuccess) return e;
-  hipLaunchKernelGGL(kern, dim3(unsigned(P)), dim3(kMgsThreads), lds, st, N, n, W, w_pt, R, r_pt, Y, y_pt, x,
-                     int64_t(width_of(L)) * n, resid);
-  return hipGetLastError();
-}
-
-template <int L>
-hipError_t launch_mgs_batch(int S, int P, int maxN, const BatchNewtonDesc* desc, const int* order, double* W,
-                            double* R, double* Y, double* x, double* resid, hipStream_t st) {
-  auto kern = mgs_solve_batch_kernel<L, kMgsThreads>;
-  const size_t lds = mgs_lds_bytes<L>(maxN);
-  hipError_t e = allow_lds(kern, lds);
-  if (e != hipSuccess) return e;
-  hipLaunchKernelGGL(kern, dim3(unsigned(int64_t(S) * P)), dim3(kMgsThreads), lds, st, desc, order, P, W, R, Y, x,
-                     resid);
-  return hipGetLastError();
-}
-
-template <int L>
 hipError_t launch_rhs_shift(double* W, int64_t w_pt, int64_t plane, int64_t ld, int N, int n, int P, const double* c,
                             double wF, double wc, hipStream_t st) {
   const int64_t tot = int64_t(P) * N;
@@ -353,83 +316,59 @@ hipError_t launch_rhs_shift(double* W, int64_t w_pt, int64_t plane, int64_t ld, 
   return hipGetLastError();
 }
 
-template <int L, int T, int EPT>
-hipError_t ls_sweep(const LsView& V, int P, hipStream_t st) {
-  const int n = V.n;
-  auto apply = [&](int k0, int k1, int j0, int j1) -> hipError_t {
-    if (j1 <= j0) return hipSuccess;
-    hipLaunchKernelGGL((ls_apply_kernel<L, T, EPT>), dim3(unsigned(int64_t(P) * (j1 - j0))), dim3(T), 0, st, V, k0,
-                       k1, j0, j1);
-    return hipGetLastError();
-  };
-  hipError_t e = apply(0, 0, 0, 1);  // the norm of column 0
-  for (int k0 = 0; k0 < n && e == hipSuccess; k0 += kLsPanel) {
-    const int k1 = std::min(k0 + kLsPanel, n);
-    for (int c = k0; c + 1 < k1 && e == hipSuccess; ++c) e = apply(c, c + 1, c + 1, k1);
-    if (e == hipSuccess) e = apply(k0, k1, k1, n + 1);
-  }
-  return e;
-}
-
-// threads and rows per thread of the sweep: T * EPT >= N, registers for the
-// column and one pivot within about 128 VGPRs
+// One group of problems through all panels.  The launches only depend on the
+// largest sizes of the group; workgroups of smaller problems end at once.
 template <int L>
-hipError_t ls_sweep_for(const LsView& V, int P, hipStream_t st) {
-  const int N = V.N;
-  if constexpr (width_of(L) <= 4) {
-    if (N <= 256) return ls_sweep<L, 256, 1>(V, P, st);
-    if (N <= 512) return ls_sweep<L, 256, 2>(V, P, st);
-    if (N <= 1024) return ls_sweep<L, 256, 4>(V, P, st);
-    if (N <= 2048) return ls_sweep<L, 256, 8>(V, P, st);
-    if (N <= 3072) return ls_sweep<L, 384, 8>(V, P, st);
-    if (N <= 4096) return ls_sweep<L, 512, 8>(V, P, st);
-  } else {
-    if (N <= 256) return ls_sweep<L, 256, 1>(V, P, st);
-    if (N <= 512) return ls_sweep<L, 256, 2>(V, P, st);
-    if (N <= 1024) return ls_sweep<L, 256, 4>(V, P, st);
-    if (N <= 2048) return ls_sweep<L, 256, 8>(V, P, st);
-    if (N <= 4096) return ls_sweep<L, 256, 16>(V, P, st);
-  }
-  return hipErrorInvalidValue;
-}
-
-template <int L>
-hipError_t launch_lstsq(const LsLayout& lo, void* ws, const double* A, int64_t ld, int64_t a_plane, int64_t a_pt,
-                        double* x, int64_t x_pt, int add, double* resid, double* Rout, double* Qout,
-                        hipStream_t st) {
-  const LsView V = ls_view(lo, ws);
-  const int P = lo.P, N = lo.N, n = lo.n;
-  const int tiles = ((n + 1 + 63) / 64) * ((N + 63) / 64);
-  hipLaunchKernelGGL(ls_copy_in_kernel<L>, dim3(unsigned(tiles), unsigned(width_of(L)), unsigned(P)), dim3(256), 0, st, V,
-                     A, ld, a_plane, a_pt);
-  hipError_t e = hipGetLastError();
-  if (e != hipSuccess) return e;
-  if (resid) {
-    hipLaunchKernelGGL(ls_bnorm_kernel<L>, dim3(unsigned(P)), dim3(256), 0, st, V, resid);
-    if ((e = hipGetLastError()) != hipSuccess) return e;
-  }
-  if ((e = ls_sweep_for<L>(V, P, st)) != hipSuccess) return e;
-  hipLaunchKernelGGL(ls_init_y_kernel<L>, dim3(unsigned((n + 255) / 256), unsigned(P)), dim3(256), 0, st, V);
+hipError_t launch_blockls(const BlView& V, int slots, int Nm, int nm, hipStream_t st) {
+  using K = Bl<L>;
+  const unsigned S = unsigned(slots);
+  const int NC = (Nm + kBlRows - 1) / kBlRows;
+  hipError_t e;
+  const size_t chol_lds = bl_chol_lds<L>(), solve_lds = bl_solve_lds<L>();
+  if ((e = allow_lds(bl_chol_kernel<L>, chol_lds)) != hipSuccess) return e;
+  if ((e = allow_lds(bl_solve_kernel<L>, solve_lds)) != hipSuccess) return e;
+  hipLaunchKernelGGL(bl_init_kernel<L>, dim3(S), dim3(256), 0, st, V);
+  hipLaunchKernelGGL(bl_copy_in_kernel<L>, dim3(unsigned(((nm + 1 + 63) / 64) * NC), unsigned(K::W), S), dim3(256), 0,
+                     st, V);
   if ((e = hipGetLastError()) != hipSuccess) return e;
-  for (int end = n; end > 0; end -= kBs) {
-    const int s = std::max(0, end - kBs);
-    hipLaunchKernelGGL(ls_backsub_diag_kernel<L>, dim3(unsigned(P)), dim3(kBs), 0, st, V, s, end);
-    if ((e = hipGetLastError()) != hipSuccess) return e;
-    if (s > 0) {
-      hipLaunchKernelGGL(ls_backsub_update_kernel<L>, dim3(unsigned((s + kBs - 1) / kBs), unsigned(P)), dim3(kBs), 0,
-                         st, V, s, end);
-      if ((e = hipGetLastError()) != hipSuccess) return e;
+  // enough workgroups for two on every CU, within the split limits
+  auto splits = [&](int tiles, int most) { return std::max(1, std::min({most, NC, (512 + tiles * slots - 1) / (tiles * slots)})); };
+  for (int panel = 0, k0 = 0; k0 < nm; ++panel, k0 += K::B) {
+    const int cur = panel & 1;
+    const int real_cols = (nm + 1 - k0) * K::CX;
+    hipLaunchKernelGGL(bl_slice_kernel<L>, dim3(unsigned(NC), S), dim3(256), 0, st, V, panel, cur);
+    const int gt = 64 / (16 * K::NT), gs = splits(gt, kBlGramSplit);
+    hipLaunchKernelGGL((bl_dot_kernel<L, true>), dim3(unsigned(gt), unsigned(gs), S), dim3(256), 0, st, V, panel, cur, gs);
+    hipLaunchKernelGGL(bl_chol_kernel<L>, dim3(S), dim3(kBlCholThreads), chol_lds, st, V, panel, cur, gs);
+    hipLaunchKernelGGL(bl_solve_kernel<L>, dim3(unsigned(NC * kBlRows / (256 / K::B)), S), dim3(256), solve_lds, st, V,
+                       panel, cur);
+    const int dt = (real_cols + 16 * K::NT - 1) / (16 * K::NT), ds = splits(dt, kBlMaxSplit);
+    hipLaunchKernelGGL((bl_dot_kernel<L, false>), dim3(unsigned(dt), unsigned(ds), S), dim3(256), 0, st, V, panel, cur,
+                       ds);
+    const int cpw = 256 / K::B;
+    hipLaunchKernelGGL(bl_fin_kernel<L>, dim3(unsigned((nm + 1 - k0 + cpw - 1) / cpw), S), dim3(256), 0, st, V, panel,
+                       cur, ds);
+    if (k0 + K::B < nm) {
+      const int tiles = (real_cols + 15) / 16 - 4;
+      const int groups = std::max(1, std::min(tiles, (768 + NC * slots - 1) / (NC * slots)));
+      const int per = (tiles + groups - 1) / groups;
+      hipLaunchKernelGGL(bl_update_kernel<L>, dim3(unsigned(NC), unsigned((tiles + per - 1) / per), S), dim3(256), 0, st,
+                         V, panel, cur, per);
     }
+    if ((e = hipGetLastError()) != hipSuccess) return e;
   }
-  hipLaunchKernelGGL(ls_finish_kernel<L>, dim3(unsigned(P)), dim3(256), 0, st, V, x, x_pt, add, resid);
-  if ((e = hipGetLastError()) != hipSuccess) return e;
-  if (Rout || Qout) {
-    const int64_t cnt = std::max(int64_t(N) * n, int64_t(n) * (n + 1));
-    hipLaunchKernelGGL(ls_export_kernel<L>, dim3(unsigned((cnt + 255) / 256), unsigned(P)), dim3(256), 0, st, V, Rout,
-                       Qout);
-    e = hipGetLastError();
+  for (int stage = 0; stage * kBlBs < nm; ++stage) {
+    hipLaunchKernelGGL(bl_bs_diag_kernel<L>, dim3(S), dim3(kBlBsThreads), 0, st, V, stage);
+    const int rest = nm - (stage + 1) * kBlBs;
+    if (rest > 0)
+      hipLaunchKernelGGL(bl_bs_update_kernel<L>, dim3(unsigned((rest + 31) / 32), S), dim3(256), 0, st, V, stage);
   }
-  return e;
+  hipLaunchKernelGGL(bl_finish_kernel<L>, dim3(S), dim3(256), 0, st, V);
+  if (V.Rout || V.Qout) {
+    const int64_t cnt = std::max(int64_t(Nm) * nm, int64_t(nm) * (nm + 1));
+    hipLaunchKernelGGL(bl_export_kernel<L>, dim3(unsigned((cnt + 255) / 256), S), dim3(256), 0, st, V);
+  }
+  return hipGetLastError();
 }
 
 #endif  // PE_LAUNCH_DEFINITIONS

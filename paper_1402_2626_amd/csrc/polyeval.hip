@@ -775,80 +775,83 @@ namespace {
 
 size_t align256(size_t b) { return (b + 255) & ~size_t(255); }
 
-struct NewtonLayout {
-  size_t w_off, r_off, y_off, total;
-  int64_t w_pt, r_pt, y_pt;  // in doubles
-};
-
-// W: doubles per number of the level
-NewtonLayout newton_layout(int W, int N, int n, int P) {
-  NewtonLayout lo;
-  lo.w_pt = int64_t(W) * N * (n + 1);
-  lo.r_pt = int64_t(n) * (n + 1) * W;
-  lo.y_pt = int64_t(n) * W;
-  lo.w_off = 0;
-  lo.r_off = align256(lo.w_off + size_t(P) * lo.w_pt * sizeof(double));
-  lo.y_off = align256(lo.r_off + size_t(P) * lo.r_pt * sizeof(double));
-  lo.total = align256(lo.y_off + size_t(P) * lo.y_pt * sizeof(double));
-  return lo;
+// Largest N of the systems below 128 variables that a Gauss-Newton step
+// takes: two columns of N numbers and the sums of 256 threads within one
+// workgroup's LDS.
+bool newton_small_fits(int code, int N) {
+  const size_t W = width_of(code);
+  return (2 * size_t(N) * W + 2 * W + 256 + 16) * sizeof(double) + 16 <= device_lds_limit();
 }
 
-hipError_t dispatch_mgs(int code, int P, int N, int n, double* W, const NewtonLayout& lo, char* base, double* x,
-                        double* resid, hipStream_t st) {
-  double* R = reinterpret_cast<double*>(base + lo.r_off);
-  double* Y = reinterpret_cast<double*>(base + lo.y_off);
+// systems of 128 variables or more, or of too many polynomials for the
+// above: N is limited to kLsMaxRows
+bool newton_large(const pe_system* sys) {
+  return sys->view.n >= 128 || !newton_small_fits(sys->code, sys->view.N);
+}
+
+// ------------------------------------------------------------------ the least-squares solver
+
+// Bytes of solver workspace that one call may take for `total` problems of at
+// most N rows and n unknowns: slots for all of them up to kSolveBytes (one
+// slot at least); more problems go through in groups.
+constexpr size_t kSolveBytes = size_t(1) << 30;
+constexpr int kSolveSlots = 32768;
+
+void bl_layout_for(int code, int N, int n, BlView& V) {
   switch (code) {
-#define PE_C(C_) \
-  case C_: return launch_mgs<C_>(P, N, n, W, lo.w_pt, R, lo.r_pt, Y, lo.y_pt, x, resid, st);
-    PE_C(1) PE_C(2) PE_C(4) PE_C(PE_REAL | 1) PE_C(PE_REAL | 2) PE_C(PE_REAL | 4)
-#undef PE_C
+    case 1: return bl_layout<1>(N, n, V);
+    case 2: return bl_layout<2>(N, n, V);
+    case 4: return bl_layout<4>(N, n, V);
+    case PE_REAL | 1: return bl_layout<PE_REAL | 1>(N, n, V);
+    case PE_REAL | 2: return bl_layout<PE_REAL | 2>(N, n, V);
+    case PE_REAL | 4: return bl_layout<PE_REAL | 4>(N, n, V);
+  }
+}
+
+size_t solve_bytes(int code, int N, int n, int64_t total) {
+  BlView V{};
+  bl_layout_for(code, N, n, V);
+  const int64_t fit = std::max<int64_t>(1, int64_t(kSolveBytes / V.slot));
+  return V.slot * size_t(std::min<int64_t>({total, fit, int64_t(kSolveSlots)}));
+}
+
+hipError_t dispatch_solve(int code, const BlView& V, int slots, int N, int n, hipStream_t st) {
+  switch (code) {
+    case 1: return launch_blockls<1>(V, slots, N, n, st);
+    case 2: return launch_blockls<2>(V, slots, N, n, st);
+    case 4: return launch_blockls<4>(V, slots, N, n, st);
+    case PE_REAL | 1: return launch_blockls<PE_REAL | 1>(V, slots, N, n, st);
+    case PE_REAL | 2: return launch_blockls<PE_REAL | 2>(V, slots, N, n, st);
+    case PE_REAL | 4: return launch_blockls<PE_REAL | 4>(V, slots, N, n, st);
   }
   return hipErrorInvalidValue;
 }
 
-size_t mgs_lds_for(int code, int N) {
-  switch (code) {
-    case 1: return mgs_lds_bytes<1>(N);
-    case 2: return mgs_lds_bytes<2>(N);
-    case 4: return mgs_lds_bytes<4>(N);
-    case PE_REAL | 1: return mgs_lds_bytes<PE_REAL | 1>(N);
-    case PE_REAL | 2: return mgs_lds_bytes<PE_REAL | 2>(N);
-    case PE_REAL | 4: return mgs_lds_bytes<PE_REAL | 4>(N);
+// P problems of one size in groups of as many slots as `bytes` hold
+hipError_t solve_uniform(int code, int P, int N, int n, BlView V, size_t bytes, hipStream_t st) {
+  bl_layout_for(code, N, n, V);
+  V.desc = nullptr;
+  V.N = N;
+  V.n = n;
+  const int slots = int(std::min<size_t>({bytes / V.slot, size_t(P), size_t(kSolveSlots)}));
+  for (int q = 0; q < P; q += slots) {
+    V.q0 = q;
+    const hipError_t e = dispatch_solve(code, V, std::min(slots, P - q), N, n, st);
+    if (e != hipSuccess) return e;
   }
-  return 0;
-}
-
-// The one-workgroup solve (mgs_solve_kernel) for small systems; the
-// column-parallel one (launch_lstsq) once a system has 128 variables or more,
-// or when the one-workgroup kernel's limits (n + 1 <= 1024, the pivot column
-// in LDS) do not hold.
-bool newton_column_parallel(const pe_system* sys) {
-  const int n = sys->view.n, N = sys->view.N;
-  return n >= 128 || n + 1 > 1024 || mgs_lds_for(sys->code, N) > device_lds_limit();
+  return hipSuccess;
 }
 
 pe_status newton_check(const pe_system* sys, int P) {
   const int n = sys->view.n, N = sys->view.N;
   if (P < 0) return fail(PE_EINVAL, "P must be nonnegative");
   if (N < n) return fail(PE_EUNSUPPORTED, "Gauss-Newton needs at least as many polynomials as variables");
-  if (newton_column_parallel(sys) && N > kLsMaxRows)
+  if (newton_large(sys) && N > kLsMaxRows)
     return fail(PE_EUNSUPPORTED, "the least-squares solve supports at most 4096 polynomials");
   if (P > 65535) return fail(PE_EUNSUPPORTED, "at most 65535 points per call");
   if (int64_t(P) * N * sys->view.col_tiles > 0x7fffffffLL)
     return fail(PE_EUNSUPPORTED, "P * N (times the column tiles of J) too large");
   return PE_OK;
-}
-
-hipError_t dispatch_lstsq(int code, const LsLayout& lo, void* ws, const double* A, int64_t ld, int64_t a_plane,
-                          int64_t a_pt, double* x, int64_t x_pt, int add, double* resid, double* Rout, double* Qout,
-                          hipStream_t st) {
-  switch (code) {
-#define PE_C(C_) \
-  case C_: return launch_lstsq<C_>(lo, ws, A, ld, a_plane, a_pt, x, x_pt, add, resid, Rout, Qout, st);
-    PE_C(1) PE_C(2) PE_C(4) PE_C(PE_REAL | 1) PE_C(PE_REAL | 2) PE_C(PE_REAL | 4)
-#undef PE_C
-  }
-  return hipErrorInvalidValue;
 }
 
 }  // namespace
@@ -858,9 +861,8 @@ extern "C" {
 size_t pe_newton_workspace_bytes(const pe_system* sys, int32_t P) {
   if (!sys || P < 0) return 0;
   const int W = width_of(sys->code), N = sys->view.N, n = sys->view.n;
-  if (!newton_column_parallel(sys)) return newton_layout(W, N, n, P).total;
-  // [J | -F] row-major as the evaluation writes it, then the solver's space
-  return align256(size_t(P) * W * N * (n + 1) * sizeof(double)) + ls_layout(sys->code, N, n, P).total;
+  // [J | -F] row-major as the evaluation writes it, then the solver's slots
+  return align256(size_t(P) * W * N * (n + 1) * sizeof(double)) + solve_bytes(sys->code, N, n, P);
 }
 
 }  // extern "C"
@@ -889,8 +891,6 @@ pe_status newton_step_impl(const pe_system* sys, int32_t P, double* x_inout, con
   if (!x_inout || !workspace) return fail(PE_EINVAL, "x or workspace is NULL");
   if (reinterpret_cast<uintptr_t>(workspace) & 255) return fail(PE_EINVAL, "workspace must be 256-byte aligned");
   const int code = sys->code, Wd = width_of(code), n = sys->view.n, N = sys->view.N;
-  const bool big = newton_column_parallel(sys);
-  const NewtonLayout lo = newton_layout(Wd, N, n, P);
   char* base = static_cast<char*>(workspace);
   double* W = reinterpret_cast<double*>(base);  // [J | -F], row stride n + 1
   const int64_t w_pt = int64_t(Wd) * N * (n + 1);
@@ -911,13 +911,18 @@ pe_status newton_step_impl(const pe_system* sys, int32_t P, double* x_inout, con
     e = dispatch_rhs_shift(code, W, w_pt, O.j_plane, n + 1, N, n, P, c, wF, wc, hs);
     if (e != hipSuccess) return fail(PE_EDEVICE, std::string("homotopy right-hand side: ") + hipGetErrorString(e));
   }
-  if (big) {
-    void* ls = base + align256(size_t(P) * w_pt * sizeof(double));
-    e = dispatch_lstsq(code, ls_layout(code, N, n, P), ls, W, n + 1, O.j_plane, w_pt, x_inout, int64_t(Wd) * n, 1,
-                       resid_out, nullptr, nullptr, hs);
-  } else {
-    e = dispatch_mgs(code, P, N, n, W, lo, base, x_inout, resid_out, hs);
-  }
+  const size_t front = align256(size_t(P) * w_pt * sizeof(double));
+  BlView V{};
+  V.A = W;
+  V.a_pt = w_pt;
+  V.a_plane = O.j_plane;
+  V.ld = n + 1;
+  V.X = x_inout;
+  V.x_pt = int64_t(Wd) * n;
+  V.add = 1;
+  V.resid = resid_out;
+  V.ws = base + front;
+  e = solve_uniform(code, P, N, n, V, solve_bytes(code, N, n, P), hs);
   if (e != hipSuccess) return fail(PE_EDEVICE, std::string("newton solve launch: ") + hipGetErrorString(e));
   return PE_OK;
 }
@@ -968,7 +973,7 @@ static bool valid_level(int level) {
 
 size_t pe_lstsq_workspace_bytes(int32_t level, int32_t P, int32_t N, int32_t n) {
   if (!valid_level(level) || P < 0 || N < 1 || n < 1) return 0;
-  return ls_layout(level, N, n, P).total;
+  return solve_bytes(level, N, n, P);
 }
 
 pe_status pe_lstsq(int32_t level, int32_t P, int32_t N, int32_t n, const double* Ab, double* x, double* resid_out,
@@ -982,9 +987,20 @@ pe_status pe_lstsq(int32_t level, int32_t P, int32_t N, int32_t n, const double*
   if (!Ab || !x || !workspace) return fail(PE_EINVAL, "Ab, x or workspace is NULL");
   if (reinterpret_cast<uintptr_t>(workspace) & 255) return fail(PE_EINVAL, "workspace must be 256-byte aligned");
   const int64_t plane = int64_t(N) * (n + 1);
-  hipError_t e = dispatch_lstsq(level, ls_layout(level, N, n, P), workspace, Ab, n + 1, plane, width_of(level) * plane,
-                                x, int64_t(width_of(level)) * n, 0, resid_out, R_out, Q_out,
-                                static_cast<hipStream_t>(stream));
+  BlView V{};
+  V.A = Ab;
+  V.a_pt = width_of(level) * plane;
+  V.a_plane = plane;
+  V.ld = n + 1;
+  V.X = x;
+  V.x_pt = int64_t(width_of(level)) * n;
+  V.add = 0;
+  V.resid = resid_out;
+  V.Rout = R_out;
+  V.Qout = Q_out;
+  V.ws = static_cast<char*>(workspace);
+  const hipError_t e =
+      solve_uniform(level, P, N, n, V, solve_bytes(level, N, n, P), static_cast<hipStream_t>(stream));
   if (e != hipSuccess) return fail(PE_EDEVICE, std::string("least-squares launch: ") + hipGetErrorString(e));
   return PE_OK;
 }
@@ -1021,7 +1037,9 @@ struct pe_batch {
   std::vector<const pe_system*> systems;
   std::vector<int64_t> x_off, F_off, J_off;  // per point, doubles, [S+1]
   std::vector<BatchNewtonDesc> ndesc;        // per point offsets of the Newton workspace
-  int64_t w_total = 0, r_total = 0, y_total = 0;  // per point, doubles
+  int64_t w_total = 0;                       // per point, doubles
+  std::vector<int> order;                    // systems in decreasing n * N
+  std::vector<int> left_N, left_n;           // largest N and n of order[i], order[i + 1], ...
   int64_t nitems = 0;
   SysView* d_views = nullptr;
   int64_t* d_offs = nullptr;  // x_off | F_off | J_off | W offsets, each [S+1]
@@ -1191,7 +1209,6 @@ pe_status pe_batch_create(pe_batch** out, int32_t S, const pe_system* const* sys
   b->J_off.assign(S + 1, 0);
   std::vector<int64_t> w_off(S + 1, 0);
   b->ndesc.resize(S);
-  int64_t ro = 0, yo = 0;
   for (int s = 0; s < S; ++s) {
     const int n = systems[s]->view.n, N = systems[s]->view.N;
     b->x_off[s + 1] = b->x_off[s] + int64_t(2) * L * n;
@@ -1202,15 +1219,9 @@ pe_status pe_batch_create(pe_batch** out, int32_t S, const pe_system* const* sys
     d.N = N;
     d.n = n;
     d.w_off = w_off[s];
-    d.r_off = ro;
-    d.y_off = yo;
     d.x_off = b->x_off[s];
-    ro += int64_t(n) * (n + 1) * 2 * L;
-    yo += int64_t(n) * 2 * L;
   }
   b->w_total = w_off[S];
-  b->r_total = ro;
-  b->y_total = yo;
   // work items of each class in decreasing cost (longest processing time
   // first)
   std::vector<uint64_t> it[pe_batch::kClasses];
@@ -1239,6 +1250,13 @@ pe_status pe_batch_create(pe_batch** out, int32_t S, const pe_system* const* sys
   std::stable_sort(order.begin(), order.end(), [&](int a, int c) {
     return int64_t(systems[a]->view.n) * systems[a]->view.N > int64_t(systems[c]->view.n) * systems[c]->view.N;
   });
+  b->order = order;
+  b->left_N.assign(S + 1, 0);
+  b->left_n.assign(S + 1, 0);
+  for (int i = S - 1; i >= 0; --i) {
+    b->left_N[i] = std::max(b->left_N[i + 1], systems[order[i]]->view.N);
+    b->left_n[i] = std::max(b->left_n[i + 1], systems[order[i]]->view.n);
+  }
   hipStream_t hs = static_cast<hipStream_t>(stream);
   pe_status e = PE_OK;
   for (int c = 0; c < pe_batch::kClasses && e == PE_OK; ++c) e = upload_raw(it[c], &b->cls[c].d_items, hs);
@@ -1306,9 +1324,8 @@ pe_status pe_batch_eval(const pe_batch* b, int32_t P, const double* x, double* F
 
 size_t pe_batch_newton_workspace_bytes(const pe_batch* b, int32_t P) {
   if (!b || P < 0) return 0;
-  // [W blocks][R blocks][y blocks]
-  return align256(size_t(P) * b->w_total * 8) + align256(size_t(P) * b->r_total * 8) +
-         align256(size_t(P) * b->y_total * 8);
+  // [J | -F] of every system-point, then the solver's slots
+  return align256(size_t(P) * b->w_total * 8) + solve_bytes(b->level, b->left_N[0], b->left_n[0], int64_t(b->S) * P);
 }
 
 pe_status pe_batch_newton_step(const pe_batch* b, int32_t P, double* x_inout, void* workspace, double* resid_out,
@@ -1318,22 +1335,14 @@ pe_status pe_batch_newton_step(const pe_batch* b, int32_t P, double* x_inout, vo
   if (P == 0) return PE_OK;
   if (!x_inout || !workspace) return fail(PE_EINVAL, "x or workspace is NULL");
   if (reinterpret_cast<uintptr_t>(workspace) & 255) return fail(PE_EINVAL, "workspace must be 256-byte aligned");
-  // the batched step runs the one-workgroup solve for every system
   for (const pe_system* y : b->systems) {
     pe_status ps = newton_check(y, P);
     if (ps != PE_OK) return ps;
     if (y->view.n + 1 > 1024) return fail(PE_EUNSUPPORTED, "the batched Gauss-Newton step supports n + 1 <= 1024");
   }
-  {
-    const size_t lds = b->level == 1 ? mgs_lds_bytes<1>(b->maxN)
-                                     : (b->level == 2 ? mgs_lds_bytes<2>(b->maxN) : mgs_lds_bytes<4>(b->maxN));
-    if (lds > device_lds_limit()) return fail(PE_EUNSUPPORTED, "too many polynomials for the LDS pivot column");
-  }
-  const int L = b->level;
+  if (!newton_small_fits(b->level, b->maxN)) return fail(PE_EUNSUPPORTED, "too many polynomials for a batched step");
   char* base = static_cast<char*>(workspace);
   double* W = reinterpret_cast<double*>(base);
-  double* Rw = reinterpret_cast<double*>(base + align256(size_t(P) * b->w_total * 8));
-  double* Yw = reinterpret_cast<double*>(base + align256(size_t(P) * b->w_total * 8) + align256(size_t(P) * b->r_total * 8));
   hipStream_t hs = static_cast<hipStream_t>(stream);
   BatchOut out;
   out.J = W;
@@ -1343,11 +1352,26 @@ pe_status pe_batch_newton_step(const pe_batch* b, int32_t P, double* x_inout, vo
   out.newton = 1;
   hipError_t e = dispatch_batch(b, P, x_inout, out, MODE_EVAL, hs);
   if (e != hipSuccess) return fail(PE_EDEVICE, std::string("batch newton eval: ") + hipGetErrorString(e));
-  const BatchNewtonDesc* nd = b->d_ndesc;
-  switch (L) {
-    case 1: e = launch_mgs_batch<1>(b->S, P, b->maxN, nd, b->d_order, W, Rw, Yw, x_inout, resid_out, hs); break;
-    case 2: e = launch_mgs_batch<2>(b->S, P, b->maxN, nd, b->d_order, W, Rw, Yw, x_inout, resid_out, hs); break;
-    case 4: e = launch_mgs_batch<4>(b->S, P, b->maxN, nd, b->d_order, W, Rw, Yw, x_inout, resid_out, hs); break;
+  // groups of system-points in decreasing size, as many at a time as the
+  // slots of that size fit in the workspace
+  const int64_t total = int64_t(b->S) * P;
+  const size_t bytes = solve_bytes(b->level, b->left_N[0], b->left_n[0], total);
+  BlView V{};
+  V.desc = b->d_ndesc;
+  V.order = b->d_order;
+  V.P = P;
+  V.A = W;
+  V.X = x_inout;
+  V.add = 1;
+  V.resid = resid_out;
+  V.ws = base + align256(size_t(P) * b->w_total * 8);
+  for (int64_t q = 0; q < total && e == hipSuccess;) {
+    const int Nm = b->left_N[q / P], nm = b->left_n[q / P];
+    bl_layout_for(b->level, Nm, nm, V);
+    V.q0 = int(q);
+    const int slots = int(std::min<int64_t>({int64_t(bytes / V.slot), total - q, int64_t(kSolveSlots)}));
+    e = dispatch_solve(b->level, V, slots, Nm, nm, hs);
+    q += slots;
   }
   if (e != hipSuccess) return fail(PE_EDEVICE, std::string("batch newton solve: ") + hipGetErrorString(e));
   return PE_OK;
