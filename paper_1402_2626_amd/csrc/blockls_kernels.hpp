@@ -4,7 +4,7 @@
 //
 // Per panel (columns k0 .. k0 + B - 1 of the working copy W, already updated
 // by the panels before it):
-//   1. bl_slice_kernel, bl_dot_kernel: the Gram matrix of the panel;
+//   1. bl_gram_kernel: the Gram matrix of the panel;
 //   2. bl_chol_kernel: its factor U^H D U, one workgroup per problem, so that
 //      the serial chain of a panel is B small steps in LDS instead of B inner
 //      products over all rows and B launches;
@@ -39,9 +39,9 @@
 // 544 int8 multiply-adds, of which the matrix cores do 2.5e15 a second.
 // Against the column-by-column sweep that this replaces (a launch and two
 // workgroup reductions per pivot, FP64 throughout) a Gauss-Newton step went
-// from 2.08 to 1.02 ms (complex double double, n = 256), 53.5 to 17.5 ms
-// (n = 2048), 35.0 to 12.8 ms (real quad double, n = 1016), and the batched
-// step over 96 system-points of n = 32 .. 256 from 39.9 to 2.5 ms.
+// from 2.08 to 0.75 ms (complex double double, n = 256), 53.5 to 14.7 ms
+// (n = 2048), 35.0 to 7.7 ms (real quad double, n = 1016), and the batched
+// step over 96 system-points of n = 32 .. 256 from 39.9 to 2.2 ms.
 #pragma once
 #include <hip/hip_runtime.h>
 
@@ -326,6 +326,22 @@ __device__ __forceinline__ C<LO> bl_narrow(const C<L>& a) {
   return r;
 }
 
+// sum over the row splits of a contraction's output, four loads in flight
+template <int L>
+__device__ __forceinline__ C<L> bl_sum_splits(const char* base, size_t stride, int ns) {
+  C<L> s = load_aos<L>(reinterpret_cast<const double*>(base));
+  for (int t = 1; t < ns; t += 3) {
+    C<L> v[3];
+#pragma unroll
+    for (int q = 0; q < 3; ++q)
+      v[q] = load_aos<L>(reinterpret_cast<const double*>(base + size_t(min(t + q, ns - 1)) * stride));
+#pragma unroll
+    for (int q = 0; q < 3; ++q)
+      if (t + q < ns) s = c_add(s, v[q]);
+  }
+  return s;
+}
+
 // ------------------------------------------------------------------ set up
 
 // Per problem: state cleared, |b|_2 (leading limbs) into resid[0].  grid
@@ -394,58 +410,140 @@ __global__ __launch_bounds__(256) void bl_copy_in_kernel(BlView V) {
 
 // ------------------------------------------------------------------ contractions over rows
 
-// Digits of the panel's columns (fixed point against each column's largest
-// entry) in the order the contraction reads: [chunk][digit][64 real
-// columns][64 rows] bytes.  grid (chunks, slots), 256 threads
-template <int L>
-__global__ __launch_bounds__(256) void bl_slice_kernel(BlView V, int panel, int cur) {
-  using K = Bl<L>;
-  const BlProb p = bl_prob<L>(V, blockIdx.y);
-  const int k0 = panel * K::B, ch = blockIdx.x;
-  if (k0 >= p.n || ch * kBlRows >= p.N || bl_at<BlMisc>(p, V.oMisc)->flag) return;
-  const int bcur = min(K::B, p.n - k0);
-  const double* Wp = bl_at<double>(p, V.oW);
-  const int64_t plane = int64_t(p.n + 1) * p.N;
-  const int* ce = bl_at<int>(p, V.oCe) + cur * V.nmax;
-  uint32_t* xd = bl_at<uint32_t>(p, V.oXD) + size_t(ch) * K::ND * 1024;
-  const int k4 = threadIdx.x & 15;
-  for (int m = threadIdx.x >> 4; m < 64; m += 16) {
-    const int c = m / K::CX, comp = m % K::CX;
-    double v[4][K::NL];
-    int e[4];
-    const int ex = c < bcur ? ce[k0 + c] - kExpOne : 0;
+// the 4 values of a lane's accumulator tile (16 rows of X's real columns from
+// row m on, one real column of the other side) into S at column `col`:
+// complex numbers join across neighbouring lanes, which hold the real and
+// imaginary part of one column: re = Xr.Ar + Xi.Ai, im = Xr.Ai - Xi.Ar
+template <int L, int LO, int ND>
+__device__ __forceinline__ void bl_store_s(double* Sp, const bl_v4i (&av)[ND], int e, int col, int m, int comp, bool in) {
+  constexpr int NO = limbs_of(LO), B = Bl<L>::B;
+  R<NO> val[4];
 #pragma unroll
-    for (int r = 0; r < 4; ++r) {
-      const int row = ch * kBlRows + k4 * 4 + r;
-      e[r] = ex;
+  for (int r = 0; r < 4; ++r) {
+    int t[ND];
 #pragma unroll
-      for (int l = 0; l < K::NL; ++l)
-        v[r][l] = (c < bcur && row < p.N) ? Wp[(comp * K::NL + l) * plane + int64_t(k0 + c) * p.N + row] : 0.0;
+    for (int d = 0; d < ND; ++d) t[d] = av[d][r];
+    val[r] = bl_value<NO, ND>(t, e);
+  }
+  if constexpr (is_real(L)) {
+    if (in)
+#pragma unroll
+      for (int r = 0; r < 4; ++r) r_store_aos(Sp + (size_t(col) * B + m + r) * width_of(LO), val[r]);
+  } else {
+#pragma unroll
+    for (int h = 0; h < 2; ++h) {
+      const R<NO> mine = val[2 * h + 1];
+      R<NO> other;
+#pragma unroll
+      for (int l = 0; l < NO; ++l) other.x[l] = __shfl_xor(mine.x[l], 1);
+      const R<NO> s = r_add(val[2 * h], comp ? r_neg(other) : other);
+      if (in) r_store_aos(Sp + (size_t(col) * B + m / 2 + h) * width_of(LO) + comp * NO, s);
     }
-    bl_put4<K::NL, K::ND>(v, e, xd + m * 16 + k4, 1024);
   }
 }
 
-// S = X^H C for the columns C of W from k0 on (GRAM: the panel's own columns,
-// and X the panel itself, both scaled by their column exponents; else X is
-// orthonormal, C the panel and all later columns with the right-hand side).
-// One workgroup takes NT tiles of 16 real columns and a range of rows: per
-// chunk of 64 rows it cuts its columns into digits in LDS once, and each of
-// its four wavefronts multiplies them by the digits of 16 of X's 64 real
-// columns.  Row ranges are summed by the kernels that read S.  S is
-// [split][column][B] numbers.  grid (column tiles, splits, slots), 256 threads
-template <int L, bool GRAM>
-__global__ __launch_bounds__(256, limbs_of(L) == 4 ? 1 : 2) void bl_dot_kernel(BlView V, int panel, int cur, int nsplit) {
+// four rows of a real column of W as limbs (zero outside)
+template <int NL>
+__device__ __forceinline__ void bl_load4(const double* src, int64_t plane, int row, int N, bool in, double (&v)[4][NL]) {
+#pragma unroll
+  for (int r = 0; r < 4; ++r)
+#pragma unroll
+    for (int l = 0; l < NL; ++l) v[r][l] = (in && row + r < N) ? src[l * plane + row + r] : 0.0;
+}
+
+// Gram matrix of the panel's columns, each scaled by its exponent: per chunk
+// of 64 rows the digits of all 64 real columns are cut into LDS once, and
+// each of the four wavefronts multiplies 16 of them with the workgroup's NT
+// tiles of 16.  Row ranges are summed by bl_chol_kernel.  S is [split][column]
+// [B] numbers of the factor's level.  grid (4 / NT, splits, slots), 256 threads
+template <int L>
+__global__ __launch_bounds__(256, limbs_of(L) == 4 ? 1 : 2) void bl_gram_kernel(BlView V, int panel, int cur,
+                                                                                int nsplit) {
   using K = Bl<L>;
   constexpr int NL = K::NL, ND = K::ND, NT = K::NT, CX = K::CX;
-  constexpr int LO = GRAM ? K::LC : L;  // level of the output
-  constexpr int NO = limbs_of(LO);
+  extern __shared__ double lds[];
+  bl_v4i* dig = reinterpret_cast<bl_v4i*>(lds);  // [digit][64 real columns][64 rows]
+  const BlProb p = bl_prob<L>(V, blockIdx.z);
+  const int k0 = panel * K::B;
+  if (k0 >= p.n) return;
+  const int flag = bl_at<BlMisc>(p, V.oMisc)->flag;  // tested where nothing waits for it
+  const int bcur = min(K::B, p.n - k0);
+  const int rc0 = blockIdx.x * NT * 16;
+  const int NC = (p.N + kBlRows - 1) / kBlRows;
+  const int ns = min(nsplit, NC), split = blockIdx.y;
+  if (rc0 >= bcur * CX || split >= ns) return;
+  const int per = (NC + ns - 1) / ns;
+  const int ch0 = split * per, ch1 = min(NC, ch0 + per);
+  const double* Wp = bl_at<double>(p, V.oW);
+  const int64_t plane = int64_t(p.n + 1) * p.N;
+  const int* ce = bl_at<int>(p, V.oCe) + cur * V.nmax + k0;
+  const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
+  const int k4 = tid & 15, c16 = tid >> 4;
+  bl_v4i av[NT][ND];
+#pragma unroll
+  for (int t = 0; t < NT; ++t)
+#pragma unroll
+    for (int d = 0; d < ND; ++d) av[t][d] = bl_v4i{0, 0, 0, 0};
+  for (int ch = ch0; ch < ch1; ++ch) {
+    if (ch > ch0) __syncthreads();  // the previous chunk's digits are read
+#pragma unroll
+    for (int u = 0; u < 4; ++u) {
+      const int m = u * 16 + c16, c = m / CX;
+      const bool in = c < bcur;
+      double v[4][NL];
+      bl_load4<NL>(Wp + int64_t(m % CX) * NL * plane + int64_t(k0 + (in ? c : 0)) * p.N, plane, ch * kBlRows + k4 * 4,
+                   p.N, in, v);
+      const int ex = in ? ce[c] - kExpOne : 0;
+      const int e[4] = {ex, ex, ex, ex};
+      bl_put4<NL, ND>(v, e, reinterpret_cast<uint32_t*>(dig) + m * 16 + k4, 1024);
+    }
+    __syncthreads();
+    bl_v4i a[ND];
+#pragma unroll
+    for (int i = 0; i < ND; ++i) a[i] = dig[(i * 64 + 16 * wave + (lane & 15)) * 4 + (lane >> 4)];
+#pragma unroll
+    for (int u = 0; u < NT; ++u)
+#pragma unroll
+      for (int j = 0; j < ND; ++j) {
+        const bl_v4i b = dig[(j * 64 + rc0 + u * 16 + (lane & 15)) * 4 + (lane >> 4)];
+#pragma unroll
+        for (int i = 0; i < ND; ++i)
+          if (i + j < ND) av[u][i + j] = __builtin_amdgcn_mfma_i32_16x16x64_i8(a[i], b, av[u][i + j], 0, 0, 0);
+      }
+  }
+  if (flag) return;
+  double* Sp = reinterpret_cast<double*>(p.base + V.oS + split * V.g_split);
+#pragma unroll
+  for (int u = 0; u < NT; ++u) {
+    const int rc = rc0 + u * 16 + (lane & 15);
+    bl_store_s<L, K::LC, ND>(Sp, av[u], -12, rc / CX, 16 * wave + 4 * (lane >> 4), rc % CX, rc < bcur * CX);
+  }
+}
+
+template <int L>
+__host__ __device__ inline size_t bl_gram_lds() {
+  return size_t(Bl<L>::ND) * 4096;
+}
+
+// S = X^H C for the orthonormal panel X and the columns C of W from k0 on
+// (the panel itself, all later columns, the right-hand side).  One workgroup
+// takes NT tiles of 16 real columns and a range of rows: per chunk of 64 rows
+// it cuts its columns into digits in LDS once, and each of its four wavefronts
+// multiplies them by the digits of 16 of X's 64 real columns.  Row ranges are
+// summed by bl_fin_kernel.  S is [split][column][B] numbers.  grid (column
+// tiles, splits, slots), 256 threads
+template <int L>
+__global__ __launch_bounds__(256, limbs_of(L) == 4 ? 1 : 2) void bl_dot_kernel(BlView V, int panel, int cur,
+                                                                               int nsplit) {
+  using K = Bl<L>;
+  constexpr int NL = K::NL, ND = K::ND, NT = K::NT, CX = K::CX;
   __shared__ bl_v4i dig[NT * ND * 64];
   const BlProb p = bl_prob<L>(V, blockIdx.z);
   const int k0 = panel * K::B;
-  if (k0 >= p.n || bl_at<BlMisc>(p, V.oMisc)->flag) return;
+  if (k0 >= p.n) return;
+  const int flag = bl_at<BlMisc>(p, V.oMisc)->flag;
   const int bcur = min(K::B, p.n - k0);
-  const int ncols = (GRAM ? bcur : p.n + 1 - k0) * CX;  // real columns
+  const int ncols = (p.n + 1 - k0) * CX;  // real columns
   const int rc0 = blockIdx.x * NT * 16;
   const int NC = (p.N + kBlRows - 1) / kBlRows;
   const int ns = min(nsplit, NC), split = blockIdx.y;
@@ -456,23 +554,19 @@ __global__ __launch_bounds__(256, limbs_of(L) == 4 ? 1 : 2) void bl_dot_kernel(B
   const int64_t plane = int64_t(p.n + 1) * p.N;
   const int* ce = bl_at<int>(p, V.oCe) + cur * V.nmax;
   const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
-  int acc[NT][ND][4];
-  bl_v4i av[NT][ND];
-#pragma unroll
-  for (int t = 0; t < NT; ++t)
-#pragma unroll
-    for (int d = 0; d < ND; ++d) av[t][d] = bl_v4i{0, 0, 0, 0};
   const int k4 = tid & 15, c16 = tid >> 4;
   // power of two of column c (from the panel's first): X itself is at most 1
-  auto col_exp = [&](int c) { return !GRAM && c < bcur ? 0 : ce[k0 + c] - kExpOne; };
+  auto col_exp = [&](int c) { return c < bcur ? 0 : ce[k0 + c] - kExpOne; };
   int ex[NT];
   const double* src[NT];
+  bl_v4i av[NT][ND];
 #pragma unroll
   for (int u = 0; u < NT; ++u) {
-    const int rc = rc0 + u * 16 + c16;
-    const int col = k0 + min(rc, ncols - 1) / CX;
-    ex[u] = col_exp(col - k0);
-    src[u] = Wp + int64_t(rc % CX) * NL * plane + int64_t(col) * p.N;
+    const int rc = min(rc0 + u * 16 + c16, ncols - 1);
+    ex[u] = col_exp(rc / CX);
+    src[u] = Wp + int64_t(rc % CX) * NL * plane + int64_t(k0 + rc / CX) * p.N;
+#pragma unroll
+    for (int d = 0; d < ND; ++d) av[u][d] = bl_v4i{0, 0, 0, 0};
   }
   for (int ch = ch0; ch < ch1; ++ch) {
     const bl_v4i* xd = bl_at<bl_v4i>(p, V.oXD) + size_t(ch) * ND * 256 + (16 * wave + (lane & 15)) * 4 + (lane >> 4);
@@ -482,13 +576,7 @@ __global__ __launch_bounds__(256, limbs_of(L) == 4 ? 1 : 2) void bl_dot_kernel(B
     double v[NT][4][NL];
 #pragma unroll
     for (int u = 0; u < NT; ++u)
-#pragma unroll
-      for (int r = 0; r < 4; ++r) {
-        const int row = ch * kBlRows + k4 * 4 + r;
-        const bool in = row < p.N && rc0 + u * 16 + c16 < ncols;
-#pragma unroll
-        for (int l = 0; l < NL; ++l) v[u][r][l] = in ? src[u][l * plane + row] : 0.0;
-      }
+      bl_load4<NL>(src[u], plane, ch * kBlRows + k4 * 4, p.N, rc0 + u * 16 + c16 < ncols, v[u]);
     __syncthreads();  // the previous chunk's digits are read
 #pragma unroll
     for (int u = 0; u < NT; ++u) {
@@ -506,52 +594,51 @@ __global__ __launch_bounds__(256, limbs_of(L) == 4 ? 1 : 2) void bl_dot_kernel(B
           if (i + j < ND) av[u][i + j] = __builtin_amdgcn_mfma_i32_16x16x64_i8(a[i], b, av[u][i + j], 0, 0, 0);
       }
   }
-#pragma unroll
-  for (int t = 0; t < NT; ++t)
-#pragma unroll
-    for (int d = 0; d < ND; ++d)
-#pragma unroll
-      for (int r = 0; r < 4; ++r) acc[t][d][r] = av[t][d][r];
-  double* Sp = reinterpret_cast<double*>(p.base + V.oS + split * (GRAM ? V.g_split : V.s_split));
+  if (flag) return;
+  double* Sp = reinterpret_cast<double*>(p.base + V.oS + split * V.s_split);
 #pragma unroll
   for (int u = 0; u < NT; ++u) {
     const int rc = rc0 + u * 16 + (lane & 15);
-    const int col = rc / CX;
-    const int e = (GRAM ? 0 : col_exp(min(rc, ncols - 1) / CX)) - 12;
-    R<NO> val[4];
-#pragma unroll
-    for (int r = 0; r < 4; ++r) {
-      int t[ND];
-#pragma unroll
-      for (int d = 0; d < ND; ++d) t[d] = acc[u][d][r];
-      val[r] = bl_value<NO, ND>(t, e);
-    }
-    const int m = 16 * wave + 4 * (lane >> 4);
-    if constexpr (is_real(L)) {
-      if (rc < ncols)
-#pragma unroll
-        for (int r = 0; r < 4; ++r) r_store_aos(Sp + (size_t(col) * K::B + m + r) * width_of(LO), val[r]);
-    } else {
-      // neighbouring lanes hold the real and imaginary part of one column,
-      // neighbouring values those of one column of X:
-      // re = Xr.Ar + Xi.Ai, im = Xr.Ai - Xi.Ar
-      const int comp = lane & 1;
-#pragma unroll
-      for (int h = 0; h < 2; ++h) {
-        const R<NO> mine = val[2 * h + 1];
-        R<NO> other;
-#pragma unroll
-        for (int l = 0; l < NO; ++l) other.x[l] = __shfl_xor(mine.x[l], 1);
-        const R<NO> s = r_add(val[2 * h], comp ? r_neg(other) : other);
-        if (rc < ncols) r_store_aos(Sp + (size_t(col) * K::B + m / 2 + h) * width_of(LO) + comp * NO, s);
-      }
-    }
+    bl_store_s<L, L, ND>(Sp, av[u], col_exp(min(rc, ncols - 1) / CX) - 12, rc / CX, 16 * wave + 4 * (lane >> 4), rc % CX,
+                         rc < ncols);
   }
 }
 
 // ------------------------------------------------------------------ the panel's factor
 
-constexpr int kBlCholThreads = 512;
+// threads of the factor's workgroup and upper-triangle entries per thread
+template <int L>
+struct BlChol {
+  static constexpr int T = Bl<L>::NL == 4 ? (is_real(L) ? 512 : 320) : (is_real(L) ? 704 : 576);
+  static constexpr int ENTRIES = Bl<L>::B * (Bl<L>::B + 1) / 2;
+  static constexpr int EPT = (ENTRIES + T - 1) / T;
+};
+
+// 1 / a to the level's precision: a double estimate corrected by its
+// residual, for quad double once more
+template <int NLV>
+__device__ __forceinline__ R<NLV> bl_recip(const R<NLV>& a) {
+  // two Newton steps on the hardware's estimate: within about one unit in the
+  // last place for pivots far from the ends of the exponent range
+  double y = __builtin_amdgcn_rcp(a.x[0]);
+  y = PE_FMA(y, PE_FMA(-a.x[0], y, 1.0), y);
+  y = PE_FMA(y, PE_FMA(-a.x[0], y, 1.0), y);
+  if constexpr (NLV == 1) {
+    return r_from_double<1>(y);
+  } else {
+    const double r = PE_FMA(-a.x[1], y, PE_FMA(-a.x[0], y, 1.0));
+    R<2> z;
+    fast_two_sum(y, y * r, z.x[0], z.x[1]);
+    if constexpr (NLV == 2) {
+      return z;
+    } else {
+      const R<4> z4{{z.x[0], z.x[1], 0.0, 0.0}};
+      const R<4> t = r_sub(r_from_double<4>(1.0), r_mul(a, z4));
+      const R<2> c = r_mul(z, R<2>{{t.x[0], t.x[1]}});
+      return r_add(z4, R<4>{{c.x[0], c.x[1], 0.0, 0.0}});
+    }
+  }
+}
 
 // squared norm of a wavefront's rows of a column summed over the wavefront
 template <int NLV>
@@ -576,7 +663,7 @@ __device__ bool bl_mgs_sweep(const BlProb& p, double* Wp, int k0, int bcur, doub
                              bool check, double* norm0, double* rmin) {
   using K = Bl<L>;
   constexpr int NL = K::NL;
-  const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6, nwave = kBlCholThreads / 64;
+  const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6, nwave = BlChol<L>::T / 64;
   const int64_t plane = int64_t(p.n + 1) * p.N;
   auto norm2 = [&](int c) {
     R<NL> s = r_zero<NL>();
@@ -598,7 +685,7 @@ __device__ bool bl_mgs_sweep(const BlProb& p, double* Wp, int k0, int bcur, doub
     *rmin = fmin(*rmin, r.x[0] / norm0[k]);
     const R<NL> ir = r_recip(r);
     __syncthreads();
-    for (int i = threadIdx.x; i < p.N; i += kBlCholThreads) {
+    for (int i = threadIdx.x; i < p.N; i += BlChol<L>::T) {
       double* c = Wp + int64_t(k0 + k) * p.N;
       store_planar(c, plane, i, c_mul_r(load_planar<L>(c, plane, i), ir));
     }
@@ -623,75 +710,108 @@ __device__ bool bl_mgs_sweep(const BlProb& p, double* Wp, int k0, int bcur, doub
 }
 
 // Factor of the panel's Gram matrix G (of the columns scaled by their
-// exponents): G = U^H D U, U unit upper triangular, in LDS, one barrier per
-// pivot: the thread of entry (i, j) subtracts conj(g_ki) (g_kj / d_k), so the
-// reciprocal of the pivot is the only serial step.  Square roots wait for the
-// end.  A pivot below kPivot of its column's squared norm would leave
+// exponents): G = U^H D U, U unit upper triangular.  A thread keeps entries
+// of the upper triangle in registers; a row is published in LDS when the
+// pivots above it are done, and step k's threads subtract
+// conj(g_ki) g_kj / d_k, every thread forming the reciprocal of the pivot
+// itself, so that a step has one barrier (quad double: the row over its pivot
+// once, and two).  Square roots wait for the end.  A pivot below kPivot of its column's squared norm would leave
 // E = X^H X - I too large for its first order (E is about u_C / pivot
 // ratio, u_C the unit roundoff of the factor's level): then the panel is
 // orthogonalised by modified Gram-Schmidt here, again if one sweep leaves
 // E above the square root of the level's roundoff.  One workgroup per
 // problem: it is bound by the chain of B pivots.
 template <int L>
-__global__ __launch_bounds__(kBlCholThreads) void bl_chol_kernel(BlView V, int panel, int cur, int nsplit) {
+__global__ __launch_bounds__(BlChol<L>::T) void bl_chol_kernel(BlView V, int panel, int cur, int nsplit) {
   using K = Bl<L>;
   constexpr int LC = K::LC, NC_ = limbs_of(LC), WC = K::WC, B = K::B, NL = K::NL;
+  constexpr int T = BlChol<L>::T, EPT = BlChol<L>::EPT;
   using RC = R<NC_>;
   extern __shared__ double lds[];
   const BlProb p = bl_prob<L>(V, blockIdx.x);
   BlMisc* misc = bl_at<BlMisc>(p, V.oMisc);
   const int k0 = panel * B;
-  if (k0 >= p.n || misc->flag) return;
+  if (k0 >= p.n) return;
+  const int flag = misc->flag;  // tested once the loads are on their way
   const int bcur = min(B, p.n - k0);
   const int tid = threadIdx.x;
-  double* G = lds;                    // [B][B] numbers
+  double* G = lds;                    // [B][B] numbers, rows published when final
   double* g0 = G + size_t(B) * B * WC;  // [B] diagonal before the factorisation
   double* dinv = g0 + B;              // [B][NC_] 1 / d
   double* sq = dinv + B * NC_;        // [B][NC_] sqrt(d)
   double* norm0 = sq + B * NC_;       // [B]
+  double* frow = norm0 + B;           // [B] numbers (quad double)
+  int* ex = reinterpret_cast<int*>(frow + B * WC);  // [B] column exponents
+  (void)frow;
   const int nch = (p.N + kBlRows - 1) / kBlRows;
   const int ns = min(nsplit, nch);
   const int* ce = bl_at<int>(p, V.oCe) + cur * V.nmax;
-  // S holds column j as [j][i]: entry (i, j) of the upper triangle
-  for (int idx = tid; idx < B * B; idx += kBlCholThreads) {
-    const int i = idx % B, j = idx / B;
-    if (i > j || j >= bcur) continue;
-    C<LC> g = c_zero<LC>();
-    for (int s = 0; s < ns; ++s) {
-      const double* Sp = reinterpret_cast<const double*>(p.base + V.oS + s * V.g_split);
-      const C<LC> t = load_aos<LC>(Sp + (size_t(j) * B + i) * WC);
-      g = s == 0 ? t : c_add(g, t);
+  if (tid < B) ex[tid] = tid < bcur ? ce[k0 + tid] - kExpOne : 0;
+  // entries in row order, so that whole wavefronts fall idle as rows finish;
+  // S holds column j as [j][i]
+  int ei[EPT], ej[EPT];
+  C<LC> g[EPT];
+#pragma unroll
+  for (int q = 0; q < EPT; ++q) {
+    int rest = tid + q * T, i = 0;
+    // rows above row i hold i B - i (i - 1) / 2 entries
+    i = int((2.0f * B + 1.0f - sqrtf((2.0f * B + 1.0f) * (2.0f * B + 1.0f) - 8.0f * float(rest))) * 0.5f);
+    i = max(0, min(B - 1, i));
+    while (i > 0 && i * B - i * (i - 1) / 2 > rest) --i;
+    while (i + 1 < B && (i + 1) * B - (i + 1) * i / 2 <= rest) ++i;
+    const int j = i + rest - (i * B - i * (i - 1) / 2);
+    const bool in = rest < BlChol<L>::ENTRIES && j < bcur;
+    ei[q] = in ? i : -1;
+    ej[q] = j;
+    g[q] = c_zero<LC>();
+    if (in) {
+      g[q] = bl_sum_splits<LC>(p.base + V.oS + (size_t(j) * B + i) * WC * 8, V.g_split, ns);
+      if (i == j) g0[i] = g[q].re.x[0];
+      if (i == 0) store_planar(G, B, j, g[q]);
     }
-    store_aos(G + (size_t(i) * B + j) * WC, g);
-    if (i == j) g0[i] = g.re.x[0];
   }
-  bool nonfinite = false;
-  for (int j = 0; j < bcur; ++j) nonfinite |= ce[k0 + j] == 0x7ff;
-  if (nonfinite) {  // uniform
-    if (tid == 0) misc->flag = 1;
-    return;
-  }
+  if (flag) return;
   constexpr double kPivot = NL == 1 ? 0x1p-26 : 0x1p-46;
-  bool bad = false;
+  bool bad = false, nonfinite = false;
   for (int k = 0; k < bcur; ++k) {
     __syncthreads();
-    const RC d = load_aos<LC>(G + (size_t(k) * B + k) * WC).re;
-    if (!(d.x[0] > kPivot * g0[k])) {
-      bad = true;
-      break;  // uniform
+    nonfinite |= ex[k] == 0x7ff - kExpOne;
+    const double* Gk = G + size_t(k) * B * WC;  // row k, planar
+    const RC d = load_planar<LC>(Gk, B, k).re;
+    bad |= !(d.x[0] > kPivot * g0[k]);
+    if constexpr (NC_ < 4) {
+      // the product does not wait for the reciprocal
+      C<LC> t[EPT];
+#pragma unroll
+      for (int q = 0; q < EPT; ++q)
+        if (ei[q] > k) t[q] = c_mul_conj_a(load_planar<LC>(Gk, B, ei[q]), load_planar<LC>(Gk, B, ej[q]));
+      const RC inv = bl_recip<NC_>(d);
+      if (tid == 0) r_store_aos(dinv + k * NC_, inv);
+#pragma unroll
+      for (int q = 0; q < EPT; ++q) {
+        if (ei[q] <= k) continue;
+        g[q] = c_sub(g[q], c_mul_r(t[q], inv));
+        if (ei[q] == k + 1) store_planar(G + size_t(k + 1) * B * WC, B, ej[q], g[q]);
+      }
+    } else {
+      // quad double: the row over its pivot once, by the first B threads
+      if (tid < B) {
+        const RC inv = bl_recip<NC_>(d);
+        if (tid == 0) r_store_aos(dinv + k * NC_, inv);
+        store_planar(frow, B, tid, c_mul_r(load_planar<LC>(Gk, B, tid), inv));
+      }
+      __syncthreads();
+#pragma unroll
+      for (int q = 0; q < EPT; ++q) {
+        if (ei[q] <= k) continue;
+        g[q] = c_sub(g[q], c_mul_conj_a(load_planar<LC>(Gk, B, ei[q]), load_planar<LC>(frow, B, ej[q])));
+        if (ei[q] == k + 1) store_planar(G + size_t(k + 1) * B * WC, B, ej[q], g[q]);
+      }
     }
-    const RC inv = r_recip(d);
-    if (tid == 0) r_store_aos(dinv + k * NC_, inv);
-    const int m = bcur - 1 - k;  // trailing rows and columns
-    for (int idx = tid; idx < m * m; idx += kBlCholThreads) {
-      const int i = k + 1 + idx / m, j = k + 1 + idx % m;
-      if (j < i) continue;
-      const C<LC> f = c_mul_r(load_aos<LC>(G + (size_t(k) * B + j) * WC), inv);
-      const C<LC> t = c_mul_conj_a(load_aos<LC>(G + (size_t(k) * B + i) * WC), f);
-      double* g = G + (size_t(i) * B + j) * WC;
-      C<LC> u = c_sub(load_aos<LC>(g), t);
-      store_aos(g, u);
-    }
+  }
+  if (nonfinite) {
+    if (tid == 0) misc->flag = 1;
+    return;
   }
   __syncthreads();
   const double thresh = double(p.n) * level_unit<L>();
@@ -702,18 +822,18 @@ __global__ __launch_bounds__(kBlCholThreads) void bl_chol_kernel(BlView V, int p
   if (!bad) {
     double* is = U + size_t(B) * B * K::W;
     if (tid < B) {
-      const RC d = tid < bcur ? load_aos<LC>(G + (size_t(tid) * B + tid) * WC).re : r_from_double<NC_>(1.0);
+      const RC d = tid < bcur ? load_planar<LC>(G + size_t(tid) * B * WC, B, tid).re : r_from_double<NC_>(1.0);
       const RC s = r_sqrt(d);
       r_store_aos(sq + tid * NC_, s);
       const RC q = r_recip(s);
 #pragma unroll
       for (int l = 0; l < NL; ++l) is[tid * NL + l] = q.x[l];
-      rexp[tid] = tid < bcur ? ce[k0 + tid] - kExpOne : 0;
+      rexp[tid] = ex[tid];
     }
     __syncthreads();
     bool singular = false;
     for (int j = 0; j < bcur; ++j) {
-      const double r = __builtin_ldexp(sq[j * NC_], ce[k0 + j] - kExpOne);
+      const double r = __builtin_ldexp(sq[j * NC_], ex[j]);
       rmax = fmax(rmax, r);
       if (!(r > thresh * rmax)) singular = true;
     }
@@ -721,7 +841,7 @@ __global__ __launch_bounds__(kBlCholThreads) void bl_chol_kernel(BlView V, int p
       if (tid == 0) misc->flag = 1;
       return;
     }
-    for (int idx = tid; idx < B * B; idx += kBlCholThreads) {
+    for (int idx = tid; idx < B * B; idx += T) {
       const int i = idx / B, j = idx % B;
       C<LC> u = c_zero<LC>();
       C<LC> r = u;
@@ -729,7 +849,7 @@ __global__ __launch_bounds__(kBlCholThreads) void bl_chol_kernel(BlView V, int p
       if (i == j) {
         r = c_from_r<LC>(s);
       } else if (i < j && j < bcur) {
-        u = c_mul_r(load_aos<LC>(G + (size_t(i) * B + j) * WC), r_load_aos<NC_>(dinv + i * NC_));
+        u = c_mul_r(load_planar<LC>(G + size_t(i) * B * WC, B, j), r_load_aos<NC_>(dinv + i * NC_));
         // the factor as the substitution takes it (rounded to the level)
         const C<L> un = bl_narrow<L>(u);
         C<LC> w = c_zero<LC>();
@@ -751,7 +871,7 @@ __global__ __launch_bounds__(kBlCholThreads) void bl_chol_kernel(BlView V, int p
   }
   // modified Gram-Schmidt on the panel itself
   double* Wp = bl_at<double>(p, V.oW);
-  for (int idx = tid; idx < B * B; idx += kBlCholThreads) {
+  for (int idx = tid; idx < B * B; idx += T) {
     store_aos(Rp + size_t(idx) * K::W, c_zero<L>());
     store_aos(U + size_t(idx) * K::W, c_zero<L>());
   }
@@ -769,7 +889,7 @@ __global__ __launch_bounds__(kBlCholThreads) void bl_chol_kernel(BlView V, int p
     __syncthreads();
     // entry (i, j) = sum over m = i .. j of R2[i][m] R1[m][j]: a thread owns a
     // column and goes down it, since entry (i, j) needs R1[m][j] for m >= i only
-    for (int j = tid; j < bcur; j += kBlCholThreads)
+    for (int j = tid; j < bcur; j += T)
       for (int i = 0; i <= j; ++i) {
         C<L> s = c_zero<L>();
         for (int m = i; m <= j; ++m)
@@ -786,14 +906,16 @@ __global__ __launch_bounds__(kBlCholThreads) void bl_chol_kernel(BlView V, int p
 template <int L>
 __host__ __device__ inline size_t bl_chol_lds() {
   using K = Bl<L>;
-  return (size_t(K::B) * K::B * K::WC + K::B * (2 + 2 * limbs_of(K::LC))) * sizeof(double);
+  return (size_t(K::B) * K::B * K::WC + K::B * (2 + 2 * limbs_of(K::LC) + K::WC)) * sizeof(double) + K::B * sizeof(int);
 }
 
 // ------------------------------------------------------------------ X = A U^-1 D^-1/2
 
-// Rows of X by forward substitution: a group of B lanes holds a row, lane j
-// its column j; step i broadcasts entry i and the lanes j > i subtract
-// a_i u_ij.  X replaces the panel in W; its digits are written in the two
+// Rows of X by forward substitution: a wavefront holds one or two rows, its
+// lanes the 64 real columns (complex: lane l the real part of column l,
+// l < 32, or the imaginary part of column l - 32); step i broadcasts entry i
+// through scalar registers, which the lanes of later columns multiply by
+// their u_ij.  X replaces the panel in W; its digits are written in the two
 // orders the products read: XD (rows contiguous, fixed point against 1) for
 // the contraction and XU ([chunk][digit][row][64 real columns], against the
 // row's largest entry, so that a small row keeps its relative precision) for
@@ -801,65 +923,134 @@ __host__ __device__ inline size_t bl_chol_lds() {
 // it spreads over the chip.  grid (64-row chunks * 64 / rows per workgroup,
 // slots), 256 threads
 template <int L>
+constexpr int bl_solve_rows() {
+  return limbs_of(L) == 4 ? 1 : 2;
+}
+
+__device__ __forceinline__ double bl_readlane(double v, int lane) {
+  const int64_t b = __double_as_longlong(v);
+  const int lo = __builtin_amdgcn_readlane(int(b), lane), hi = __builtin_amdgcn_readlane(int(b >> 32), lane);
+  return __longlong_as_double((int64_t(hi) << 32) | uint32_t(lo));
+}
+
+template <int L>
 __global__ __launch_bounds__(256) void bl_solve_kernel(BlView V, int panel, int cur) {
   using K = Bl<L>;
-  constexpr int B = K::B, NL = K::NL, ND = K::ND, CX = K::CX, RPW = 256 / B;
+  constexpr int B = K::B, NL = K::NL, ND = K::ND, CX = K::CX, NR = bl_solve_rows<L>(), RPW = 4 * NR;
+  using RL = R<NL>;
   extern __shared__ double lds[];
   const BlProb p = bl_prob<L>(V, blockIdx.y);
   const BlMisc* misc = bl_at<BlMisc>(p, V.oMisc);
   const int k0 = panel * B, r0 = blockIdx.x * RPW;
   const int NC = (p.N + kBlRows - 1) / kBlRows;
-  if (k0 >= p.n || r0 >= NC * kBlRows || misc->flag) return;
+  if (k0 >= p.n || r0 >= NC * kBlRows) return;
+  const int flag = misc->flag, mgs = misc->mgs;  // tested once the loads are on their way
   const int bcur = min(B, p.n - k0);
-  double* Us = lds;                             // [B][B] numbers
-  double* xs = lds + size_t(B) * B * K::W;      // [RPW][64][NL] results
+  constexpr int UP = is_real(L) ? NL : 4 * NL;  // planes of a row of U in LDS
+  double* Us = lds;                             // [B][planes][B]
+  double* xs = lds + size_t(B) * B * UP;        // [RPW][64][NL] results
   int* er = reinterpret_cast<int*>(xs + RPW * 64 * NL);  // [RPW] row exponents
   const double* U = bl_at<double>(p, V.oU);
   double* Wp = bl_at<double>(p, V.oW);
   const int64_t plane = int64_t(p.n + 1) * p.N;
-  const int tid = threadIdx.x, j = tid % B, rr = tid / B;
-  const int row = r0 + rr;
-  const bool live = row < p.N && j < bcur;
-  const bool mgs = misc->mgs != 0;
-  C<L> a = live ? load_planar<L>(Wp + int64_t(k0 + j) * p.N, plane, row) : c_zero<L>();
+  const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
+  const int j = lane % B, comp = lane / B;
+  RL a[NR];
+#pragma unroll
+  for (int r = 0; r < NR; ++r) {
+    const int row = r0 + wave * NR + r;
+    const bool live = row < p.N && j < bcur;
+#pragma unroll
+    for (int l = 0; l < NL; ++l)
+      a[r].x[l] = live ? Wp[(comp * NL + l) * plane + int64_t(k0 + j) * p.N + row] : 0.0;
+  }
+      // entry (i, j) of plane k at [i][k][j]: the lanes of a row read consecutive
+      // words; planes: real limbs, imaginary limbs, their negatives, real limbs
+      // again, so that a lane's two factors sit at fixed offsets
+#pragma unroll 16
+      for (int q = 0; q < B * B * K::W / 256; ++q) {
+        const int idx = tid + q * 256, k = idx % K::W, ij = idx / K::W;
+        const double u = U[idx];
+        double* at = Us + size_t(ij / B) * UP * B + ij % B;
+        if constexpr (is_real(L)) {
+          at[k * B] = u;
+        } else {
+          at[k * B] = u;
+          at[(k + 2 * NL) * B] = k < NL ? u : -u;
+        }
+      }
+  if (flag) return;
   if (!mgs) {
-    // entry (i, j) of component k at [i][k][j]: the lanes of a row read
-    // consecutive words
-    for (int idx = tid; idx < B * B * K::W; idx += 256) {
-      const int k = idx % K::W, ij = idx / K::W;
-      Us[(size_t(ij / B) * K::W + k) * B + ij % B] = U[idx];
-    }
     const double* is = U + size_t(B) * B * K::W;
-    R<NL> inv;
+    RL inv;
 #pragma unroll
     for (int l = 0; l < NL; ++l) inv.x[l] = is[j * NL + l];
-    if (live) a = bl_ldexp(a, -(bl_at<int>(p, V.oCe)[cur * V.nmax + k0 + j] - kExpOne));
+    const int ex = j < bcur ? -(bl_at<int>(p, V.oCe)[cur * V.nmax + k0 + j] - kExpOne) : 0;
+#pragma unroll
+    for (int r = 0; r < NR; ++r)
+#pragma unroll
+      for (int l = 0; l < NL; ++l) a[r].x[l] = __builtin_ldexp(a[r].x[l], ex);
     __syncthreads();
-    for (int i = 0; i + 1 < bcur; ++i) {
-      C<L> ai;
+    // a_i u_ij = re: ar ur + ai (-ui), im: ar ui + ai ur
+    const double* ux = Us + comp * NL * B + j;
+    const double* uy = Us + (comp ? 2 * NL : 3 * NL) * B + j;
+    auto load_u = [&](int i, RL& x, RL& y) {
 #pragma unroll
       for (int l = 0; l < NL; ++l) {
-        ai.re.x[l] = __shfl(a.re.x[l], i, B);
-        if constexpr (!is_real(L)) ai.im.x[l] = __shfl(a.im.x[l], i, B);
+        x.x[l] = ux[(size_t(i) * UP + l) * B];
+        if constexpr (!is_real(L)) y.x[l] = uy[(size_t(i) * UP + l) * B];
       }
-      const C<L> u = load_planar<L>(Us + size_t(i) * K::W * B, B, j);
-      // u is zero for j <= i
-      if (j > i) a = c_sub(a, c_mul(ai, u));
+    };
+    RL x, y, xn, yn;
+    load_u(0, xn, yn);
+    for (int i = 0; i + 1 < bcur; ++i) {
+      x = xn;
+      y = yn;
+      load_u(i + 1, xn, yn);
+      // the factors of columns up to i are zero: nothing to branch on
+      RL t[NR];
+#pragma unroll
+      for (int r = 0; r < NR; ++r) {
+        C<L> ai;
+#pragma unroll
+        for (int l = 0; l < NL; ++l) {
+          ai.re.x[l] = bl_readlane(a[r].x[l], i);
+          if constexpr (!is_real(L)) ai.im.x[l] = bl_readlane(a[r].x[l], B + i);
+        }
+        if constexpr (is_real(L))
+          t[r] = r_mul(ai.re, x);
+        else if constexpr (NL == 1)
+          t[r].x[0] = PE_FMA(ai.re.x[0], x.x[0], ai.im.x[0] * y.x[0]);
+        else if constexpr (NL == 2)
+          t[r] = dd_dot2(ai.re, x, ai.im, y, 1.0);
+        else
+          t[r] = qd_dot2(ai.re, x, ai.im, y);
+      }
+#pragma unroll
+      for (int r = 0; r < NR; ++r) a[r] = r_sub(a[r], t[r]);
     }
-    a = c_mul_r(a, inv);
-    if (live) store_planar(Wp + int64_t(k0 + j) * p.N, plane, row, a);
-  }
-  int e = live ? max(bl_exp(a.re.x[0]), bl_exp(im_lead(a))) : 0;
 #pragma unroll
-  for (int m = 1; m < B; m <<= 1) e = max(e, __shfl_xor(e, m));
+    for (int r = 0; r < NR; ++r) {
+      const int row = r0 + wave * NR + r;
+      a[r] = r_mul(a[r], inv);
+      if (row < p.N && j < bcur)
 #pragma unroll
-  for (int l = 0; l < NL; ++l) {
-    xs[(rr * 64 + j * CX) * NL + l] = a.re.x[l];
-    if constexpr (!is_real(L)) xs[(rr * 64 + j * CX + 1) * NL + l] = a.im.x[l];
+        for (int l = 0; l < NL; ++l)
+          Wp[(comp * NL + l) * plane + int64_t(k0 + j) * p.N + row] = a[r].x[l];
+    }
   }
-  if (j == 0) {
-    er[rr] = e - kExpOne;
-    bl_at<int>(p, V.oXr)[row] = e - kExpOne;
+#pragma unroll
+  for (int r = 0; r < NR; ++r) {
+    const int rr = wave * NR + r;
+    int e = bl_exp(a[r].x[0]);  // zero for rows and columns past the end
+#pragma unroll
+    for (int m = 1; m < 64; m <<= 1) e = max(e, __shfl_xor(e, m));
+#pragma unroll
+    for (int l = 0; l < NL; ++l) xs[(rr * 64 + j * CX + comp) * NL + l] = a[r].x[l];
+    if (lane == 0) {
+      er[rr] = e - kExpOne;
+      bl_at<int>(p, V.oXr)[r0 + rr] = e - kExpOne;
+    }
   }
   __syncthreads();
   const int ch = r0 / kBlRows, rin = r0 % kBlRows;
@@ -895,7 +1086,7 @@ __global__ __launch_bounds__(256) void bl_solve_kernel(BlView V, int panel, int 
 template <int L>
 __host__ __device__ inline size_t bl_solve_lds() {
   using K = Bl<L>;
-  return (size_t(K::B) * K::B * K::W + (256 / K::B) * 64 * K::NL) * sizeof(double) + (256 / K::B) * sizeof(int);
+  return (size_t(K::B) * K::B * (is_real(L) ? K::NL : 4 * K::NL) + 4 * bl_solve_rows<L>() * 64 * K::NL) * sizeof(double) + 4 * bl_solve_rows<L>() * sizeof(int);
 }
 
 // ------------------------------------------------------------------ R and T
@@ -915,23 +1106,19 @@ __global__ __launch_bounds__(256) void bl_fin_kernel(BlView V, int panel, int cu
   __shared__ double sl[CPW * B * CX];  // leading limbs of the columns of S
   const BlProb p = bl_prob<L>(V, blockIdx.y);
   const int k0 = panel * B;
-  if (k0 >= p.n || bl_at<BlMisc>(p, V.oMisc)->flag) return;
+  if (k0 >= p.n) return;
+  const int flag = bl_at<BlMisc>(p, V.oMisc)->flag;
   const int bcur = min(B, p.n - k0);
   const int c0 = blockIdx.x * CPW;
   if (k0 + c0 > p.n) return;
   const int ns = min(nsplit, (p.N + kBlRows - 1) / kBlRows);
   const int tid = threadIdx.x;
   auto sum = [&](int c, int i) {
-    C<L> s = c_zero<L>();
-    for (int t = 0; t < ns; ++t) {
-      const C<L> v =
-          load_aos<L>(reinterpret_cast<const double*>(p.base + V.oS + t * V.s_split) + (size_t(c) * B + i) * W);
-      s = t == 0 ? v : c_add(s, v);
-    }
-    return s;
+    return bl_sum_splits<L>(p.base + V.oS + (size_t(c) * B + i) * W * 8, V.s_split, ns);
   };
-  for (int idx = tid; idx < B * B; idx += 256) {
-    const int j = idx / B, i = idx % B;
+#pragma unroll 4
+  for (int q = 0; q < B * B / 256; ++q) {
+    const int idx = tid + q * 256, j = idx / B, i = idx % B;
     double re = 0.0, im = 0.0;
     if (i < bcur && j < bcur) {
       C<L> s = sum(j, i);
@@ -949,8 +1136,9 @@ __global__ __launch_bounds__(256) void bl_fin_kernel(BlView V, int panel, int cu
   C<L> s = in ? (own ? c_zero<L>() : sum(c, i)) : c_zero<L>();
   sl[tid * CX] = s.re.x[0];
   if (CX == 2) sl[tid * CX + 1] = im_lead(s);
+  if (flag) return;
   __syncthreads();
-  if (panel * B < p.n && blockIdx.x == 0)
+  if (blockIdx.x == 0)
     for (int idx = tid; idx < B * B * CX; idx += 256) bl_at<double>(p, V.oF)[size_t(panel) * B * B * CX + idx] = E[idx];
   double* R = bl_at<double>(p, V.oR);
   const int64_t rplane = int64_t(p.n + 1) * p.n;
@@ -1069,7 +1257,8 @@ __global__ __launch_bounds__(256, limbs_of(L) == 4 ? 1 : 2) void bl_update_kerne
   const BlProb p = bl_prob<L>(V, blockIdx.z);
   const int k0 = panel * B, k1 = k0 + B;
   const int ch = blockIdx.x;
-  if (k1 >= p.n || ch * kBlRows >= p.N || bl_at<BlMisc>(p, V.oMisc)->flag) return;
+  if (k1 >= p.n || ch * kBlRows >= p.N) return;
+  const int flag = bl_at<BlMisc>(p, V.oMisc)->flag;
   // tiles count from the panel's first column; its own 64 real columns are 4 tiles
   const int ntiles = ((p.n + 1 - k0) * CX + 15) / 16;
   const int t0 = 4 + blockIdx.y * tiles_per, t1 = min(ntiles, t0 + tiles_per);
@@ -1087,6 +1276,7 @@ __global__ __launch_bounds__(256, limbs_of(L) == 4 ? 1 : 2) void bl_update_kerne
   int er[4];
 #pragma unroll
   for (int r = 0; r < 4; ++r) er[r] = bl_at<int>(p, V.oXr)[row0 + r] - 12;
+  if (flag) return;
   for (int t = t0; t < t1; ++t) {
     const bl_v4i* sd = bl_at<bl_v4i>(p, V.oSD) + size_t(t) * ND * 64 + (lane & 15) * 4 + (lane >> 4);
     const int rc = t * 16 + (lane & 15);
@@ -1138,16 +1328,22 @@ __global__ __launch_bounds__(256, limbs_of(L) == 4 ? 1 : 2) void bl_update_kerne
 constexpr int kBlBsThreads = 512;
 
 // Diagonal block `stage` (of kBlBs rows, from the bottom) of R x = y, in
-// sub-blocks of 32 rows: a wavefront solves the sub-block (its triangle staged
-// in LDS, x_j broadcast from lane to lanes), then all threads subtract its
-// columns from the block's rows above.  grid (slots), 512 threads
+// sub-blocks of 32 rows.  Wavefront 0 solves a sub-block, its lanes the rows
+// (complex: real parts in the lower, imaginary parts in the upper half), x_j
+// broadcast through scalar registers, the triangle staged in LDS; then all
+// threads subtract its columns from the block's rows above, the next
+// sub-block's triangle being loaded meanwhile.  grid (slots), 512 threads
 template <int L>
 __global__ __launch_bounds__(kBlBsThreads) void bl_bs_diag_kernel(BlView V, int stage) {
-  constexpr int NL = limbs_of(L), W = width_of(L), SB = 32;
-  __shared__ double tri[SB * W * SB];  // [column][component][row]
+  constexpr int NL = limbs_of(L), W = width_of(L), SB = 32, PT = SB * SB / kBlBsThreads;
+  constexpr int RP = W <= 4 ? SB / 2 : 4;  // entries of R held per thread (registers)
+  using RL = R<NL>;
+  constexpr int TP = is_real(L) ? NL : 4 * NL;  // planes: re, im, re, -im
+  __shared__ double tri[SB * TP * SB];          // [column][plane][row]
   __shared__ double y[kBlBs * W];
+  __shared__ double dinv[kBlBs * NL];
   const BlProb p = bl_prob<L>(V, blockIdx.x);
-  if (bl_at<BlMisc>(p, V.oMisc)->flag) return;
+  const int flag = bl_at<BlMisc>(p, V.oMisc)->flag;
   const int e = p.n - stage * kBlBs;
   if (e <= 0) return;
   const int s = max(0, e - kBlBs);
@@ -1157,50 +1353,102 @@ __global__ __launch_bounds__(kBlBsThreads) void bl_bs_diag_kernel(BlView V, int 
   double* yw = bl_at<double>(p, V.oY);
   const double* inv = bl_at<double>(p, V.oInv);
   if (tid < e - s) {
-    const C<L> v = stage == 0 ? load_planar<L>(Rm + int64_t(p.n) * p.n, rplane, s + tid) : load_planar<L>(yw, p.n, s + tid);
+    const C<L> v =
+        stage == 0 ? load_planar<L>(Rm + int64_t(p.n) * p.n, rplane, s + tid) : load_planar<L>(yw, p.n, s + tid);
     store_planar(y, kBlBs, tid, v);
+    r_store_aos(dinv + tid * NL, r_load_aos<NL>(inv + size_t(s + tid) * NL));
   }
+  C<L> next[PT];  // the thread's entries of the next triangle
+  auto fetch = [&](int se) {
+    const int ss = max(s, se - SB), sb = se - ss;
+#pragma unroll
+    for (int q = 0; q < PT; ++q) {
+      const int idx = tid + q * kBlBsThreads, jj = idx / SB, ii = idx % SB;
+      next[q] = (jj < sb && ii < jj) ? load_planar<L>(Rm + int64_t(ss + jj) * p.n, rplane, ss + ii) : c_zero<L>();
+    }
+  };
+  fetch(e);
+  if (flag) return;
   for (int se = e; se > s; se -= SB) {
     const int ss = max(s, se - SB), sb = se - ss;
-    __syncthreads();
-    for (int idx = tid; idx < SB * SB; idx += kBlBsThreads) {
-      const int jj = idx / SB, ii = idx % SB;
-      if (jj < sb && ii < jj)
-        store_planar(tri + jj * W * SB, SB, ii, load_planar<L>(Rm + int64_t(ss + jj) * p.n, rplane, ss + ii));
+#pragma unroll
+    for (int q = 0; q < PT; ++q) {
+      const int idx = tid + q * kBlBsThreads;
+      store_planar(tri + (idx / SB) * TP * SB, SB, idx % SB, next[q]);
+      if constexpr (!is_real(L)) store_planar(tri + ((idx / SB) * TP + 2 * NL) * SB, SB, idx % SB, c_conj(next[q]));
     }
     __syncthreads();
+    if (ss > s) fetch(ss);
+    // rows above inside the block: two threads per row, even and odd columns,
+    // whose entries of R arrive while wavefront 0 solves
+    const int rows = ss - s, i = tid >> 1, h = tid & 1;
+    const double* Ri = Rm + int64_t(ss + h) * p.n + s + i;
+    C<L> rp[RP];
+#pragma unroll
+    for (int q = 0; q < RP; ++q)
+      rp[q] = (i < rows && h + 2 * q < sb) ? load_planar<L>(Ri + int64_t(2 * q) * p.n, rplane, 0) : c_zero<L>();
     if (tid < 64) {
-      const int ii = tid & (SB - 1);
-      C<L> v = ii < sb ? load_planar<L>(y, kBlBs, ss - s + ii) : c_zero<L>();
-      R<NL> dv = r_zero<NL>();
-      if (ii < sb) dv = r_load_aos<NL>(inv + size_t(ss + ii) * NL);
+      const int ii = is_real(L) ? (tid & (SB - 1)) : tid % SB, comp = is_real(L) ? 0 : tid / SB;
+      RL v = r_zero<NL>(), dv = v;
+      if (ii < sb) {
+#pragma unroll
+        for (int l = 0; l < NL; ++l) v.x[l] = y[(comp * NL + l) * kBlBs + ss - s + ii];
+        dv = r_load_aos<NL>(dinv + (ss - s + ii) * NL);
+      }
+      const double* fx = tri + comp * NL * SB + ii;
+      const double* fy = tri + (comp ? 2 * NL : 3 * NL) * SB + ii;
+      auto load_r = [&](int jj, RL& f, RL& g) {
+#pragma unroll
+        for (int l = 0; l < NL; ++l) {
+          f.x[l] = fx[(jj * TP + l) * SB];
+          if constexpr (!is_real(L)) g.x[l] = fy[(jj * TP + l) * SB];
+        }
+      };
+      RL f, g, fn, gn, res = v;
+      load_r(sb - 1, fn, gn);
       for (int jj = sb - 1; jj >= 0; --jj) {
-        const C<L> mine = c_mul_r(v, dv);
+        f = fn;
+        g = gn;
+        load_r(max(jj - 1, 0), fn, gn);
+        const RL mine = r_mul(v, dv);
         C<L> xj;
 #pragma unroll
         for (int l = 0; l < NL; ++l) {
-          xj.re.x[l] = __shfl(mine.re.x[l], jj, SB);
-          if constexpr (!is_real(L)) xj.im.x[l] = __shfl(mine.im.x[l], jj, SB);
+          xj.re.x[l] = bl_readlane(mine.x[l], jj);
+          if constexpr (!is_real(L)) xj.im.x[l] = bl_readlane(mine.x[l], SB + jj);
         }
-        if (ii == jj) {
-          if (tid < SB) store_planar(y, kBlBs, ss - s + ii, xj);
-        } else if (ii < jj) {
-          v = c_sub(v, c_mul(load_planar<L>(tri + jj * W * SB, SB, ii), xj));
-        }
+        RL t;
+        if constexpr (is_real(L))
+          t = r_mul(xj.re, f);
+        else if constexpr (NL == 1)
+          t.x[0] = PE_FMA(xj.re.x[0], f.x[0], xj.im.x[0] * g.x[0]);
+        else if constexpr (NL == 2)
+          t = dd_dot2(xj.re, f, xj.im, g, 1.0);
+        else
+          t = qd_dot2(xj.re, f, xj.im, g);
+        if (ii == jj) res = mine;
+        v = r_sub(v, t);  // the entries of rows from jj on are zero
+      }
+      if (ii < sb && (!is_real(L) || tid < SB)) {
+#pragma unroll
+        for (int l = 0; l < NL; ++l) y[(comp * NL + l) * kBlBs + ss - s + ii] = res.x[l];
       }
     }
     __syncthreads();
-    // rows above inside the block: two threads per row, even and odd columns
-    const int rows = ss - s, i = tid >> 1, h = tid & 1;
     C<L> acc = c_zero<L>();
-    if (i < rows)
-      for (int jj = h; jj < sb; jj += 2)
-        acc = c_add(acc, c_mul(load_planar<L>(Rm + int64_t(ss + jj) * p.n, rplane, s + i),
-                               load_planar<L>(y, kBlBs, ss - s + jj)));
+    if (i < rows) {
+#pragma unroll
+      for (int q = 0; q < RP; ++q)
+        if (h + 2 * q < sb) acc = c_add(acc, c_mul(rp[q], load_planar<L>(y, kBlBs, ss - s + h + 2 * q)));
+#pragma unroll 4
+      for (int q = RP; h + 2 * q < sb; ++q)
+        acc = c_add(acc, c_mul(load_planar<L>(Ri + int64_t(2 * q) * p.n, rplane, 0),
+                               load_planar<L>(y, kBlBs, ss - s + h + 2 * q)));
+    }
     acc = c_add(acc, shfl_xor_c(acc, 1));
     if (i < rows && h == 0) store_planar(y, kBlBs, i, c_sub(load_planar<L>(y, kBlBs, i), acc));
+    __syncthreads();
   }
-  __syncthreads();
   if (tid < e - s) store_planar(yw, p.n, s + tid, load_planar<L>(y, kBlBs, tid));
 }
 
@@ -1227,6 +1475,7 @@ __global__ __launch_bounds__(256) void bl_bs_update_kernel(BlView V, int stage) 
   const int i = r0 + (tid & 31), part = tid >> 5;
   C<L> acc = c_zero<L>();
   if (i < s)
+#pragma unroll 8
     for (int j = part * (kBlBs / 8); j < (part + 1) * (kBlBs / 8); ++j)
       acc = c_add(acc, c_mul(load_planar<L>(R + int64_t(s + j) * p.n, rplane, i), load_planar<L>(xs, kBlBs, j)));
   __syncthreads();

@@ -324,7 +324,8 @@ hipError_t launch_blockls(const BlView& V, int slots, int Nm, int nm, hipStream_
   const unsigned S = unsigned(slots);
   const int NC = (Nm + kBlRows - 1) / kBlRows;
   hipError_t e;
-  const size_t chol_lds = bl_chol_lds<L>(), solve_lds = bl_solve_lds<L>();
+  const size_t chol_lds = bl_chol_lds<L>(), solve_lds = bl_solve_lds<L>(), gram_lds = bl_gram_lds<L>();
+  if ((e = allow_lds(bl_gram_kernel<L>, gram_lds)) != hipSuccess) return e;
   if ((e = allow_lds(bl_chol_kernel<L>, chol_lds)) != hipSuccess) return e;
   if ((e = allow_lds(bl_solve_kernel<L>, solve_lds)) != hipSuccess) return e;
   hipLaunchKernelGGL(bl_init_kernel<L>, dim3(S), dim3(256), 0, st, V);
@@ -336,14 +337,13 @@ hipError_t launch_blockls(const BlView& V, int slots, int Nm, int nm, hipStream_
   for (int panel = 0, k0 = 0; k0 < nm; ++panel, k0 += K::B) {
     const int cur = panel & 1;
     const int real_cols = (nm + 1 - k0) * K::CX;
-    hipLaunchKernelGGL(bl_slice_kernel<L>, dim3(unsigned(NC), S), dim3(256), 0, st, V, panel, cur);
     const int gt = 64 / (16 * K::NT), gs = splits(gt, kBlGramSplit);
-    hipLaunchKernelGGL((bl_dot_kernel<L, true>), dim3(unsigned(gt), unsigned(gs), S), dim3(256), 0, st, V, panel, cur, gs);
-    hipLaunchKernelGGL(bl_chol_kernel<L>, dim3(S), dim3(kBlCholThreads), chol_lds, st, V, panel, cur, gs);
-    hipLaunchKernelGGL(bl_solve_kernel<L>, dim3(unsigned(NC * kBlRows / (256 / K::B)), S), dim3(256), solve_lds, st, V,
+    hipLaunchKernelGGL(bl_gram_kernel<L>, dim3(unsigned(gt), unsigned(gs), S), dim3(256), gram_lds, st, V, panel, cur, gs);
+    hipLaunchKernelGGL(bl_chol_kernel<L>, dim3(S), dim3(BlChol<L>::T), chol_lds, st, V, panel, cur, gs);
+    hipLaunchKernelGGL(bl_solve_kernel<L>, dim3(unsigned(NC * kBlRows / (4 * bl_solve_rows<L>())), S), dim3(256), solve_lds, st, V,
                        panel, cur);
     const int dt = (real_cols + 16 * K::NT - 1) / (16 * K::NT), ds = splits(dt, kBlMaxSplit);
-    hipLaunchKernelGGL((bl_dot_kernel<L, false>), dim3(unsigned(dt), unsigned(ds), S), dim3(256), 0, st, V, panel, cur,
+    hipLaunchKernelGGL(bl_dot_kernel<L>, dim3(unsigned(dt), unsigned(ds), S), dim3(256), 0, st, V, panel, cur,
                        ds);
     const int cpw = 256 / K::B;
     hipLaunchKernelGGL(bl_fin_kernel<L>, dim3(unsigned((nm + 1 - k0 + cpw - 1) / cpw), S), dim3(256), 0, st, V, panel,
