@@ -24,10 +24,10 @@ HIPCC = os.environ.get("HIPCC", "/opt/rocm/bin/hipcc")
 ARCH = os.environ.get("PE_OFFLOAD_ARCH", "gfx950")
 
 LEVELS = (1, 2, 4)
-KINDS = (0, 1, 2, 3, 4)  # rows, adjoint, batch, Gauss-Newton, least squares
+KINDS = (0, 1, 2, 3, 4, 5)  # rows, adjoint, batch, homotopy right-hand side, least squares, monomial values
 # real-arithmetic level codes (8 | limbs) and the kinds compiled for them
 REAL_LEVELS = (9, 10, 12)
-REAL_KINDS = (0, 3, 4)
+REAL_KINDS = (0, 3, 4, 5)
 
 FLAGS = ["-O3", "-std=c++17", f"--offload-arch={ARCH}", "-fPIC", "-ffp-contract=off", "-fno-fast-math",
          "-Xclang", "-target-feature", "-Xclang", "-packed-fp32-ops",

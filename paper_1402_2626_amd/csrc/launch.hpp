@@ -10,6 +10,7 @@
 #include "blockls_kernels.hpp"
 #include "eval_kernels.hpp"
 #include "newton_kernels.hpp"
+#include "value_kernels.hpp"
 
 namespace pe {
 
@@ -78,6 +79,27 @@ hipError_t launch_batch(const BatchShape& b, int P, const double* x, const Batch
 template <int L>
 hipError_t launch_rhs_shift(double* W, int64_t w_pt, int64_t plane, int64_t ld, int N, int n, int P, const double* c,
                             double wF, double wc, hipStream_t st);
+
+// evaluation through monomial values (value_kernels.hpp); lds: bytes of a
+// workgroup of one copy
+template <int L>
+hipError_t launch_val_rows(const ValView& V, int P, const double* x, const OutView& O, int mode, hipStream_t st);
+template <int L>
+hipError_t launch_val_adjoint(const ValView& V, int P, const double* x, const double* v, int NG, int gsize, double* part,
+                              double* g, hipStream_t st);
+
+// a batch's items whose systems evaluate through monomial values
+struct ValBatchShape {
+  size_t lds = 0;
+  int64_t nitems = 0;
+  const uint64_t* items = nullptr;
+  const ValView* views = nullptr;
+  const int64_t* x_off = nullptr;
+  int* counter = nullptr;
+};
+template <int L>
+hipError_t launch_val_batch(const ValBatchShape& b, int P, const double* x, const BatchOut& out, int mode,
+                            hipStream_t st);
 
 // Least-squares solve (blockls_kernels.hpp) of `slots` problems of at most
 // Nm rows and nm unknowns, whose workspace slots V.ws holds.
@@ -305,6 +327,81 @@ hipError_t launch_batch(const BatchShape& K, int P, const double* x, const Batch
   PE_SHAPES(PE_X)
 #undef PE_X
   return hipErrorInvalidValue;
+}
+
+// Copies per workgroup and rows per copy: one row per workgroup of one copy
+// while the rows are fewer than the chip can hold at once (about 1024
+// workgroups), then copies of narrow systems side by side (256 threads) and up
+// to four rows behind one table.  Rows of uneven cost stay apart, so that the
+// longest start first.  A launch of at most 1024 rows leaves wavefront slots
+// idle: a copy then has a wavefront for F besides those of the slices (DD, n =
+// 128, 64 x 12: 8.9 us against 9.4 at P = 1; at P = 64 the wider copies would
+// take 67 us against 48).  No sum depends on the number of wavefronts.
+template <int L, int MODE>
+hipError_t launch_val_rows_t(ValView V, int P, const double* x, const OutView& O, hipStream_t st) {
+  auto kern = val_rows_kernel<L, MODE>;
+  const size_t copy = val_copy_doubles<L>(V.n, V.emax, V.max_mon, V.multi != 0);
+  const int64_t rows = int64_t(P) * V.N;
+  if (rows <= 1024)
+    while ((1 << V.lgvw) < kValThreads && (1 << V.lgvw) < 64 * std::max(V.max_units, V.slices + 1)) ++V.lgvw;
+  const int vw = 1 << V.lgvw;
+  int copies = 1;
+  if (!V.multi)
+    while (vw * copies * 2 <= 256 && rows >= 2048 * copies && copy * copies * 2 * sizeof(double) <= 65536) copies *= 2;
+  const int Rr = V.row_order ? 1 : int(std::max<int64_t>(1, std::min<int64_t>({4, rows / (1024 * copies), V.N})));
+  const size_t lds = copy * copies * sizeof(double);
+  hipError_t e = allow_lds(kern, lds);
+  if (e != hipSuccess) return e;
+  const int groups = (V.N + Rr - 1) / Rr;
+  const int64_t items = int64_t(P) * groups;
+  hipLaunchKernelGGL(kern, dim3(unsigned((items + copies - 1) / copies)), dim3(unsigned(vw * copies)), lds, st, V, O, x,
+                     int64_t(width_of(L)) * V.n, P, copies, Rr, groups, int(copy));
+  return hipGetLastError();
+}
+
+template <int L>
+hipError_t launch_val_rows(const ValView& V, int P, const double* x, const OutView& O, int mode, hipStream_t st) {
+  return mode == MODE_EVAL ? launch_val_rows_t<L, MODE_EVAL>(V, P, x, O, st)
+                           : launch_val_rows_t<L, MODE_FONLY>(V, P, x, O, st);
+}
+
+template <int L>
+hipError_t launch_val_adjoint(const ValView& V, int P, const double* x, const double* v, int NG, int gsize, double* part,
+                              double* g, hipStream_t st) {
+  auto kern = val_adjoint_kernel<L>;
+  const size_t lds = val_copy_doubles<L>(V.n, V.emax, V.max_mon, true) * sizeof(double);
+  hipError_t e = allow_lds(kern, lds);
+  if (e != hipSuccess) return e;
+  hipLaunchKernelGGL(kern, dim3(unsigned(int64_t(P) * NG)), dim3(unsigned(std::max(1 << V.lgvw, 256))), lds, st, V, x,
+                     int64_t(width_of(L)) * V.n, v, int64_t(width_of(L)) * V.N, NG, gsize, part);
+  if ((e = hipGetLastError()) != hipSuccess) return e;
+  // grid.y is limited to 65535 points per launch
+  for (int p0 = 0; p0 < P; p0 += 65535) {
+    const int np = std::min(65535, P - p0);
+    const size_t num = size_t(width_of(L)) * V.n;
+    hipLaunchKernelGGL(val_adjoint_reduce_kernel<L>, dim3(unsigned((V.n + 63) / 64), unsigned(np)), dim3(256), 0, st, V.n,
+                       NG, (const double*)part + p0 * size_t(NG) * num, g + p0 * num);
+  }
+  return hipGetLastError();
+}
+
+template <int L, int MODE>
+hipError_t launch_val_batch_t(const ValBatchShape& K, int P, const double* x, const BatchOut& out, hipStream_t st) {
+  auto kern = val_batch_kernel<L, MODE>;
+  hipError_t e = allow_lds(kern, K.lds);
+  if (e != hipSuccess) return e;
+  int64_t grid = 0;
+  if ((e = persistent_grid(kern, kValThreads, K.lds, K.nitems, grid)) != hipSuccess) return e;
+  hipLaunchKernelGGL(kern, dim3(unsigned(grid)), dim3(kValThreads), K.lds, st, K.views, K.items, K.nitems, K.counter, P,
+                     x, K.x_off, out);
+  return hipGetLastError();
+}
+
+template <int L>
+hipError_t launch_val_batch(const ValBatchShape& K, int P, const double* x, const BatchOut& out, int mode,
+                            hipStream_t st) {
+  return mode == MODE_EVAL ? launch_val_batch_t<L, MODE_EVAL>(K, P, x, out, st)
+                           : launch_val_batch_t<L, MODE_FONLY>(K, P, x, out, st);
 }
 
 template <int L>

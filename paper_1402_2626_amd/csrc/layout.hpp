@@ -52,4 +52,38 @@ constexpr int kMaxSeg = 16;      // largest segment any kernel variant handles
 constexpr int kMaxWave = 64;     // lanes per wavefront on gfx950
 constexpr int kMaxMonomialVars = kMaxWave * kMaxSeg;  // 1024
 
+// ------------------------------------------------------------------ value layout
+//
+// A second packing of the same system for the evaluation through monomial
+// values (value_kernels.hpp): the product phase takes UNITS of one wavefront,
+// the column phase the rows' occurrences by COLUMN.
+//
+// A unit is up to 64 / s monomials, s lanes each (a power of two); lane l's
+// record i is rec[base + 64 i + l], the index (exp - 1) (n + 1) + var of the
+// factor in the table of powers, padded with the neutral record n (variable
+// n, the constant 1).  The monomials of a row are in the same
+// order as in the chunks (larger first).
+struct ValUnit {
+  uint32_t base;  // first record
+  uint16_t mon;   // first monomial, counted from the block's first
+  uint8_t count;  // monomials
+  uint8_t lgs;    // log2 of the lanes per monomial
+  uint32_t seg;   // records per lane
+  uint32_t pad;
+};
+
+// A block is a run of a row's units whose monomial values fit in LDS together.
+// Its column lists are stored in slices of 64 lanes, Q lanes per column, the
+// row's columns in decreasing length (val_perm): entry i of lane l of slice c
+// is ell[64 (slice[slice0 + c] + i) + l], monomial (from the block's first) |
+// exponent << 16, padded with the dummy monomial `nmon` (value 0) and
+// exponent 0; the slice ends at slice[slice0 + c + 1].
+struct ValBlock {
+  uint32_t unit0, unit1;
+  uint32_t mon0;      // first monomial (packed order)
+  uint32_t nmon;
+  uint32_t slice0;
+  uint32_t pad;
+};
+
 }  // namespace pe

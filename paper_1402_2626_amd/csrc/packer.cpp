@@ -19,6 +19,15 @@ int lanes_for(int k, int seg) {
   return s;
 }
 
+// log2 of a monomial's lanes in the value layout: the fewest that leave at most 12
+// factors per lane (a lane's factors are one chain of products, the lanes'
+// are joined by log2 s more)
+static int val_lg_lanes(int k) {
+  int lg = 0;
+  while (lg < 6 && (k + (1 << lg) - 1) >> lg > 12) ++lg;
+  return lg;
+}
+
 int validate(const SysInput& in, std::string& msg) {
   // level codes: 1, 2, 4 complex; 8 | 1, 8 | 2, 8 | 4 real (layout.hpp)
   if ((in.level & ~kRealLevel) != 1 && (in.level & ~kRealLevel) != 2 && (in.level & ~kRealLevel) != 4) {
@@ -159,13 +168,8 @@ int pack_system(const SysInput& in, const PackParams& pp, Packed& out, std::stri
   out.poly_cost.assign(size_t(N), 0);
 
   std::vector<int64_t> order;
-  std::vector<Occ> occ_sorted;
-  struct Contrib {
-    int col, g, r;
-  };
-  std::vector<Contrib> contribs;
-  std::vector<int> counts;
-  std::vector<std::vector<int>> slot_of;
+  std::vector<Occ> chunk_occ;
+  std::vector<int> counts, next_slot;
 
   int64_t packed_t = 0;
   for (int p = 0; p < N; ++p) {
@@ -212,31 +216,26 @@ int pack_system(const SysInput& in, const PackParams& pp, Packed& out, std::stri
       }
       cd.colptr_base = uint32_t(out.colptr.size());
 
-      // contributions: (column, monomial in chunk, position) -> slot
-      contribs.clear();
-      slot_of.resize(size_t(count));
+      // slots by column, then monomial, then position: a counting sort over
+      // the columns that keeps the order of the monomials
+      chunk_occ.clear();
+      counts.assign(size_t(n) + 1, 0);
       for (int g = 0; g < count; ++g) {
         const int64_t t = order[i + g];
         const int64_t a = in.mon_ptr[t], b = in.mon_ptr[t + 1];
-        occ_sorted.clear();
-        for (int64_t o = a; o < b; ++o) occ_sorted.push_back({in.var_idx[o], in.exps[o], o});
-        std::sort(occ_sorted.begin(), occ_sorted.end(), [](const Occ& x, const Occ& y) { return x.var < y.var; });
-        for (int r = 0; r < int(occ_sorted.size()); ++r) contribs.push_back({occ_sorted[r].var, g, r});
-        slot_of[size_t(g)].assign(occ_sorted.size(), 0);
-      }
-      std::stable_sort(contribs.begin(), contribs.end(), [](const Contrib& x, const Contrib& y) {
-        if (x.col != y.col) return x.col < y.col;
-        if (x.g != y.g) return x.g < y.g;
-        return x.r < y.r;
-      });
-      // slot of (g, r): position in the sorted list
-      counts.assign(size_t(n) + 1, 0);
-      for (int sidx = 0; sidx < int(contribs.size()); ++sidx) {
-        const Contrib& c = contribs[size_t(sidx)];
-        slot_of[size_t(c.g)][size_t(c.r)] = sidx;
-        counts[size_t(c.col) + 1]++;
+        const size_t first = chunk_occ.size();
+        bool sorted = true;
+        for (int64_t o = a; o < b; ++o) {
+          sorted = sorted && (o == a || in.var_idx[o - 1] < in.var_idx[o]);
+          chunk_occ.push_back({in.var_idx[o], in.exps[o], o});
+          counts[size_t(in.var_idx[o]) + 1]++;
+        }
+        if (!sorted)
+          std::sort(chunk_occ.begin() + int64_t(first), chunk_occ.end(),
+                    [](const Occ& x, const Occ& y) { return x.var < y.var; });
       }
       for (int c = 0; c < n; ++c) counts[size_t(c) + 1] += counts[size_t(c)];
+      next_slot.assign(counts.begin(), counts.end());
       for (int c = 0; c <= n; ++c) out.colptr.push_back(uint16_t(counts[size_t(c)]));
 
       // occurrence records, lane-major; positions past a lane's segment hold
@@ -247,30 +246,24 @@ int pack_system(const SysInput& in, const PackParams& pp, Packed& out, std::stri
       out.occ.resize(rec0 + size_t(segc) * cd.width, pad);
       out.occ_orig.resize(rec0 + size_t(segc) * cd.width, kNoOcc);
       int64_t cost = 0;
+      size_t at = 0;
       for (int g = 0; g < count; ++g) {
         const int64_t t = order[i + g];
-        const int64_t a = in.mon_ptr[t], b = in.mon_ptr[t + 1];
-        const int k = int(b - a);
-        occ_sorted.clear();
-        for (int64_t o = a; o < b; ++o) occ_sorted.push_back({in.var_idx[o], in.exps[o], o});
-        std::sort(occ_sorted.begin(), occ_sorted.end(), [](const Occ& x, const Occ& y) { return x.var < y.var; });
+        const int k = int(in.mon_ptr[t + 1] - in.mon_ptr[t]);
+        const Occ* occ_sorted = chunk_occ.data() + at;
+        at += size_t(k);
         // lane q of the group takes occurrences q, q + s, q + 2s, ... (in
         // variable order): a wavefront's gathers and slot stores at one step
         // then touch neighbouring variables when a monomial's variables are
         // runs of consecutive indices, instead of addresses a segment apart
-        const int base = k / s, extra = k % s;
-        for (int q = 0; q < s; ++q) {
-          const int len = base + (q < extra ? 1 : 0);
-          const int lane = g * s + q;
-          for (int ii = 0; ii < len; ++ii) {
-            const int r = q + ii * s;
-            const Occ& oc = occ_sorted[size_t(r)];
-            OccRec& rec = out.occ[rec0 + size_t(ii) * cd.width + size_t(lane)];
-            rec.var = uint16_t(oc.var);
-            rec.exp = uint16_t(oc.exp);
-            rec.slot = uint16_t(slot_of[size_t(g)][size_t(r)]);
-            out.occ_orig[rec0 + size_t(ii) * cd.width + size_t(lane)] = uint32_t(oc.orig);
-          }
+        for (int r = 0; r < k; ++r) {
+          const Occ& oc = occ_sorted[r];
+          const size_t pos = rec0 + size_t(r / s) * cd.width + size_t(g * s + r % s);
+          OccRec& rec = out.occ[pos];
+          rec.var = uint16_t(oc.var);
+          rec.exp = uint16_t(oc.exp);
+          rec.slot = uint16_t(next_slot[size_t(oc.var)]++);
+          out.occ_orig[pos] = uint32_t(oc.orig);
         }
         // packed monomial: coefficient and metadata
         for (int c = 0; c < ncomp; ++c)
@@ -292,6 +285,163 @@ int pack_system(const SysInput& in, const PackParams& pp, Packed& out, std::stri
     for (uint32_t j = 0; j < uint32_t(kRowDesc) && out.chunk_ptr[p] + j < out.chunk_ptr[p + 1]; ++j)
       out.rowdesc[size_t(p) * kRowDesc + j] = out.chunks[out.chunk_ptr[p] + j];
   return kOk;
+}
+
+// Lanes join by a shuffle and an addition, as long as about four entries of a
+// lane's own sum: a column is split while its halves keep 8 entries and the
+// row's columns take at most eight wavefronts.
+int val_lg_lanes_per_column(int n, int64_t len) {
+  int lg = 0;
+  while (lg < 3 && (int64_t(n) << (lg + 1)) <= 512 && len >> (lg + 1) >= 8) ++lg;
+  return lg;
+}
+
+bool pack_values(const SysInput& in, int block_mons, PackedValues& out) {
+  const int n = in.n_vars, N = in.n_polys;
+  if (n > 32768 || block_mons < 1 || block_mons > 65534) return false;
+  out = PackedValues();
+  int64_t longest = 0;
+  for (int p = 0; p < N; ++p)
+    longest = std::max<int64_t>(longest, in.mon_ptr[in.poly_ptr[p + 1]] - in.mon_ptr[in.poly_ptr[p]]);
+  out.lgQ = val_lg_lanes_per_column(n, longest / std::max(n, 1));
+  const int Q = 1 << out.lgQ;
+  const int per = 64 / Q;  // columns of a slice
+  const int slices = out.slices = (n + per - 1) / per;
+  out.row_block.assign(size_t(N) + 1, 0);
+  out.perm.assign(size_t(N) * slices * per, uint16_t(n));
+  const int64_t nnz = in.poly_ptr[N] > 0 ? in.mon_ptr[in.poly_ptr[N]] : 0;
+  out.rec.reserve(size_t(nnz) + size_t(nnz) / 8);
+  out.ell.reserve(size_t(nnz) + size_t(nnz) / 4);
+  std::vector<int64_t> order;
+  std::vector<int> total, cnt, fill, bucket, place;
+  const uint32_t neutral = uint32_t(n), cols = uint32_t(n) + 1;
+  uint32_t packed = 0;
+  for (int p = 0; p < N; ++p) {
+    const int64_t t0 = in.poly_ptr[p], t1 = in.poly_ptr[p + 1];
+    const int64_t M = t1 - t0;
+    order.resize(size_t(M));
+    std::iota(order.begin(), order.end(), t0);
+    bool even = true;
+    for (int64_t t = t0 + 1; t < t1 && even; ++t)
+      even = in.mon_ptr[t + 1] - in.mon_ptr[t] <= in.mon_ptr[t] - in.mon_ptr[t - 1];
+    if (!even)
+      std::stable_sort(order.begin(), order.end(), [&](int64_t a, int64_t b) {
+        return (in.mon_ptr[a + 1] - in.mon_ptr[a]) > (in.mon_ptr[b + 1] - in.mon_ptr[b]);
+      });
+    // columns in decreasing number of occurrences in the row (counting sort)
+    total.assign(size_t(n), 0);
+    for (int64_t t = t0; t < t1; ++t)
+      for (int64_t o = in.mon_ptr[t]; o < in.mon_ptr[t + 1]; ++o) total[size_t(in.var_idx[o])]++;
+    int most = 0;
+    for (int c = 0; c < n; ++c) most = std::max(most, total[size_t(c)]);
+    bucket.assign(size_t(most) + 2, 0);
+    for (int c = 0; c < n; ++c) bucket[size_t(most - total[size_t(c)]) + 1]++;
+    for (int b = 0; b <= most; ++b) bucket[size_t(b) + 1] += bucket[size_t(b)];
+    uint16_t* perm = out.perm.data() + size_t(p) * slices * per;
+    place.resize(size_t(n));
+    for (int c = 0; c < n; ++c) {
+      const int at = bucket[size_t(most - total[size_t(c)])]++;
+      perm[at] = uint16_t(c);
+      place[size_t(c)] = at;
+    }
+    out.row_block[size_t(p)] = uint32_t(out.block.size());
+    int64_t done = 0;
+    do {
+      const int64_t nm = std::min<int64_t>(block_mons, M - done);
+      ValBlock blk{};
+      blk.unit0 = uint32_t(out.unit.size());
+      blk.mon0 = packed;
+      blk.nmon = uint32_t(nm);
+      // units
+      int64_t j = 0;
+      while (j < nm) {
+        const int64_t tf = order[size_t(done + j)];
+        const int kf = int(in.mon_ptr[tf + 1] - in.mon_ptr[tf]);
+        const int lgs = val_lg_lanes(kf), s = 1 << lgs;
+        ValUnit u{};
+        if (out.rec.size() > 0xffffffffu - 64u * 16u) return false;
+        u.base = uint32_t(out.rec.size());
+        u.mon = uint16_t(j);
+        u.lgs = uint8_t(lgs);
+        u.seg = uint32_t(std::max(1, (kf + s - 1) / s));
+        int count = 0;
+        while (j + count < nm && count < 64 / s) {
+          const int64_t t = order[size_t(done + j + count)];
+          if (val_lg_lanes(int(in.mon_ptr[t + 1] - in.mon_ptr[t])) != lgs) break;
+          ++count;
+        }
+        u.count = uint8_t(count);
+        out.rec.resize(out.rec.size() + 64 * size_t(u.seg), neutral);
+        for (int g = 0; g < count; ++g) {
+          const int64_t t = order[size_t(done + j + g)];
+          const int64_t a = in.mon_ptr[t], b = in.mon_ptr[t + 1];
+          uint32_t* r = out.rec.data() + u.base + size_t(g) * s;
+          for (int64_t o = a; o < b; ++o) {
+            const int i = int(o - a);
+            r[64 * (i / s) + i % s] = uint32_t(in.var_idx[o]) + uint32_t(in.exps[o] - 1) * cols;
+          }
+        }
+        out.unit.push_back(u);
+        j += count;
+      }
+      blk.unit1 = uint32_t(out.unit.size());
+      // column lists
+      const std::vector<int>* c_of = &total;
+      if (M > block_mons) {
+        cnt.assign(size_t(n), 0);
+        for (int64_t g = 0; g < nm; ++g) {
+          const int64_t t = order[size_t(done + g)];
+          for (int64_t o = in.mon_ptr[t]; o < in.mon_ptr[t + 1]; ++o) cnt[size_t(in.var_idx[o])]++;
+        }
+        c_of = &cnt;
+        out.multi = true;
+      }
+      blk.slice0 = uint32_t(out.slice.size());
+      uint32_t rows = uint32_t(out.ell.size() / 64);
+      for (int c = 0; c < slices; ++c) {
+        out.slice.push_back(rows);
+        int len = 0;
+        for (int x = 0; x < per && c * per + x < n; ++x)
+          len = std::max(len, ((*c_of)[perm[c * per + x]] + Q - 1) / Q);
+        rows += uint32_t(len);
+      }
+      out.slice.push_back(rows);
+      if (rows > 0xffffffffu / 64) return false;
+      out.ell.resize(size_t(rows) * 64, uint32_t(nm));
+      fill.assign(size_t(n), 0);
+      const uint32_t* sl = out.slice.data() + blk.slice0;
+      for (int64_t g = 0; g < nm; ++g) {
+        const int64_t t = order[size_t(done + g)];
+        for (int64_t o = in.mon_ptr[t]; o < in.mon_ptr[t + 1]; ++o) {
+          const int col = in.var_idx[o], at = place[size_t(col)], e = fill[size_t(col)]++;
+          out.ell[(size_t(sl[at / per]) + size_t(e / Q)) * 64 + size_t((at % per) * Q + e % Q)] =
+              uint32_t(g) | (uint32_t(in.exps[o]) << 16);
+        }
+      }
+      out.max_mon = std::max(out.max_mon, int(nm));
+      out.max_units = std::max(out.max_units, int(blk.unit1 - blk.unit0));
+      out.block.push_back(blk);
+      packed += uint32_t(nm);
+      done += nm;
+    } while (done < M);
+  }
+  out.row_block[size_t(N)] = uint32_t(out.block.size());
+  // uniform rows
+  if (N > 0 && !out.multi && out.block[0].nmon > 0) {
+    const ValUnit& f = out.unit[0];
+    const uint32_t nm = out.block[0].nmon, per = 64u >> f.lgs, units = (nm + per - 1) / per;
+    bool uni = true;
+    for (const ValBlock& b : out.block) uni = uni && b.nmon == nm && b.unit1 - b.unit0 == units;
+    for (size_t u = 0; u < out.unit.size() && uni; ++u)
+      uni = out.unit[u].lgs == f.lgs && out.unit[u].seg == f.seg && out.unit[u].base == uint32_t(u) * 64 * f.seg;
+    if (uni) {
+      out.uni_mons = int(nm);
+      out.uni_lgs = f.lgs;
+      out.uni_units = int(units);
+      out.uni_seg = int(f.seg);
+    }
+  }
+  return true;
 }
 
 }  // namespace pe

@@ -49,6 +49,31 @@ struct Packed {
   std::vector<int64_t> poly_cost;   // [N] relative cost of a polynomial (for scheduling)
 };
 
+// the value layout (layout.hpp)
+struct PackedValues {
+  int lgQ = 0;          // log2 of the lanes per column
+  int slices = 0;       // slices of a row: ceil(n Q / 64)
+  int max_mon = 0;      // largest number of monomials of a block
+  int max_units = 0;    // largest number of units of a block
+  bool multi = false;   // some row has more than one block
+  // every row has uni_mons monomials of 2^uni_lgs lanes and uni_seg records,
+  // uni_units units in one block: the units and blocks follow from the row's index (0: not so)
+  int uni_mons = 0, uni_lgs = 0, uni_seg = 0, uni_units = 0;
+  std::vector<uint32_t> rec, ell, slice;
+  std::vector<ValUnit> unit;
+  std::vector<ValBlock> block;
+  std::vector<uint32_t> row_block;  // [N+1]
+  std::vector<uint16_t> perm;       // [N][slices * 64 / Q], n where there is no column
+};
+
+// log2 of the lanes per column of the value layout, for n columns of at most
+// `len` occurrences on average over a row
+int val_lg_lanes_per_column(int n, int64_t len);
+
+// Packs the value layout of a valid system with n <= 32768; blocks of at most
+// `block_mons` monomials (< 65535).  False when an index does not fit.
+bool pack_values(const SysInput& in, int block_mons, PackedValues& out);
+
 // status codes as in the C ABI
 constexpr int kOk = 0, kEinval = -1, kEnomem = -2, kEunsupported = -3;
 

@@ -140,6 +140,10 @@ struct pe_system {
   Packed host;  // kept for batches and tuning (structure only)
   Plan plan;
   SysView view{};
+  // evaluation through monomial values, when the system suits it
+  bool use_val = false;      // F and J
+  bool use_val_adj = false;  // the adjoint (its column sums take more LDS)
+  ValView val{};
   std::vector<void*> allocs;
   size_t device_bytes = 0;
   // batches that hold a copy of this system's device view; while any is
@@ -172,6 +176,15 @@ EvalShape eval_shape(const pe_system* sys) {
 
 hipError_t dispatch_rows(const pe_system* sys, int P, const double* x, const OutView& O, int mode,
                          hipStream_t st) {
+  if (sys->use_val) {
+    switch (sys->code) {
+#define PE_C(C_) \
+  case C_: return launch_val_rows<C_>(sys->val, P, x, O, mode, st);
+      PE_C(1) PE_C(2) PE_C(4) PE_C(PE_REAL | 1) PE_C(PE_REAL | 2) PE_C(PE_REAL | 4)
+#undef PE_C
+    }
+    return hipErrorInvalidValue;
+  }
   const EvalShape sh = eval_shape(sys);
   switch (sys->code) {
     case 1: return launch_rows<1>(sh, P, x, O, mode, st);
@@ -186,6 +199,14 @@ hipError_t dispatch_rows(const pe_system* sys, int P, const double* x, const Out
 
 hipError_t dispatch_adj(const pe_system* sys, int P, const double* x, const double* v, int NG, int gsize,
                         double* part, double* g, hipStream_t st) {
+  if (sys->use_val_adj) {
+    switch (sys->code) {
+      case 1: return launch_val_adjoint<1>(sys->val, P, x, v, NG, gsize, part, g, st);
+      case 2: return launch_val_adjoint<2>(sys->val, P, x, v, NG, gsize, part, g, st);
+      case 4: return launch_val_adjoint<4>(sys->val, P, x, v, NG, gsize, part, g, st);
+    }
+    return hipErrorInvalidValue;
+  }
   const EvalShape sh = eval_shape(sys);
   switch (sys->code) {
     case 1: return launch_adjoint<1>(sh, P, x, v, NG, gsize, part, g, st);
@@ -283,6 +304,7 @@ int slots_for(int L, int seg) {
 }
 
 void free_device(pe_system* sys) {
+  sys->use_val = sys->use_val_adj = false;
   for (void* p : sys->allocs) (void)hipFree(p);
   sys->allocs.clear();
   sys->device_bytes = 0;
@@ -303,6 +325,101 @@ SysInput stored_input(const pe_system* sys) {
   in.exps = sys->in_exp.data();
   in.coef = sys->in_coef.data();
   return in;
+}
+
+size_t val_doubles(int code, int n, int emax, int max_mon, bool sums) {
+  switch (code) {
+    case 1: return val_copy_doubles<1>(n, emax, max_mon, sums);
+    case 2: return val_copy_doubles<2>(n, emax, max_mon, sums);
+    case 4: return val_copy_doubles<4>(n, emax, max_mon, sums);
+    case PE_REAL | 1: return val_copy_doubles<PE_REAL | 1>(n, emax, max_mon, sums);
+    case PE_REAL | 2: return val_copy_doubles<PE_REAL | 2>(n, emax, max_mon, sums);
+  }
+  return val_copy_doubles<PE_REAL | 4>(n, emax, max_mon, sums);
+}
+
+// monomials of a block of the value layout: 32 KB of values
+int val_block_mons(int code) { return 4096 / width_of(code); }
+
+// half of a CU's LDS (two workgroups per CU); quad double, which is bound by
+// arithmetic, all of it
+size_t val_lds_limit(const pe_system* sys) {
+  return sys->level == 4 ? device_lds_limit() : device_lds_limit() / 2;
+}
+
+// Whether a system is evaluated through monomial values (value_kernels.hpp).
+// The products are k per monomial of k variables against about 4 k - 3, so
+// the mean k has to be 4 or more for the extra product and reciprocal per
+// column not to cost precision or time; a row's table of powers and
+// reciprocals costs about emax + 3 products per variable, so a row has to
+// touch each variable twice on average (at one occurrence per variable the
+// reverse sweep without a table is faster: the shape of Table 1 runs at the
+// memory's rate); the powers, the reciprocals and a block's values have to
+// fit in val_lds_limit; rows of J are not tiled.
+// Numbers of one or two doubles (D, real D, real DD) need rows of two or more
+// chunks besides: their products cost so little that one chunk in registers is
+// ahead when the launch is short (D, n = N = 32, P = 1: 4.9 us against 6.0 in
+// a graph; real D, n = 256, 128 x 16, P = 8: 11.7 against 13.5), while chunks
+// in sequence are not (D, n = 128, 256 x 16, P = 8: 28 us against 18).
+bool val_suits(const pe_system* sys) {
+  const Packed& H = sys->host;
+  if (H.N == 0 || H.M == 0 || H.n > kTileCols) return false;
+  if (H.nnz < 4 * H.M || H.nnz < 2 * int64_t(H.N) * H.n) return false;
+  int64_t most = 0;
+  int chunks = 0;
+  for (int p = 0; p < H.N; ++p) {
+    most = std::max(most, sys->in_poly_ptr[p + 1] - sys->in_poly_ptr[p]);
+    chunks = std::max<int>(chunks, H.chunk_ptr[p + 1] - H.chunk_ptr[p]);
+  }
+  if (width_of(sys->code) <= 2 && chunks < 2) return false;
+  const int mons = int(std::min<int64_t>(most, val_block_mons(sys->code)));
+  if (H.emax > 64) return false;
+  return val_doubles(sys->code, H.n, H.emax, mons, most > mons) * sizeof(double) <= val_lds_limit(sys);
+}
+
+// Pack and upload the value layout; on success sys->val is complete.
+pe_status upload_values(pe_system* sys, hipStream_t hs) {
+  sys->use_val = sys->use_val_adj = false;
+  if (!val_suits(sys)) return PE_OK;
+  PackedValues PV;
+  if (!pack_values(stored_input(sys), val_block_mons(sys->code), PV)) return PE_OK;
+  ValView& V = sys->val;
+  V = ValView{};
+  V.n = sys->host.n;
+  V.N = sys->host.N;
+  V.emax = sys->host.emax;
+  V.lgQ = PV.lgQ;
+  V.slices = PV.slices;
+  V.max_mon = PV.max_mon;
+  V.multi = PV.multi;
+  V.uni_mons = PV.uni_mons;
+  V.uni_lgs = PV.uni_lgs;
+  V.uni_seg = PV.uni_seg;
+  V.uni_units = PV.uni_units;
+  // wavefronts of a copy where the launch fills the chip: one per unit of the
+  // product phase and one per slice of the column phase, at least two (F
+  // beside a single slice), at most eight
+  V.max_units = PV.max_units;
+  int nw = 2;
+  while (nw < kValThreads / 64 && nw < std::max(PV.max_units, PV.slices)) nw *= 2;
+  int vw = PV.multi ? kValThreads : 64 * nw;
+  // (and a batch's workgroup of kValThreads holds as many copies as that
+  // leaves within half of a CU's LDS)
+  const size_t copy = val_doubles(sys->code, V.n, V.emax, V.max_mon, V.multi != 0) * sizeof(double);
+  while (vw < kValThreads && size_t(kValThreads / vw) * copy > device_lds_limit() / 2) vw *= 2;
+  while ((1 << V.lgvw) < vw) ++V.lgvw;
+  V.mcoef = sys->view.mcoef;
+  V.row_order = sys->view.row_order;
+  pe_status e = PE_OK;
+  if ((e = upload(sys, PV.block, V.block, hs)) != PE_OK || (e = upload(sys, PV.row_block, V.row_block, hs)) != PE_OK ||
+      (e = upload(sys, PV.unit, V.unit, hs)) != PE_OK || (e = upload(sys, PV.rec, V.rec, hs)) != PE_OK ||
+      (e = upload(sys, PV.ell, V.ell, hs)) != PE_OK || (e = upload(sys, PV.slice, V.slice, hs)) != PE_OK ||
+      (e = upload(sys, PV.perm, V.perm, hs)) != PE_OK)
+    return e;
+  PE_HIP(hipStreamSynchronize(hs));
+  sys->use_val = true;
+  sys->use_val_adj = val_doubles(sys->code, V.n, V.emax, V.max_mon, true) * sizeof(double) <= val_lds_limit(sys);
+  return PE_OK;
 }
 
 // (Re)pack the stored input for segment length `seg`, choose G and upload.
@@ -373,7 +490,7 @@ pe_status pack_and_upload(pe_system* sys, int seg, int force_G, hipStream_t hs) 
   sys->host.occ_orig.shrink_to_fit();
   sys->host.mon_orig.clear();
   sys->host.mon_orig.shrink_to_fit();
-  return PE_OK;
+  return upload_values(sys, hs);
 }
 
 // ------------------------------------------------------------------ plan cache
@@ -418,10 +535,12 @@ void cache_store(const std::string& key, int seg, int G, double us) {
 }
 
 // Groups of polynomials of the adjoint: gsize consecutive polynomials per
-// workgroup, NG groups per point, enough workgroups (about 4096) to fill the
-// device.
-void adjoint_groups(int N, int P, int& NG, int& gsize) {
-  const int target = 4096;
+// workgroup, NG groups per point, enough workgroups to fill the device: about
+// 4096, or 1024 where a workgroup's table of powers and reciprocals is worth
+// several rows.
+void adjoint_groups(const pe_system* sys, int P, int& NG, int& gsize) {
+  const int N = sys->view.N;
+  const int target = sys->use_val_adj ? 1024 : 4096;
   gsize = int(std::max<int64_t>(1, (int64_t(N) * P + target - 1) / target));
   gsize = std::min(gsize, N);
   NG = (N + gsize - 1) / gsize;
@@ -662,7 +781,7 @@ pe_status pe_eval_adjoint(const pe_system* sys, int32_t P, const double* x, cons
     return PE_OK;
   }
   int NG = 0, gsize = 0;
-  adjoint_groups(N, P, NG, gsize);
+  adjoint_groups(sys, P, NG, gsize);
   const size_t need = size_t(P) * NG * 2 * L * n * sizeof(double);
   double* part = nullptr;
   {
@@ -756,7 +875,7 @@ pe_status pe_eval_adjoint_static(const pe_system* sys, int32_t P, const double* 
   // the groups of pe_eval_adjoint when their partial rows fit, else fewer
   // and larger groups
   int NG = 0, gsize = 0;
-  adjoint_groups(N, P, NG, gsize);
+  adjoint_groups(sys, P, NG, gsize);
   const int ng_fit = int(std::min<size_t>(kStaticScratchBytes / row_bytes, size_t(N)));
   if (NG > ng_fit) {
     gsize = (N + ng_fit - 1) / ng_fit;
@@ -1031,9 +1150,12 @@ struct pe_batch {
   // whose rows are at most one chunk of at most VW lanes and that have at
   // most VW variables, VW = 32, 64, 128, 256 (batch_small_kernel, 256 / VW
   // points per pass)
-  static constexpr int kClasses = 6;
+  static constexpr int kOldClasses = 6;
+  // class 6: systems evaluated through monomial values, of any width
+  static constexpr int kClasses = 7;
   BatchClass cls[kClasses];
   int maxN = 0;
+  bool any_multi = false;  // a system has a row of two or more chunks
   std::vector<const pe_system*> systems;
   std::vector<int64_t> x_off, F_off, J_off;  // per point, doubles, [S+1]
   std::vector<BatchNewtonDesc> ndesc;        // per point offsets of the Newton workspace
@@ -1042,6 +1164,7 @@ struct pe_batch {
   std::vector<int> left_N, left_n;           // largest N and n of order[i], order[i + 1], ...
   int64_t nitems = 0;
   SysView* d_views = nullptr;
+  ValView* d_vviews = nullptr;
   int64_t* d_offs = nullptr;  // x_off | F_off | J_off | W offsets, each [S+1]
   BatchNewtonDesc* d_ndesc = nullptr;
   int* d_order = nullptr;
@@ -1057,6 +1180,21 @@ __global__ void reset_counter_kernel(int* counter, int count) {
 hipError_t dispatch_batch_class(const pe_batch* b, int c, int P, const double* x, const BatchOut& out, int mode,
                                 hipStream_t st) {
   const BatchClass& C = b->cls[c];
+  if (c == pe_batch::kOldClasses) {
+    ValBatchShape K;
+    K.lds = C.lds;
+    K.nitems = C.nitems;
+    K.items = C.d_items;
+    K.views = b->d_vviews;
+    K.x_off = b->d_offs;
+    K.counter = b->d_counter + c;
+    switch (b->level) {
+      case 1: return launch_val_batch<1>(K, P, x, out, mode, st);
+      case 2: return launch_val_batch<2>(K, P, x, out, mode, st);
+      case 4: return launch_val_batch<4>(K, P, x, out, mode, st);
+    }
+    return hipErrorInvalidValue;
+  }
   BatchShape K;
   K.seg = b->seg;
   K.G = C.G;
@@ -1088,7 +1226,7 @@ hipError_t dispatch_batch(const pe_batch* b, int P, const double* x, const Batch
 }
 
 void batch_free(pe_batch* b) {
-  for (void* p : {(void*)b->d_views, (void*)b->d_offs, (void*)b->d_ndesc, (void*)b->d_order, (void*)b->d_counter})
+  for (void* p : {(void*)b->d_views, (void*)b->d_vviews, (void*)b->d_offs, (void*)b->d_ndesc, (void*)b->d_order, (void*)b->d_counter})
     if (p) (void)hipFree(p);
   for (BatchClass& c : b->cls)
     if (c.d_items) (void)hipFree(c.d_items);
@@ -1150,7 +1288,7 @@ pe_status pe_batch_create(pe_batch** out, int32_t S, const pe_system* const* sys
   // every system's table and two slot regions fit in LDS
   constexpr int kVw[4] = {32, 64, 128, 256};
   std::vector<int> cls_of(S, 1);
-  int maxcols[pe_batch::kClasses] = {1, 1, 1, 1, 1, 1};
+  int maxcols[pe_batch::kClasses] = {1, 1, 1, 1, 1, 1, 1};
   size_t lds2 = 0;
   bool two_fit = shape_compiled(L, b->seg, 2);
   for (int s = 0; s < S; ++s) {
@@ -1159,6 +1297,7 @@ pe_status pe_batch_create(pe_batch** out, int32_t S, const pe_system* const* sys
     for (int p = 0; p < y->view.N; ++p) mc = std::max<int>(mc, y->host.chunk_ptr[p + 1] - y->host.chunk_ptr[p]);
     for (const ChunkDesc& cd : y->host.chunks) wmax = std::max<int>(wmax, cd.width);
     int c = mc >= 2 ? 0 : 1;
+    b->any_multi = b->any_multi || mc >= 2;
     if (c == 1)
       for (int v = 0; v < 4; ++v)
         if (std::max(y->view.n, wmax) <= kVw[v]) {
@@ -1182,7 +1321,7 @@ pe_status pe_batch_create(pe_batch** out, int32_t S, const pe_system* const* sys
       two_fit = two_fit && multi_chunk_fits(y->view.n, cpl_bucket(y->view.n, kSub), y->view.max_slots, 2);
     }
   }
-  for (int c = 0; c < pe_batch::kClasses; ++c) {
+  for (int c = 0; c < pe_batch::kOldClasses; ++c) {
     b->cls[c].cpl = c >= 2 ? 1 : cpl_bucket(maxcols[c], kSub);
     b->cls[c].vw = c >= 2 ? kVw[c - 2] : 0;
   }
@@ -1193,7 +1332,7 @@ pe_status pe_batch_create(pe_batch** out, int32_t S, const pe_system* const* sys
     b->cls[0].lds = lds2;
   }
   // a small class whose copies do not fit in LDS goes to class 1
-  for (int c = 2; c < pe_batch::kClasses; ++c)
+  for (int c = 2; c < pe_batch::kOldClasses; ++c)
     if (b->cls[c].lds > device_lds_limit()) {
       for (int s = 0; s < S; ++s)
         if (cls_of[s] == c) {
@@ -1203,6 +1342,19 @@ pe_status pe_batch_create(pe_batch** out, int32_t S, const pe_system* const* sys
         }
       b->cls[c].lds = 0;
     }
+  // systems evaluated through monomial values go to their own class (the same
+  // rule as pe_eval's, so that rows have the same bits)
+  {
+    BatchClass& c = b->cls[pe_batch::kOldClasses];
+    for (int s = 0; s < S; ++s) {
+      const pe_system* y = systems[s];
+      if (!y->use_val) continue;
+      cls_of[s] = pe_batch::kOldClasses;
+      const size_t copies = y->val.multi ? 1 : size_t(kValThreads >> y->val.lgvw);
+      c.lds = std::max(c.lds, copies * sizeof(double) * val_doubles(y->code, y->val.n, y->val.emax, y->val.max_mon,
+                                                                    y->val.multi != 0));
+    }
+  }
   // packed layout per point
   b->x_off.assign(S + 1, 0);
   b->F_off.assign(S + 1, 0);
@@ -1239,7 +1391,11 @@ pe_status pe_batch_create(pe_batch** out, int32_t S, const pe_system* const* sys
   b->nitems = 0;
   for (const BatchClass& c : b->cls) b->nitems += c.nitems;
   std::vector<SysView> views(S);
-  for (int s = 0; s < S; ++s) views[s] = systems[s]->view;
+  std::vector<ValView> vviews(S);
+  for (int s = 0; s < S; ++s) {
+    views[s] = systems[s]->view;
+    vviews[s] = systems[s]->val;
+  }
   std::vector<int64_t> offs;
   offs.insert(offs.end(), b->x_off.begin(), b->x_off.end());
   offs.insert(offs.end(), b->F_off.begin(), b->F_off.end());
@@ -1261,6 +1417,7 @@ pe_status pe_batch_create(pe_batch** out, int32_t S, const pe_system* const* sys
   pe_status e = PE_OK;
   for (int c = 0; c < pe_batch::kClasses && e == PE_OK; ++c) e = upload_raw(it[c], &b->cls[c].d_items, hs);
   if (e != PE_OK || (e = upload_raw(views, &b->d_views, hs)) != PE_OK ||
+      (e = upload_raw(vviews, &b->d_vviews, hs)) != PE_OK ||
       (e = upload_raw(offs, &b->d_offs, hs)) != PE_OK || (e = upload_raw(b->ndesc, &b->d_ndesc, hs)) != PE_OK ||
       (e = upload_raw(order, &b->d_order, hs)) != PE_OK) {
     batch_free(b);
@@ -1302,7 +1459,7 @@ pe_status pe_batch_info(const pe_batch* b, int64_t info[4]) {
   info[0] = b->S;
   info[1] = b->level;
   info[2] = b->seg;
-  info[3] = b->cls[0].nitems > 0 ? b->cls[0].G : b->cls[1].G;
+  info[3] = b->any_multi ? b->cls[0].G : b->cls[1].G;
   return PE_OK;
 }
 
