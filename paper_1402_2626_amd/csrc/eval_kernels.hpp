@@ -524,14 +524,92 @@ __device__ __forceinline__ void dd_sum_slots(double& hi, double& lo, const doubl
   }
 }
 
+// Sum of a value over groups of SPAN neighbouring lanes (SPAN a power of two
+// up to 64) by an XOR butterfly; every lane of a group gets the same sum.
+// Double-double: TwoSum on the high parts, low parts and errors in a plain
+// sum, renormalized once (the compensated summation of the owners).
+template <int L, int SPAN>
+__device__ __forceinline__ C<L> lane_group_sum(const C<L>& v) {
+  C<L> f = v;
+  if constexpr (limbs_of(L) == 2) {
+    auto sum = [](R<2>& x) {
+      double h = x.x[0], l = x.x[1];
+      for (int m = 1; m < SPAN; m <<= 1) {
+        const double oh = __shfl_xor(h, m), ol = __shfl_xor(l, m);
+        double s, e;
+        two_sum(h, oh, s, e);
+        h = s;
+        l = (l + ol) + e;
+      }
+      two_sum(h, l, x.x[0], x.x[1]);
+    };
+    sum(f.re);
+    if constexpr (!is_real(L)) sum(f.im);
+  } else {
+    for (int m = 1; m < SPAN; m <<= 1) f = c_add(f, shfl_xor_c(f, m));
+  }
+  return f;
+}
+
+// Long columns.  A column of many slots is a serial chain in its owner's lane
+// (in the H-equation's system every monomial of row i contains H_i: 256 slots
+// per chunk), so a wavefront with one or two of them adds each with all its
+// lanes and leaves the sum in the column's first slot; returns the columns
+// (bits) that the calling lane then finds as one slot.  More than two take
+// longer in turn than side by side in their lanes.  A copy of a workgroup that
+// shares a wavefront has at most 32 slots per column, so the bits are the same
+// wherever the row is evaluated.  H-equation, n = 2048 in double double: 1263 ->
+// 475 us; n = 1016 in real quad double: 634 -> 72 us.
+constexpr int kLongColumn = 48;
+static_assert(kLongColumn > 32, "columns of copies narrower than a wavefront");
+
+template <int L, int CPL>
+__device__ __forceinline__ int long_columns(const int (&cb)[CPL], const int (&ce)[CPL], double* contrib, int ms) {
+  int longest = 0;
+#pragma unroll
+  for (int cc = 0; cc < CPL; ++cc) longest = max(longest, ce[cc] - cb[cc]);
+  if (__ballot(longest >= kLongColumn) == 0) return 0;
+  const int lane = int(threadIdx.x) & 63;
+  int done = 0;
+#pragma unroll 1
+  for (int c = 0; c < CPL; ++c) {
+    int b = cb[0], e = ce[0];
+#pragma unroll
+    for (int cc = 1; cc < CPL; ++cc)
+      if (c == cc) {
+        b = cb[cc];
+        e = ce[cc];
+      }
+    uint64_t m = __ballot(e - b >= kLongColumn);
+    if (__popcll(m) > 2) continue;
+    for (; m != 0; m &= m - 1) {
+      const int o = __ffsll((unsigned long long)m) - 1;
+      const int b1 = __builtin_amdgcn_readlane(b, o), e1 = __builtin_amdgcn_readlane(e, o);
+      C<L> a = c_zero<L>();
+#pragma unroll 1
+      for (int sl = b1 + lane; sl < e1; sl += 64) a = c_add(a, lds_ld<L>(contrib, ms, sl));
+      a = lane_group_sum<L, 64>(a);
+      if (lane == o) {
+        lds_st(contrib, ms, b1, a);
+        done |= 1 << c;
+      }
+    }
+  }
+  return done;
+}
+
 // Owner phase: add the chunk's slots into the register accumulators in slot
 // order.  Double-double uses the compensated sum above; the other levels add
 // four slots per step as acc + ((a + b) + (c + d)) (the tail one by one), so
 // that the loads of a step are in flight together and the additions form
 // short chains.  The order depends only on the slot layout.
 template <int L, int CPL>
-__device__ __forceinline__ void chunk_owners(const int (&cb)[CPL], const int (&ce)[CPL], const double* contrib,
-                                             int ms, C<L> (&acc)[CPL]) {
+__device__ __forceinline__ void chunk_owners(const int (&cb)[CPL], const int (&cend)[CPL], double* contrib, int ms,
+                                             C<L> (&acc)[CPL]) {
+  const int done = long_columns<L, CPL>(cb, cend, contrib, ms);
+  int ce[CPL];
+#pragma unroll
+  for (int cc = 0; cc < CPL; ++cc) ce[cc] = done & (1 << cc) ? cb[cc] + 1 : cend[cc];
   if constexpr (limbs_of(L) == 2) {
 #pragma unroll
     for (int cc = 0; cc < CPL; ++cc) {
@@ -564,33 +642,6 @@ __device__ __forceinline__ void chunk_owners(const int (&cb)[CPL], const int (&c
 // F: each wavefront adds its lanes' running sums pairwise and stores the
 // result as its F partial (fpart[w], planar with plane stride kMaxWaves)
 constexpr int kMaxWaves = 16;
-
-// Sum of a value over groups of SPAN neighbouring lanes (SPAN a power of two
-// up to 64) by an XOR butterfly; every lane of a group gets the same sum.
-// Double-double: TwoSum on the high parts, low parts and errors in a plain
-// sum, renormalized once (the compensated summation of the owners).
-template <int L, int SPAN>
-__device__ __forceinline__ C<L> lane_group_sum(const C<L>& v) {
-  C<L> f = v;
-  if constexpr (limbs_of(L) == 2) {
-    auto sum = [](R<2>& x) {
-      double h = x.x[0], l = x.x[1];
-      for (int m = 1; m < SPAN; m <<= 1) {
-        const double oh = __shfl_xor(h, m), ol = __shfl_xor(l, m);
-        double s, e;
-        two_sum(h, oh, s, e);
-        h = s;
-        l = (l + ol) + e;
-      }
-      two_sum(h, l, x.x[0], x.x[1]);
-    };
-    sum(f.re);
-    if constexpr (!is_real(L)) sum(f.im);
-  } else {
-    for (int m = 1; m < SPAN; m <<= 1) f = c_add(f, shfl_xor_c(f, m));
-  }
-  return f;
-}
 
 template <int L>
 __device__ __forceinline__ void store_wave_f(const C<L>& facc, double* fpart) {
