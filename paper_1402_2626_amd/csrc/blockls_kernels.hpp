@@ -1328,15 +1328,19 @@ __global__ __launch_bounds__(256, limbs_of(L) == 4 ? 1 : 2) void bl_update_kerne
 constexpr int kBlBsThreads = 512;
 
 // Diagonal block `stage` (of kBlBs rows, from the bottom) of R x = y, in
-// sub-blocks of 32 rows.  Wavefront 0 solves a sub-block, its lanes the rows
-// (complex: real parts in the lower, imaginary parts in the upper half), x_j
-// broadcast through scalar registers, the triangle staged in LDS; then all
-// threads subtract its columns from the block's rows above, the next
-// sub-block's triangle being loaded meanwhile.  grid (slots), 512 threads
+// sub-blocks of 32 rows, the columns of their triangles over their pivots so
+// that a step of the chain is one product and one sum.  Wavefront 0 solves a
+// sub-block, its lanes the rows (complex: real parts in the lower, imaginary
+// parts in the upper half), x_j broadcast through scalar registers, the
+// triangle staged in LDS.  Meanwhile the other wavefronts subtract the columns
+// of the sub-block before from the rows above this one; the rows of the next
+// sub-block take this one's columns first, 16 threads a row.  256 rows:
+// 88 -> 70 us (complex double double), 228 -> 152 us (real quad double).
+// grid (slots), 512 threads
 template <int L>
 __global__ __launch_bounds__(kBlBsThreads) void bl_bs_diag_kernel(BlView V, int stage) {
   constexpr int NL = limbs_of(L), W = width_of(L), SB = 32, PT = SB * SB / kBlBsThreads;
-  constexpr int RP = W <= 4 ? SB / 2 : 4;  // entries of R held per thread (registers)
+  static_assert(kBlBsThreads == 16 * SB && kBlBsThreads - 64 >= 2 * (kBlBs - 2 * SB), "threads of the updates");
   using RL = R<NL>;
   constexpr int TP = is_real(L) ? NL : 4 * NL;  // planes: re, im, re, -im
   __shared__ double tri[SB * TP * SB];          // [column][plane][row]
@@ -1358,13 +1362,15 @@ __global__ __launch_bounds__(kBlBsThreads) void bl_bs_diag_kernel(BlView V, int 
     store_planar(y, kBlBs, tid, v);
     r_store_aos(dinv + tid * NL, r_load_aos<NL>(inv + size_t(s + tid) * NL));
   }
-  C<L> next[PT];  // the thread's entries of the next triangle
+  C<L> next[PT];  // the thread's entries of the next triangle and 1 / their column's pivot
+  RL scale[PT];
   auto fetch = [&](int se) {
     const int ss = max(s, se - SB), sb = se - ss;
 #pragma unroll
     for (int q = 0; q < PT; ++q) {
       const int idx = tid + q * kBlBsThreads, jj = idx / SB, ii = idx % SB;
       next[q] = (jj < sb && ii < jj) ? load_planar<L>(Rm + int64_t(ss + jj) * p.n, rplane, ss + ii) : c_zero<L>();
+      scale[q] = r_load_aos<NL>(inv + size_t(ss + min(jj, sb - 1)) * NL);
     }
   };
   fetch(e);
@@ -1374,19 +1380,21 @@ __global__ __launch_bounds__(kBlBsThreads) void bl_bs_diag_kernel(BlView V, int 
 #pragma unroll
     for (int q = 0; q < PT; ++q) {
       const int idx = tid + q * kBlBsThreads;
+      next[q] = c_mul_r(next[q], scale[q]);
       store_planar(tri + (idx / SB) * TP * SB, SB, idx % SB, next[q]);
       if constexpr (!is_real(L)) store_planar(tri + ((idx / SB) * TP + 2 * NL) * SB, SB, idx % SB, c_conj(next[q]));
     }
     __syncthreads();
     if (ss > s) fetch(ss);
-    // rows above inside the block: two threads per row, even and odd columns,
-    // whose entries of R arrive while wavefront 0 solves
-    const int rows = ss - s, i = tid >> 1, h = tid & 1;
-    const double* Ri = Rm + int64_t(ss + h) * p.n + s + i;
-    C<L> rp[RP];
+    // the rows of the next sub-block: row sn + tid / 16, columns tid % 16 and
+    // 16 further on, whose entries of R arrive while wavefront 0 solves
+    const int sn = max(s, ss - SB), un = tid >> 4, uc = tid & 15;
+    C<L> up[2];
 #pragma unroll
-    for (int q = 0; q < RP; ++q)
-      rp[q] = (i < rows && h + 2 * q < sb) ? load_planar<L>(Ri + int64_t(2 * q) * p.n, rplane, 0) : c_zero<L>();
+    for (int q = 0; q < 2; ++q)
+      up[q] = (sn + un < ss && uc + 16 * q < sb)
+                  ? load_planar<L>(Rm + int64_t(ss + uc + 16 * q) * p.n, rplane, sn + un)
+                  : c_zero<L>();
     if (tid < 64) {
       const int ii = is_real(L) ? (tid & (SB - 1)) : tid % SB, comp = is_real(L) ? 0 : tid / SB;
       RL v = r_zero<NL>(), dv = v;
@@ -1410,12 +1418,11 @@ __global__ __launch_bounds__(kBlBsThreads) void bl_bs_diag_kernel(BlView V, int 
         f = fn;
         g = gn;
         load_r(max(jj - 1, 0), fn, gn);
-        const RL mine = r_mul(v, dv);
         C<L> xj;
 #pragma unroll
         for (int l = 0; l < NL; ++l) {
-          xj.re.x[l] = bl_readlane(mine.x[l], jj);
-          if constexpr (!is_real(L)) xj.im.x[l] = bl_readlane(mine.x[l], SB + jj);
+          xj.re.x[l] = bl_readlane(v.x[l], jj);
+          if constexpr (!is_real(L)) xj.im.x[l] = bl_readlane(v.x[l], SB + jj);
         }
         RL t;
         if constexpr (is_real(L))
@@ -1426,29 +1433,48 @@ __global__ __launch_bounds__(kBlBsThreads) void bl_bs_diag_kernel(BlView V, int 
           t = dd_dot2(xj.re, f, xj.im, g, 1.0);
         else
           t = qd_dot2(xj.re, f, xj.im, g);
-        if (ii == jj) res = mine;
+        if (ii == jj) res = v;
         v = r_sub(v, t);  // the entries of rows from jj on are zero
       }
+      res = r_mul(res, dv);
       if (ii < sb && (!is_real(L) || tid < SB)) {
 #pragma unroll
         for (int l = 0; l < NL; ++l) y[(comp * NL + l) * kBlBs + ss - s + ii] = res.x[l];
       }
-    }
-    __syncthreads();
-    C<L> acc = c_zero<L>();
-    if (i < rows) {
+    } else if (se < e) {
+      // the columns of the sub-block before (full: [se, se + 32)) from the
+      // rows above this one: two threads per row, even and odd columns
+      const int rows = ss - s, i = (tid - 64) >> 1, h = tid & 1;
+      if (i < rows) {
+        const int64_t at = int64_t(se + h) * p.n + s + i;
+        constexpr int UN = W <= 4 ? 8 : 2;  // loads in flight: they would outlast the solve one by one
+        C<L> acc = c_zero<L>();
+#pragma unroll 1
+        for (int q0 = 0; q0 < SB / 2; q0 += UN) {
+          C<L> r[UN];
 #pragma unroll
-      for (int q = 0; q < RP; ++q)
-        if (h + 2 * q < sb) acc = c_add(acc, c_mul(rp[q], load_planar<L>(y, kBlBs, ss - s + h + 2 * q)));
-#pragma unroll 4
-      for (int q = RP; h + 2 * q < sb; ++q)
-        acc = c_add(acc, c_mul(load_planar<L>(Ri + int64_t(2 * q) * p.n, rplane, 0),
-                               load_planar<L>(y, kBlBs, ss - s + h + 2 * q)));
+          for (int q = 0; q < UN; ++q) r[q] = load_planar<L>(Rm + at + int64_t(2 * (q0 + q)) * p.n, rplane, 0);
+#pragma unroll
+          for (int q = 0; q < UN; ++q)
+            acc = c_add(acc, c_mul(r[q], load_planar<L>(y, kBlBs, se - s + h + 2 * (q0 + q))));
+        }
+        acc = c_add(acc, shfl_xor_c(acc, 1));
+        if (h == 0) store_planar(y, kBlBs, i, c_sub(load_planar<L>(y, kBlBs, i), acc));
+      }
     }
-    acc = c_add(acc, shfl_xor_c(acc, 1));
-    if (i < rows && h == 0) store_planar(y, kBlBs, i, c_sub(load_planar<L>(y, kBlBs, i), acc));
     __syncthreads();
+    if (ss > s) {
+      C<L> acc = c_zero<L>();
+#pragma unroll
+      for (int q = 0; q < 2; ++q)
+        if (uc + 16 * q < sb) acc = c_add(acc, c_mul(up[q], load_planar<L>(y, kBlBs, ss - s + uc + 16 * q)));
+#pragma unroll 1
+      for (int m = 1; m < 16; m <<= 1) acc = c_add(acc, shfl_xor_c(acc, m));
+      if (uc == 0 && sn + un < ss)
+        store_planar(y, kBlBs, sn - s + un, c_sub(load_planar<L>(y, kBlBs, sn - s + un), acc));
+    }
   }
+  __syncthreads();
   if (tid < e - s) store_planar(yw, p.n, s + tid, load_planar<L>(y, kBlBs, tid));
 }
 
