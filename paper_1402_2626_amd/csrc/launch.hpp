@@ -429,6 +429,10 @@ hipError_t launch_blockls(const BlView& V, int slots, int Nm, int nm, hipStream_
   hipLaunchKernelGGL(bl_copy_in_kernel<L>, dim3(unsigned(((nm + 1 + 63) / 64) * NC), unsigned(K::W), S), dim3(256), 0,
                      st, V);
   if ((e = hipGetLastError()) != hipSuccess) return e;
+  // the update's workgroups hold 256 registers (quad double 512): two (one)
+  // fit on a CU, and one round of them leaves no tail (double double, n =
+  // 2048: 60 us a panel against 68 with three per CU and 74 with one)
+  constexpr int kUpdate = limbs_of(L) == 4 ? 256 : 512;
   // enough workgroups for two on every CU, within the split limits
   auto splits = [&](int tiles, int most) { return std::max(1, std::min({most, NC, (512 + tiles * slots - 1) / (tiles * slots)})); };
   for (int panel = 0, k0 = 0; k0 < nm; ++panel, k0 += K::B) {
@@ -447,7 +451,7 @@ hipError_t launch_blockls(const BlView& V, int slots, int Nm, int nm, hipStream_
                        cur, ds);
     if (k0 + K::B < nm) {
       const int tiles = (real_cols + 15) / 16 - 4;
-      const int groups = std::max(1, std::min(tiles, (768 + NC * slots - 1) / (NC * slots)));
+      const int groups = std::max(1, std::min(tiles, (kUpdate + NC * slots - 1) / (NC * slots)));
       const int per = (tiles + groups - 1) / groups;
       hipLaunchKernelGGL(bl_update_kernel<L>, dim3(unsigned(NC), unsigned((tiles + per - 1) / per), S), dim3(256), 0, st,
                          V, panel, cur, per);
