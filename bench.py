@@ -50,7 +50,7 @@ BATCH_COUNT, BATCH_POINTS = 4096, 8
 # and launchers (the least-squares and Gauss-Newton kernels are not among
 # them).
 COUNTERS_DIR = os.path.join(ROOT, "profiles")
-KERNEL_SOURCES = ["eval_kernels.hpp", "mdarith.hpp", "layout.hpp", "polyeval.hip", "packer.cpp", "packer.hpp",
+KERNEL_SOURCES = ["eval_kernels.hpp", "value_kernels.hpp", "mdarith.hpp", "layout.hpp", "polyeval.hip", "packer.cpp", "packer.hpp",
                   "launch.hpp", "instances.hip"]
 
 
