@@ -91,6 +91,7 @@ hipError_t launch_val_adjoint(const ValView& V, int P, const double* x, const do
 // a batch's items whose systems evaluate through monomial values
 struct ValBatchShape {
   size_t lds = 0;
+  bool small = false;  // a system's table holds x alone
   int64_t nitems = 0;
   const uint64_t* items = nullptr;
   const ValView* views = nullptr;
@@ -337,10 +338,10 @@ hipError_t launch_batch(const BatchShape& K, int P, const double* x, const Batch
 // idle: a copy then has a wavefront for F besides those of the slices (DD, n =
 // 128, 64 x 12: 8.9 us against 9.4 at P = 1; at P = 64 the wider copies would
 // take 67 us against 48).  No sum depends on the number of wavefronts.
-template <int L, int MODE>
+template <int L, int MODE, bool SMALL>
 hipError_t launch_val_rows_t(ValView V, int P, const double* x, const OutView& O, hipStream_t st) {
-  auto kern = val_rows_kernel<L, MODE>;
-  const size_t copy = val_copy_doubles<L>(V.n, V.emax, V.max_mon, V.multi != 0);
+  auto kern = val_rows_kernel<L, MODE, SMALL>;
+  const size_t copy = val_copy_doubles<L>(V.n, V.tab + V.inv, V.max_mon, V.multi != 0);
   const int64_t rows = int64_t(P) * V.N;
   if (rows <= 1024)
     while ((1 << V.lgvw) < kValThreads && (1 << V.lgvw) < 64 * std::max(V.max_units, V.slices + 1)) ++V.lgvw;
@@ -361,15 +362,18 @@ hipError_t launch_val_rows_t(ValView V, int P, const double* x, const OutView& O
 
 template <int L>
 hipError_t launch_val_rows(const ValView& V, int P, const double* x, const OutView& O, int mode, hipStream_t st) {
-  return mode == MODE_EVAL ? launch_val_rows_t<L, MODE_EVAL>(V, P, x, O, st)
-                           : launch_val_rows_t<L, MODE_FONLY>(V, P, x, O, st);
+  if (V.inv)
+    return mode == MODE_EVAL ? launch_val_rows_t<L, MODE_EVAL, false>(V, P, x, O, st)
+                             : launch_val_rows_t<L, MODE_FONLY, false>(V, P, x, O, st);
+  return mode == MODE_EVAL ? launch_val_rows_t<L, MODE_EVAL, true>(V, P, x, O, st)
+                           : launch_val_rows_t<L, MODE_FONLY, true>(V, P, x, O, st);
 }
 
 template <int L>
 hipError_t launch_val_adjoint(const ValView& V, int P, const double* x, const double* v, int NG, int gsize, double* part,
                               double* g, hipStream_t st) {
-  auto kern = val_adjoint_kernel<L>;
-  const size_t lds = val_copy_doubles<L>(V.n, V.emax, V.max_mon, true) * sizeof(double);
+  auto kern = V.inv ? val_adjoint_kernel<L, false> : val_adjoint_kernel<L, true>;
+  const size_t lds = val_copy_doubles<L>(V.n, V.tab + V.inv, V.max_mon, true) * sizeof(double);
   hipError_t e = allow_lds(kern, lds);
   if (e != hipSuccess) return e;
   hipLaunchKernelGGL(kern, dim3(unsigned(int64_t(P) * NG)), dim3(unsigned(std::max(1 << V.lgvw, 256))), lds, st, V, x,
@@ -385,9 +389,9 @@ hipError_t launch_val_adjoint(const ValView& V, int P, const double* x, const do
   return hipGetLastError();
 }
 
-template <int L, int MODE>
+template <int L, int MODE, bool SMALL>
 hipError_t launch_val_batch_t(const ValBatchShape& K, int P, const double* x, const BatchOut& out, hipStream_t st) {
-  auto kern = val_batch_kernel<L, MODE>;
+  auto kern = val_batch_kernel<L, MODE, SMALL>;
   hipError_t e = allow_lds(kern, K.lds);
   if (e != hipSuccess) return e;
   int64_t grid = 0;
@@ -400,8 +404,11 @@ hipError_t launch_val_batch_t(const ValBatchShape& K, int P, const double* x, co
 template <int L>
 hipError_t launch_val_batch(const ValBatchShape& K, int P, const double* x, const BatchOut& out, int mode,
                             hipStream_t st) {
-  return mode == MODE_EVAL ? launch_val_batch_t<L, MODE_EVAL>(K, P, x, out, st)
-                           : launch_val_batch_t<L, MODE_FONLY>(K, P, x, out, st);
+  if (!K.small)
+    return mode == MODE_EVAL ? launch_val_batch_t<L, MODE_EVAL, false>(K, P, x, out, st)
+                             : launch_val_batch_t<L, MODE_FONLY, false>(K, P, x, out, st);
+  return mode == MODE_EVAL ? launch_val_batch_t<L, MODE_EVAL, true>(K, P, x, out, st)
+                           : launch_val_batch_t<L, MODE_FONLY, true>(K, P, x, out, st);
 }
 
 template <int L>

@@ -327,15 +327,15 @@ SysInput stored_input(const pe_system* sys) {
   return in;
 }
 
-size_t val_doubles(int code, int n, int emax, int max_mon, bool sums) {
+size_t val_doubles(int code, int n, int blocks, int max_mon, bool sums) {
   switch (code) {
-    case 1: return val_copy_doubles<1>(n, emax, max_mon, sums);
-    case 2: return val_copy_doubles<2>(n, emax, max_mon, sums);
-    case 4: return val_copy_doubles<4>(n, emax, max_mon, sums);
-    case PE_REAL | 1: return val_copy_doubles<PE_REAL | 1>(n, emax, max_mon, sums);
-    case PE_REAL | 2: return val_copy_doubles<PE_REAL | 2>(n, emax, max_mon, sums);
+    case 1: return val_copy_doubles<1>(n, blocks, max_mon, sums);
+    case 2: return val_copy_doubles<2>(n, blocks, max_mon, sums);
+    case 4: return val_copy_doubles<4>(n, blocks, max_mon, sums);
+    case PE_REAL | 1: return val_copy_doubles<PE_REAL | 1>(n, blocks, max_mon, sums);
+    case PE_REAL | 2: return val_copy_doubles<PE_REAL | 2>(n, blocks, max_mon, sums);
   }
-  return val_copy_doubles<PE_REAL | 4>(n, emax, max_mon, sums);
+  return val_copy_doubles<PE_REAL | 4>(n, blocks, max_mon, sums);
 }
 
 // monomials of a block of the value layout: 32 KB of values
@@ -361,7 +361,18 @@ size_t val_lds_limit(const pe_system* sys) {
 // ahead when the launch is short (D, n = N = 32, P = 1: 4.9 us against 6.0 in
 // a graph; real D, n = 256, 128 x 16, P = 8: 11.7 against 13.5), while chunks
 // in sequence are not (D, n = 128, 256 x 16, P = 8: 28 us against 18).
-bool val_suits(const pe_system* sys) {
+// Where the table of powers does not fit, x alone does more often: higher
+// powers are then formed factor by factor and reciprocals column by column,
+// and if the sums of several blocks are in the way a block takes a whole row
+// (QD, n = 1024, 1024 x 32: 4.75 -> 2.2 ms; DD, n = 1024, 200 x 24, 8 points:
+// 319 -> 132 us; both against the reverse sweep).  The adjoint, which keeps its
+// column sums in LDS besides, may take all of it (64 points of 512 x 1024 in DD:
+// 9.2 -> 6.4 ms).
+struct ValPlan {
+  int tab = 0, inv = 0, block = 0;
+};
+
+bool val_suits(const pe_system* sys, ValPlan& plan) {
   const Packed& H = sys->host;
   if (H.N == 0 || H.M == 0 || H.n > kTileCols) return false;
   if (H.nnz < 4 * H.M || H.nnz < 2 * int64_t(H.N) * H.n) return false;
@@ -372,22 +383,31 @@ bool val_suits(const pe_system* sys) {
     chunks = std::max<int>(chunks, H.chunk_ptr[p + 1] - H.chunk_ptr[p]);
   }
   if (width_of(sys->code) <= 2 && chunks < 2) return false;
-  const int mons = int(std::min<int64_t>(most, val_block_mons(sys->code)));
   if (H.emax > 64) return false;
-  return val_doubles(sys->code, H.n, H.emax, mons, most > mons) * sizeof(double) <= val_lds_limit(sys);
+  const int std_block = val_block_mons(sys->code), row = int(std::min<int64_t>(most, 65534));
+  for (const ValPlan p : {ValPlan{H.emax, 1, std_block}, ValPlan{1, 0, std_block}, ValPlan{1, 0, row}}) {
+    const int mons = int(std::min<int64_t>(most, p.block));
+    if (val_doubles(sys->code, H.n, p.tab + p.inv, mons, most > mons) * sizeof(double) > val_lds_limit(sys)) continue;
+    plan = p;
+    return true;
+  }
+  return false;
 }
 
 // Pack and upload the value layout; on success sys->val is complete.
 pe_status upload_values(pe_system* sys, hipStream_t hs) {
   sys->use_val = sys->use_val_adj = false;
-  if (!val_suits(sys)) return PE_OK;
+  ValPlan plan;
+  if (!val_suits(sys, plan)) return PE_OK;
   PackedValues PV;
-  if (!pack_values(stored_input(sys), val_block_mons(sys->code), PV)) return PE_OK;
+  if (!pack_values(stored_input(sys), plan.block, PV)) return PE_OK;
   ValView& V = sys->val;
   V = ValView{};
   V.n = sys->host.n;
   V.N = sys->host.N;
   V.emax = sys->host.emax;
+  V.tab = plan.tab;
+  V.inv = plan.inv;
   V.lgQ = PV.lgQ;
   V.slices = PV.slices;
   V.max_mon = PV.max_mon;
@@ -405,7 +425,7 @@ pe_status upload_values(pe_system* sys, hipStream_t hs) {
   int vw = PV.multi ? kValThreads : 64 * nw;
   // (and a batch's workgroup of kValThreads holds as many copies as that
   // leaves within half of a CU's LDS)
-  const size_t copy = val_doubles(sys->code, V.n, V.emax, V.max_mon, V.multi != 0) * sizeof(double);
+  const size_t copy = val_doubles(sys->code, V.n, V.tab + V.inv, V.max_mon, V.multi != 0) * sizeof(double);
   while (vw < kValThreads && size_t(kValThreads / vw) * copy > device_lds_limit() / 2) vw *= 2;
   while ((1 << V.lgvw) < vw) ++V.lgvw;
   V.mcoef = sys->view.mcoef;
@@ -418,7 +438,7 @@ pe_status upload_values(pe_system* sys, hipStream_t hs) {
     return e;
   PE_HIP(hipStreamSynchronize(hs));
   sys->use_val = true;
-  sys->use_val_adj = val_doubles(sys->code, V.n, V.emax, V.max_mon, true) * sizeof(double) <= val_lds_limit(sys);
+  sys->use_val_adj = val_doubles(sys->code, V.n, V.tab + V.inv, V.max_mon, true) * sizeof(double) <= device_lds_limit();
   return PE_OK;
 }
 
@@ -1156,6 +1176,7 @@ struct pe_batch {
   BatchClass cls[kClasses];
   int maxN = 0;
   bool any_multi = false;  // a system has a row of two or more chunks
+  bool any_small = false;  // a system evaluated by values has a table of x alone
   std::vector<const pe_system*> systems;
   std::vector<int64_t> x_off, F_off, J_off;  // per point, doubles, [S+1]
   std::vector<BatchNewtonDesc> ndesc;        // per point offsets of the Newton workspace
@@ -1186,6 +1207,7 @@ hipError_t dispatch_batch_class(const pe_batch* b, int c, int P, const double* x
     K.nitems = C.nitems;
     K.items = C.d_items;
     K.views = b->d_vviews;
+    K.small = b->any_small;
     K.x_off = b->d_offs;
     K.counter = b->d_counter + c;
     switch (b->level) {
@@ -1350,8 +1372,9 @@ pe_status pe_batch_create(pe_batch** out, int32_t S, const pe_system* const* sys
       const pe_system* y = systems[s];
       if (!y->use_val) continue;
       cls_of[s] = pe_batch::kOldClasses;
+      b->any_small = b->any_small || !y->val.inv;
       const size_t copies = y->val.multi ? 1 : size_t(kValThreads >> y->val.lgvw);
-      c.lds = std::max(c.lds, copies * sizeof(double) * val_doubles(y->code, y->val.n, y->val.emax, y->val.max_mon,
+      c.lds = std::max(c.lds, copies * sizeof(double) * val_doubles(y->code, y->val.n, y->val.tab + y->val.inv, y->val.max_mon,
                                                                     y->val.multi != 0));
     }
   }

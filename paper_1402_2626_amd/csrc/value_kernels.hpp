@@ -54,6 +54,8 @@ namespace pe {
 
 struct ValView {
   int n, N, emax;
+  int tab;  // powers in the table: emax, or 1 (higher ones formed per factor)
+  int inv;  // reciprocals behind them, or formed per column
   int lgQ, slices, max_mon;
   int max_units;
   int lgvw;   // log2 of the threads of a copy
@@ -101,13 +103,13 @@ __device__ __forceinline__ C<L> val_ld_coef(const double* p) {
   return r;
 }
 
-// doubles of a copy's LDS: [emax + 1 blocks of n + 1 numbers][max_mon + 1
+// doubles of a copy's LDS: [`blocks` (powers, reciprocals) of n + 1 numbers][max_mon + 1
 // values][n column sums when rows have several blocks or the sums run over
 // rows][zero counts, bytes][2 flags]
 template <int L>
-__host__ __device__ inline size_t val_copy_doubles(int n, int emax, int max_mon, bool sums) {
+__host__ __device__ inline size_t val_copy_doubles(int n, int blocks, int max_mon, bool sums) {
   const size_t d =
-      size_t(width_of(L)) * (size_t(emax + 1) * (n + 1) + max_mon + 1 + (sums ? n : 0)) + size_t(max_mon + 8) / 8 + 1;
+      size_t(width_of(L)) * (size_t(blocks) * (n + 1) + max_mon + 1 + (sums ? n : 0)) + size_t(max_mon + 8) / 8 + 1;
   return (d + 1) & ~size_t(1);  // 16-byte words
 }
 
@@ -153,7 +155,7 @@ __device__ __forceinline__ void val_put(double* base, int i, const C<L>& v) {
 
 template <int L>
 struct ValLds {
-  double* tab;    // x^e at (e - 1) cols + v; 1 / x (1 for x = 0) at emax cols + v
+  double* tab;    // x^e at (e - 1) cols + v, e <= S.tab; 1 / x (1 for x = 0) at S.tab cols + v
   double* val;    // [max_mon + 1]
   double* sum;    // [n]
   uint8_t* zeros;  // [max_mon]
@@ -166,7 +168,7 @@ __device__ __forceinline__ ValLds<L> val_lds(const ValView& S, double* base, boo
   ValLds<L> M;
   M.cols = S.n + 1;
   M.tab = base;
-  M.val = M.tab + size_t(width_of(L)) * (S.emax + 1) * M.cols;
+  M.val = M.tab + size_t(width_of(L)) * (S.tab + S.inv) * M.cols;
   M.sum = M.val + size_t(width_of(L)) * (S.max_mon + 1);
   double* z = M.sum + (sums ? size_t(width_of(L)) * S.n : 0);
   M.zeros = reinterpret_cast<uint8_t*>(z);
@@ -174,8 +176,12 @@ __device__ __forceinline__ ValLds<L> val_lds(const ValView& S, double* base, boo
   return M;
 }
 
-template <int L>
-__device__ __forceinline__ C<L> val_power(const ValLds<L>& M, int v, int e) {
+// SMALL: the kernels that also take systems whose table holds x alone (apart,
+// since the code costs the others 3 to 9 %)
+template <int L, bool SMALL>
+__device__ __forceinline__ C<L> val_power(const ValView& S, const ValLds<L>& M, int v, int e) {
+  if constexpr (SMALL)
+    if (e > S.tab) return c_pow(val_get<L>(M.tab, v), e);
   return val_get<L>(M.tab, (e - 1) * M.cols + v);
 }
 
@@ -256,7 +262,7 @@ __device__ __forceinline__ void val_table(const ValView& S, const ValLds<L>& M, 
   for (int v = lv; v <= S.n; v += VW) {
     const C<L> x = v == lv ? x0 : (v < S.n ? load_planar<L>(xpt, S.n, v) : c_one<L>());
     C<L> p = x;
-    for (int e = 1; e <= S.emax; ++e) {
+    for (int e = 1; e <= S.tab; ++e) {
       if (e > 1) p = c_mul(p, x);
       val_put(M.tab, (e - 1) * M.cols + v, p);
     }
@@ -277,8 +283,8 @@ __device__ __forceinline__ void val_table(const ValView& S, const ValLds<L>& M, 
 template <int L>
 __device__ __forceinline__ void val_inverses(const ValView& S, const ValLds<L>& M, int lv, int VW) {
   for (int v = VW - 1 - lv; v < S.n; v += VW) {
-    const C<L> x = val_power(M, v, 1);
-    val_put(M.tab, S.emax * M.cols + v, val_mag(x) == 0.0 ? c_one<L>() : val_inverse(x));
+    const C<L> x = val_get<L>(M.tab, v);
+    val_put(M.tab, S.tab * M.cols + v, val_mag(x) == 0.0 ? c_one<L>() : val_inverse(x));
   }
 }
 
@@ -367,11 +373,18 @@ __device__ __forceinline__ void val_prefetch(const ValView& S, int p, int w, int
 
 // one factor, x^d of a record; with ZERO a zero variable counts into z and is
 // taken as 1
-template <int L, bool ZERO>
+template <int L, bool ZERO, bool FULL>
 __device__ __forceinline__ C<L> val_factor(const ValLds<L>& M, uint32_t r, int& z) {
-  C<L> f = val_get<L>(M.tab, int(r));
+  C<L> f;
+  if constexpr (FULL) {
+    f = val_get<L>(M.tab, int(r));
+  } else {
+    const uint32_t e = r / uint32_t(M.cols);
+    f = val_get<L>(M.tab, int(r - e * uint32_t(M.cols)));
+    if (e > 0) f = c_pow(f, int(e) + 1);
+  }
   if constexpr (ZERO) {
-    if (val_mag(val_power(M, int(r % uint32_t(M.cols)), 1)) == 0.0) {
+    if (val_mag(val_get<L>(M.tab, int(r % uint32_t(M.cols)))) == 0.0) {
       z += r < uint32_t(M.cols) ? 1 : 2;
       f = c_one<L>();
     }
@@ -382,7 +395,7 @@ __device__ __forceinline__ C<L> val_factor(const ValLds<L>& M, uint32_t r, int& 
 // Product phase of one unit by one wavefront (its first records and
 // coefficient in r, cf): values into LDS.  Four factors at a time, joined as
 // (f0 f1)(f2 f3), so that only one product in four is in the lane's chain.
-template <int L, bool ZERO>
+template <int L, bool ZERO, bool FULL>
 __device__ __forceinline__ void val_unit(const ValView& S, const ValLds<L>& M, const ValUnit& u, int lane,
                                          uint32_t (&r)[4], const C<L>& cf, bool direct, bool weighted,
                                          const C<L>& weight) {
@@ -396,8 +409,8 @@ __device__ __forceinline__ void val_unit(const ValView& S, const ValLds<L>& M, c
     uint32_t nx[4];
 #pragma unroll
     for (int i = 0; i < 4; ++i) nx[i] = val_ld(rec, 64 * min(i0 + 4 + i, seg - 1));
-    const C<L> f0 = val_factor<L, ZERO>(M, r[0], z), f1 = val_factor<L, ZERO>(M, r[1], z);
-    const C<L> f2 = val_factor<L, ZERO>(M, r[2], z), f3 = val_factor<L, ZERO>(M, r[3], z);
+    const C<L> f0 = val_factor<L, ZERO, FULL>(M, r[0], z), f1 = val_factor<L, ZERO, FULL>(M, r[1], z);
+    const C<L> f2 = val_factor<L, ZERO, FULL>(M, r[2], z), f3 = val_factor<L, ZERO, FULL>(M, r[3], z);
     const C<L> B = c_mul(c_mul(f0, f1), c_mul(f2, f3));
     A = i0 == 0 ? B : c_mul(A, B);
 #pragma unroll
@@ -406,7 +419,7 @@ __device__ __forceinline__ void val_unit(const ValView& S, const ValLds<L>& M, c
 #pragma unroll
   for (int i = 0; i < 3; ++i)
     if (i0 + i < seg) {
-      const C<L> f = val_factor<L, ZERO>(M, r[i], z);
+      const C<L> f = val_factor<L, ZERO, FULL>(M, r[i], z);
       A = i0 + i == 0 ? f : c_mul(A, f);
     }
   for (int m = 1; m < s; m <<= 1) {
@@ -501,7 +514,7 @@ __device__ __forceinline__ R<NL> val_total(const ValSum<NL>& s) {
 
 // partial derivative of monomial t with respect to column v (exponent d),
 // every factor in turn: the definition, for points the division does not suit
-template <int L>
+template <int L, bool SMALL>
 __device__ C<L> val_direct(const ValView& S, const ValLds<L>& M, const ValBlock& blk, uint32_t t, int v, int d) {
   uint32_t u = blk.unit0;
   while (u + 1 < blk.unit1 && val_ld(S.unit, u + 1).mon <= t) ++u;
@@ -514,9 +527,9 @@ __device__ C<L> val_direct(const ValView& S, const ValLds<L>& M, const ValBlock&
       const int wv = int(w % uint32_t(M.cols)), wd = int(w / uint32_t(M.cols)) + 1;
       if (wv == S.n) continue;
       if (wv != v)
-        r = c_mul(r, val_power(M, wv, wd));
+        r = c_mul(r, val_power<L, SMALL>(S, M, wv, wd));
       else if (wd > 1)
-        r = c_mul(r, val_power(M, v, wd - 1));
+        r = c_mul(r, val_power<L, SMALL>(S, M, v, wd - 1));
     }
   return c_mul_d(r, double(d));
 }
@@ -524,13 +537,13 @@ __device__ C<L> val_direct(const ValView& S, const ValLds<L>& M, const ValBlock&
 // Column `col`'s sum over a slice by the calling lane and its Q - 1
 // neighbours (the slice's first entries in r): the block's share of J_pv, in
 // every one of the Q lanes.  All lanes of the wavefront call it.
-template <int L, bool ZERO>
+template <int L, bool ZERO, bool SMALL>
 __device__ __forceinline__ C<L> val_column(const ValView& S, const ValLds<L>& M, const ValBlock& blk, uint32_t e0,
                                            uint32_t e1, int col, int lane, uint32_t (&r)[4]) {
   constexpr int NL = limbs_of(L);
   const uint32_t* ell = S.ell + lane;
   ValSum<NL> re{}, im{};
-  const bool at_zero = ZERO && val_mag(val_power(M, col, 1)) == 0.0;  // the column's own variable
+  const bool at_zero = ZERO && val_mag(val_get<L>(M.tab, col)) == 0.0;  // the column's own variable
   for (uint32_t i0 = e0; i0 < e1; i0 += 4) {
     uint32_t nx[4];
 #pragma unroll
@@ -563,18 +576,23 @@ __device__ __forceinline__ C<L> val_column(const ValView& S, const ValLds<L>& M,
   J.re = val_total<NL>(re);
   if constexpr (!is_real(L)) J.im = val_total<NL>(im);
   for (int m = 1; m < (1 << S.lgQ); m <<= 1) J = c_add(J, shfl_xor_c(J, m));
-  return c_mul(J, val_get<L>(M.tab, S.emax * M.cols + col));
+  if constexpr (SMALL)
+    if (!S.inv) {
+      const C<L> x = val_get<L>(M.tab, col);
+      return val_mag(x) == 0.0 ? J : c_mul(J, val_inverse(x));
+    }
+  return c_mul(J, val_get<L>(M.tab, S.tab * M.cols + col));
 }
 
 // the same by products of all factors
-template <int L>
+template <int L, bool SMALL>
 __device__ __forceinline__ C<L> val_column_direct(const ValView& S, const ValLds<L>& M, const ValBlock& blk, uint32_t e0,
                                                   uint32_t e1, int col, int lane) {
   const uint32_t* ell = S.ell + lane;
   C<L> J = c_zero<L>();
   for (uint32_t i = e0; i < e1; ++i) {
     const uint32_t r = val_ld(ell, 64 * size_t(i)), t = r & 0xffffu;
-    if (t < blk.nmon) J = c_add(J, val_direct(S, M, blk, t, col, int(r >> 16)));
+    if (t < blk.nmon) J = c_add(J, val_direct<L, SMALL>(S, M, blk, t, col, int(r >> 16)));
   }
   for (int m = 1; m < (1 << S.lgQ); m <<= 1) J = c_add(J, shfl_xor_c(J, m));
   return J;
@@ -604,7 +622,7 @@ __device__ __forceinline__ C<L> val_f(const ValLds<L>& M, const ValBlock& blk, i
 // same number of blocks).  MODE_EVAL: F and J through O; MODE_FONLY: F;
 // MODE_ADJ: conj(v_p) J added to M.sum.  inv: the point's first row, which
 // forms the reciprocals.
-template <int L, int MODE>
+template <int L, int MODE, bool SMALL>
 __device__ __forceinline__ void val_row(const ValView& S, const ValLds<L>& M, const OutView& O, int pt, int p, int lv,
                                         int VW, bool live, bool inv, const C<L>& weight, ValPre<L>& pre) {
   const int lane = lv & 63, w = val_uniform(lv >> 6), nw = VW >> 6;
@@ -621,12 +639,16 @@ __device__ __forceinline__ void val_row(const ValView& S, const ValLds<L>& M, co
         pre.u = val_unit_of(S, blk, u);
         val_records<L>(S, blk, pre.u, lane, pre.r, pre.cf);
       }
-      if (zero)
-        val_unit<L, true>(S, M, pre.u, lane, pre.r, pre.cf, direct0, weighted, weight);
-      else
-        val_unit<L, false>(S, M, pre.u, lane, pre.r, pre.cf, direct0, weighted, weight);
+      if (SMALL && S.tab < S.emax) {
+        // the forms with zero counts hold for every point
+        val_unit<L, true, false>(S, M, pre.u, lane, pre.r, pre.cf, direct0, weighted, weight);
+      } else if (zero) {
+        val_unit<L, true, true>(S, M, pre.u, lane, pre.r, pre.cf, direct0, weighted, weight);
+      } else {
+        val_unit<L, false, true>(S, M, pre.u, lane, pre.r, pre.cf, direct0, weighted, weight);
+      }
     }
-    if (MODE != MODE_FONLY && inv && b == b0) val_inverses(S, M, lv, VW);
+    if (MODE != MODE_FONLY && inv && (!SMALL || S.inv) && b == b0) val_inverses(S, M, lv, VW);
     if (lv == 0) val_put(M.val, int(blk.nmon), c_zero<L>());
     __syncthreads();
     const bool direct = direct0 || val_uniform(M.flag[1]) != 0;
@@ -647,12 +669,12 @@ __device__ __forceinline__ void val_row(const ValView& S, const ValLds<L>& M, co
         }
         C<L> J;
         if (direct) {
-          J = val_column_direct<L>(S, M, blk, pre.e0, pre.e1, pre.col, lane);
+          J = val_column_direct<L, SMALL>(S, M, blk, pre.e0, pre.e1, pre.col, lane);
           if (weighted) J = c_mul(J, weight);
         } else if (zero) {
-          J = val_column<L, true>(S, M, blk, pre.e0, pre.e1, pre.col, lane, pre.el);
+          J = val_column<L, true, SMALL>(S, M, blk, pre.e0, pre.e1, pre.col, lane, pre.el);
         } else {
-          J = val_column<L, false>(S, M, blk, pre.e0, pre.e1, pre.col, lane, pre.el);
+          J = val_column<L, false, SMALL>(S, M, blk, pre.e0, pre.e1, pre.col, lane, pre.el);
         }
         if (pre.col < S.n && (lane & ((1 << S.lgQ) - 1)) == 0) {
           if constexpr (MODE == MODE_ADJ) {
@@ -683,7 +705,7 @@ constexpr int kValThreads = 512;
 // when there is one) of point pt, c = pt * groups + i.  Several copies share a
 // workgroup when VW is small; systems with rows of several blocks take one
 // copy per workgroup.  grid: ceil(P groups / copies)
-template <int L, int MODE>
+template <int L, int MODE, bool SMALL>
 __global__ __launch_bounds__(kValThreads, limbs_of(L) == 4 ? 2 : 4) void val_rows_kernel(ValView S, OutView O, const double* __restrict__ x,
                                                                int64_t x_pt, int P, int copies, int Rr, int groups,
                                                                int copy_doubles) {
@@ -713,13 +735,13 @@ __global__ __launch_bounds__(kValThreads, limbs_of(L) == 4 ? 2 : 4) void val_row
       M.flag[1] = 0;
     }
     __syncthreads();
-    val_row<L, MODE>(S, M, O, pt, p, lv, VW, in, r == 0, c_one<L>(), pre);
+    val_row<L, MODE, SMALL>(S, M, O, pt, p, lv, VW, in, r == 0, c_one<L>(), pre);
   }
 }
 
 // Adjoint: one workgroup (one copy) per point and group of gsize rows; its
 // column sums part[(pt NG + gi)][components][n]
-template <int L>
+template <int L, bool SMALL>
 __global__ __launch_bounds__(kValThreads, limbs_of(L) == 4 ? 2 : 4) void val_adjoint_kernel(ValView S, const double* __restrict__ x, int64_t x_pt,
                                                                   const double* __restrict__ v, int64_t v_pt, int NG,
                                                                   int gsize, double* __restrict__ part) {
@@ -744,7 +766,7 @@ __global__ __launch_bounds__(kValThreads, limbs_of(L) == 4 ? 2 : 4) void val_adj
       M.flag[1] = 0;
     }
     __syncthreads();
-    val_row<L, MODE_ADJ>(S, M, O, 0, p, lv, VW, true, p == gi * gsize, weight, pre);
+    val_row<L, MODE_ADJ, SMALL>(S, M, O, 0, p, lv, VW, true, p == gi * gsize, weight, pre);
   }
   double* out = part + size_t(pt * NG + gi) * width_of(L) * S.n;
   for (int c = lv; c < S.n; c += VW) store_planar(out, S.n, c, val_get<L>(M.sum, c));
@@ -776,7 +798,7 @@ __global__ __launch_bounds__(256) void val_adjoint_reduce_kernel(int n, int NG, 
 // as the workgroup has copies of the system's width (systems of several blocks
 // per row have kValThreads).  Every workgroup reaches the exit test after
 // every item, so the grid drains.
-template <int L, int MODE>
+template <int L, int MODE, bool SMALL>
 __global__ __launch_bounds__(kValThreads, limbs_of(L) == 4 ? 2 : 4) void val_batch_kernel(const ValView* __restrict__ views,
                                                                 const uint64_t* __restrict__ items, int64_t nitems,
                                                                 int* counter, int P, const double* __restrict__ x,
@@ -796,7 +818,7 @@ __global__ __launch_bounds__(kValThreads, limbs_of(L) == 4 ? 2 : 4) void val_bat
     const int lv = int(threadIdx.x) & (VW - 1);
     const OutView O = batch_out_view<L>(out, s, S.n, S.N, P);
     const ValLds<L> M =
-        val_lds<L>(S, lds + val_copy_doubles<L>(S.n, S.emax, S.max_mon, S.multi != 0) * cp, S.multi != 0);
+        val_lds<L>(S, lds + val_copy_doubles<L>(S.n, S.tab + S.inv, S.max_mon, S.multi != 0) * cp, S.multi != 0);
     const double* xs = x + x_off[s] * P;
     for (int pt0 = 0; pt0 < P; pt0 += copies) {
       const int pt = pt0 + cp;
@@ -809,7 +831,7 @@ __global__ __launch_bounds__(kValThreads, limbs_of(L) == 4 ? 2 : 4) void val_bat
       __syncthreads();
       val_table<L>(S, M, xpt, lv, VW, x0);
       __syncthreads();
-      val_row<L, MODE>(S, M, O, pt, p, lv, VW, live, true, c_one<L>(), pre);
+      val_row<L, MODE, SMALL>(S, M, O, pt, p, lv, VW, live, true, c_one<L>(), pre);
     }
   }
 }

@@ -88,6 +88,11 @@ SHAPES = [
     (4, False, 16, [17] * 4, 6, 3),
     (4, True, 128, [1024, 1030, 3], 8, 2),
     (4, False, 200, [65] * 3, 150, 1),        # sixteen lanes per monomial
+    # the table holds x alone: one block, several, a whole row of more values than a block has
+    (2, False, 900, [300, 250], 10, 4),
+    (4, False, 600, [700, 1, 400], 12, 3),
+    (4, False, 1000, [900, 700], 8, 2),
+    (4, True, 1900, [1500, 1400], 8, 3),
 ]
 
 
@@ -122,6 +127,33 @@ def test_zero_variables(pe, L, real, zeros):
     x[:, :, :, [3, 7, 8, 11, 19][:zeros]] = 0.0
     F, J = evaluate(pe, s, x, real)
     check(s, x[0], F[0], J[0], range(4))
+
+
+@pytest.mark.parametrize("L,n,mons", [(2, 900, [300, 250]), (4, 600, [500, 300])])
+def test_small_table(pe, L, n, mons):
+    """The table of x alone with zero variables and with a variable out of range, and the adjoint."""
+    import torch
+    s = ragged((45, L), L, n, mons, 12, 3, False)
+    x = points((46, L), 3, n, L, False)
+    x[1, :, :, [3, 70, 71, 500]] = 0.0
+    x[2, :, :, 9] *= 2.0**-310
+    F, J = evaluate(pe, s, x, False)
+    for pt in range(3):
+        check(s, x[pt], F[pt], J[pt], range(len(mons)))
+    v = synth.unit_circle_points(synth.rng_for((47, L)), 3, len(mons), L)
+    S = pe.System.from_sparse(s)
+    g = S.adjoint(U.to_device(x), U.to_device(v)).cpu().numpy()
+    torch.cuda.synchronize()
+    S.close()
+    import oracle as O
+    cols = [0, 3, 9, 71, n - 1]
+    for pt in range(3):
+        exact = O.adjoint_columns(s, x[pt], v[pt], cols)
+        Sc = O.abs_sums_columns(s, x[pt], cols)
+        av = np.hypot(v[pt, 0].sum(axis=0), v[pt, 1].sum(axis=0))
+        for j in cols:
+            scale = sum(q * av[p] for p, q in Sc[j].items())
+            assert O.rel_error(g[pt, 0, :, j], g[pt, 1, :, j], exact[j], scale) <= 3 * U.tolerance(s)
 
 
 @pytest.mark.parametrize("L,real", [(1, False), (2, False), (4, False), (4, True)])
