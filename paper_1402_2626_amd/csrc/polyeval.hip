@@ -341,11 +341,12 @@ size_t val_doubles(int code, int n, int blocks, int max_mon, bool sums) {
 // monomials of a block of the value layout: 32 KB of values
 int val_block_mons(int code) { return 4096 / width_of(code); }
 
+// all of a CU's LDS but what the batch kernel has besides
+size_t val_lds_all() { return device_lds_limit() - 64; }
+
 // half of a CU's LDS (two workgroups per CU); quad double, which is bound by
 // arithmetic, all of it
-size_t val_lds_limit(const pe_system* sys) {
-  return sys->level == 4 ? device_lds_limit() : device_lds_limit() / 2;
-}
+size_t val_lds_limit(const pe_system* sys) { return sys->level == 4 ? val_lds_all() : val_lds_all() / 2; }
 
 // Whether a system is evaluated through monomial values (value_kernels.hpp).
 // The products are k per monomial of k variables against about 4 k - 3, so
@@ -426,7 +427,7 @@ pe_status upload_values(pe_system* sys, hipStream_t hs) {
   // (and a batch's workgroup of kValThreads holds as many copies as that
   // leaves within half of a CU's LDS)
   const size_t copy = val_doubles(sys->code, V.n, V.tab + V.inv, V.max_mon, V.multi != 0) * sizeof(double);
-  while (vw < kValThreads && size_t(kValThreads / vw) * copy > device_lds_limit() / 2) vw *= 2;
+  while (vw < kValThreads && size_t(kValThreads / vw) * copy > val_lds_all() / 2) vw *= 2;
   while ((1 << V.lgvw) < vw) ++V.lgvw;
   V.mcoef = sys->view.mcoef;
   V.row_order = sys->view.row_order;
@@ -438,7 +439,7 @@ pe_status upload_values(pe_system* sys, hipStream_t hs) {
     return e;
   PE_HIP(hipStreamSynchronize(hs));
   sys->use_val = true;
-  sys->use_val_adj = val_doubles(sys->code, V.n, V.tab + V.inv, V.max_mon, true) * sizeof(double) <= device_lds_limit();
+  sys->use_val_adj = val_doubles(sys->code, V.n, V.tab + V.inv, V.max_mon, true) * sizeof(double) <= val_lds_all();
   return PE_OK;
 }
 
