@@ -512,8 +512,9 @@ __device__ __forceinline__ R<NL> val_total(const ValSum<NL>& s) {
   return r;
 }
 
-// partial derivative of monomial t with respect to column v (exponent d),
-// every factor in turn: the definition, for points the division does not suit
+// partial derivative of monomial t with respect to column v (exponent d), or
+// for v < 0 its value (d = 1), every factor in turn: the definition, for points
+// the division does not suit
 template <int L, bool SMALL>
 __device__ C<L> val_direct(const ValView& S, const ValLds<L>& M, const ValBlock& blk, uint32_t t, int v, int d) {
   uint32_t u = blk.unit0;
@@ -598,20 +599,27 @@ __device__ __forceinline__ C<L> val_column_direct(const ValView& S, const ValLds
   return J;
 }
 
-// F's share of a block by one wavefront, the same in every lane
-template <int L>
-__device__ __forceinline__ C<L> val_f(const ValLds<L>& M, const ValBlock& blk, int lane, bool zero) {
+// F's share of a block by one wavefront, the same in every lane.  Where the
+// row takes direct products, so does F: a value stored with its zero factors
+// left out is not a term of F beside a factor that is out of range.
+template <int L, bool SMALL>
+__device__ __forceinline__ C<L> val_f(const ValView& S, const ValLds<L>& M, const ValBlock& blk, int lane, bool zero,
+                                      bool direct) {
   constexpr int NL = limbs_of(L);
-  ValSum<NL> re{}, im{};
-  for (uint32_t t = lane; t < blk.nmon; t += 64) {
-    if (zero && M.zeros[t] != 0) continue;
-    const C<L> V = val_get<L>(M.val, int(t));
-    val_add<NL>(re, V.re, 1.0);
-    if constexpr (!is_real(L)) val_add<NL>(im, V.im, 1.0);
+  C<L> f = c_zero<L>();
+  if (direct) {
+    for (uint32_t t = lane; t < blk.nmon; t += 64) f = c_add(f, val_direct<L, SMALL>(S, M, blk, t, -1, 1));
+  } else {
+    ValSum<NL> re{}, im{};
+    for (uint32_t t = lane; t < blk.nmon; t += 64) {
+      if (zero && M.zeros[t] != 0) continue;
+      const C<L> V = val_get<L>(M.val, int(t));
+      val_add<NL>(re, V.re, 1.0);
+      if constexpr (!is_real(L)) val_add<NL>(im, V.im, 1.0);
+    }
+    f.re = val_total<NL>(re);
+    if constexpr (!is_real(L)) f.im = val_total<NL>(im);
   }
-  C<L> f;
-  f.re = val_total<NL>(re);
-  if constexpr (!is_real(L)) f.im = val_total<NL>(im);
 #pragma unroll 1
   for (int m = 1; m < 64; m <<= 1) f = c_add(f, shfl_xor_c(f, m));
   return f;
@@ -653,7 +661,7 @@ __device__ __forceinline__ void val_row(const ValView& S, const ValLds<L>& M, co
     __syncthreads();
     const bool direct = direct0 || val_uniform(M.flag[1]) != 0;
     if (MODE != MODE_ADJ && w == nw - 1) {
-      const C<L> f = val_f<L>(M, blk, lane, zero);
+      const C<L> f = val_f<L, SMALL>(S, M, blk, lane, zero, direct);
       F = b == b0 ? f : c_add(F, f);
     }
     if (MODE != MODE_FONLY) {

@@ -1,0 +1,87 @@
+"""Evaluation through monomial values (value_kernels.hpp) where a value or a partial product leaves the range in which
+the division by x_v is exact enough: F beside zero and out-of-range variables, coefficients and weights that are tiny or
+not finite, products that leave the range and come back.  Against the exact oracle with the tolerance of the other
+evaluation tests, and for what is finite against the reverse sweep (the same monomials over more variables)."""
+import numpy as np
+import pytest
+
+import gpu_util as U
+import oracle as O
+import test_gpu_values as V
+from paper_1402_2626_amd import synth
+
+pytestmark = pytest.mark.gpu
+
+
+@pytest.fixture(scope="module")
+def pe():
+    import torch
+    if not torch.cuda.is_available():
+        pytest.fail("no GPU visible")
+    from paper_1402_2626_amd import polyeval
+    return polyeval
+
+
+def uniform(seed, level, n, N, m, pick, coef=None):
+    """N polynomials of m monomials over the variables pick(rng, p, i), exponents 1."""
+    rng = synth.rng_for(seed)
+    var = [np.sort(np.asarray(pick(rng, p, i), np.int32)) for p in range(N) for i in range(m)]
+    k = np.array([len(v) for v in var])
+    return synth.PolySystem(level=level, n_vars=n, poly_ptr=np.arange(0, N * m + 1, m, dtype=np.int64),
+                            mon_ptr=np.concatenate([[0], np.cumsum(k)]).astype(np.int64), var_idx=np.concatenate(var),
+                            exps=np.ones(int(k.sum()), np.int32),
+                            coef=synth.unit_circle(rng, N * m, level) if coef is None else coef)
+
+
+def sweep(pe, s, x, wide):
+    """F and J of the reverse sweep."""
+    F, J = V.evaluate(pe, V.widened(s, wide), np.concatenate([x, np.zeros(x.shape[:3] + (wide - s.n_vars,))], 3), False)
+    return F, J[..., :s.n_vars]
+
+
+# the table of x alone (emax 4 at these n) and the full table
+@pytest.mark.parametrize("L,n,emax", [(2, 900, 4), (4, 600, 3), (1, 40, 2), (2, 40, 2), (4, 40, 2)])
+def test_zero_beside_out_of_range(pe, L, n, emax):
+    """Exact zeros and a variable out of range at one point: F with J, F alone and in a batch."""
+    import torch
+    s = V.ragged((201, L, n), L, n, [700, 690], 10, emax, False)
+    x = V.points((202, L), 2, n, L, False)
+    x[:, :, :, [3, 7, n // 2]] = 0.0
+    x[0, :, :, 9] *= 2.0**-310
+    x[1, :, :, 11] *= 2.0**(310 if emax < 4 else 240)  # beyond 2^(900 / emax); its powers are representable
+    F, J = V.evaluate(pe, s, x, False)
+    F1, _ = V.evaluate(pe, s, x, False, want_J=False)
+    assert np.array_equal(F, F1)
+    for pt in range(2):
+        V.check(s, x[pt], F[pt], J[pt], range(2))
+    S = pe.System.from_sparse(s)
+    B = pe.Batch([S])
+    Fb, Jb = B.eval(U.to_device(x).reshape(-1), 2)
+    torch.cuda.synchronize()
+    assert np.array_equal(Fb.cpu().numpy(), F.reshape(-1)) and np.array_equal(Jb.cpu().numpy(), J.reshape(-1))
+    B.close()
+    S.close()
+
+
+@pytest.mark.parametrize("L,n", [(2, 900), (4, 600), (2, 40)])
+@pytest.mark.parametrize("bad", [np.nan, np.inf])
+def test_zero_times_nonfinite(pe, L, n, bad):
+    """A variable that is not finite and occurs beside a zero only: F is not finite where the sweep's is not."""
+    others = np.array([v for v in range(n) if v not in (3, 9)])
+
+    def pick(rng, p, i):
+        if p == 0 and i == 5:
+            return [3, 9] + list(rng.choice(others, size=8, replace=False))
+        return rng.choice(others, size=10, replace=False)
+
+    s = uniform((211, L), L, n, 2, 400, pick)
+    s.exps[::7] = 4
+    x = V.points((212, L), 1, n, L, False)
+    x[0, :, :, 3] = 0.0
+    x[0, :, :, 9] = 0.0
+    x[0, 0, 0, 9] = bad
+    F, J = V.evaluate(pe, s, x, False)
+    Fw, Jw = sweep(pe, s, x, 4 * n + s.nnz // 2)
+    ok = lambda a: np.isfinite(a).all(axis=(1, 2))  # noqa: E731
+    assert np.array_equal(ok(F), ok(Fw)) and not ok(F)[0, 0] and ok(F)[0, 1]
+    assert np.array_equal(ok(J), ok(Jw))
