@@ -516,12 +516,14 @@ __device__ __forceinline__ R<NL> val_total(const ValSum<NL>& s) {
 // for v < 0 its value (d = 1), every factor in turn: the definition, for points
 // the division does not suit
 template <int L, bool SMALL>
-__device__ C<L> val_direct(const ValView& S, const ValLds<L>& M, const ValBlock& blk, uint32_t t, int v, int d) {
+__device__ C<L> val_direct(const ValView& S, const ValLds<L>& M, const ValBlock& blk, uint32_t t, int v, int d,
+                           bool weighted, const C<L>& weight) {
   uint32_t u = blk.unit0;
   while (u + 1 < blk.unit1 && val_ld(S.unit, u + 1).mon <= t) ++u;
   const ValUnit U = val_ld(S.unit, u);
   const int g = int(t) - int(U.mon);
   C<L> r = val_ld_coef<L>(S.mcoef + size_t(blk.mon0 + t) * width_of(L));
+  if (weighted) r = c_mul(r, weight);
   for (int i = 0; i < int(U.seg); ++i)
     for (int q = 0; q < (1 << U.lgs); ++q) {
       const uint32_t w = val_ld(S.rec, U.base + 64 * i + (g << U.lgs) + q);
@@ -588,12 +590,12 @@ __device__ __forceinline__ C<L> val_column(const ValView& S, const ValLds<L>& M,
 // the same by products of all factors
 template <int L, bool SMALL>
 __device__ __forceinline__ C<L> val_column_direct(const ValView& S, const ValLds<L>& M, const ValBlock& blk, uint32_t e0,
-                                                  uint32_t e1, int col, int lane) {
+                                                  uint32_t e1, int col, int lane, bool weighted, const C<L>& weight) {
   const uint32_t* ell = S.ell + lane;
   C<L> J = c_zero<L>();
   for (uint32_t i = e0; i < e1; ++i) {
     const uint32_t r = val_ld(ell, 64 * size_t(i)), t = r & 0xffffu;
-    if (t < blk.nmon) J = c_add(J, val_direct<L, SMALL>(S, M, blk, t, col, int(r >> 16)));
+    if (t < blk.nmon) J = c_add(J, val_direct<L, SMALL>(S, M, blk, t, col, int(r >> 16), weighted, weight));
   }
   for (int m = 1; m < (1 << S.lgQ); m <<= 1) J = c_add(J, shfl_xor_c(J, m));
   return J;
@@ -608,7 +610,7 @@ __device__ __forceinline__ C<L> val_f(const ValView& S, const ValLds<L>& M, cons
   constexpr int NL = limbs_of(L);
   C<L> f = c_zero<L>();
   if (direct) {
-    for (uint32_t t = lane; t < blk.nmon; t += 64) f = c_add(f, val_direct<L, SMALL>(S, M, blk, t, -1, 1));
+    for (uint32_t t = lane; t < blk.nmon; t += 64) f = c_add(f, val_direct<L, SMALL>(S, M, blk, t, -1, 1, false, c_one<L>()));
   } else {
     ValSum<NL> re{}, im{};
     for (uint32_t t = lane; t < blk.nmon; t += 64) {
@@ -677,8 +679,7 @@ __device__ __forceinline__ void val_row(const ValView& S, const ValLds<L>& M, co
         }
         C<L> J;
         if (direct) {
-          J = val_column_direct<L, SMALL>(S, M, blk, pre.e0, pre.e1, pre.col, lane);
-          if (weighted) J = c_mul(J, weight);
+          J = val_column_direct<L, SMALL>(S, M, blk, pre.e0, pre.e1, pre.col, lane, weighted, weight);
         } else if (zero) {
           J = val_column<L, true, SMALL>(S, M, blk, pre.e0, pre.e1, pre.col, lane, pre.el);
         } else {

@@ -85,3 +85,32 @@ def test_zero_times_nonfinite(pe, L, n, bad):
     ok = lambda a: np.isfinite(a).all(axis=(1, 2))  # noqa: E731
     assert np.array_equal(ok(F), ok(Fw)) and not ok(F)[0, 0] and ok(F)[0, 1]
     assert np.array_equal(ok(J), ok(Jw))
+
+
+def check_adjoint(s, x, v, g, cols):
+    exact = O.adjoint_columns(s, x, v, cols)
+    Sc = O.abs_sums_columns(s, x, cols)
+    av = np.hypot(v[0].sum(axis=0), v[1].sum(axis=0))
+    for j in cols:
+        scale = sum(q * av[p] for p, q in Sc[j].items())
+        assert O.rel_error(g[0, :, j], g[1, :, j], exact[j], scale) <= 3 * U.tolerance(s), j
+
+
+@pytest.mark.parametrize("L", [1, 2, 4])
+@pytest.mark.parametrize("bad", [np.nan, np.inf])
+def test_nonfinite_weight(pe, L, bad):
+    """A weight that is not finite reaches the variables of its polynomial and no others."""
+    import torch
+    n, m = 40, 600
+    s = uniform((241, L), L, n, 4, m, lambda rng, p, i: rng.choice(20, size=4, replace=False) + 20 * (p & 1))
+    x = V.points((242, L), 1, n, L, False)
+    v = synth.unit_circle_points(synth.rng_for((243, L)), 1, 4, L)
+    v[0, 0, 0, 2] = bad
+    S = pe.System.from_sparse(s)
+    g = S.adjoint(U.to_device(x), U.to_device(v)).cpu().numpy()[0]
+    torch.cuda.synchronize()
+    S.close()
+    assert not np.isfinite(g[:, :, :20]).all(axis=(0, 1)).any()
+    assert np.isfinite(g[:, :, 20:]).all()
+    v[0, :, :, 2] = 0.0
+    check_adjoint(s, x[0], v[0], g, [20, 31, 39])
