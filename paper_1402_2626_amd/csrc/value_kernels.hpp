@@ -16,9 +16,10 @@
 // of exponent 1: the value is the partial derivative with respect to that
 // variable; otherwise the monomial contributes nothing).  Points with values
 // outside 2^-300 .. 2^300 (2^(900 / emax) for large exponents), infinities or
-// NaN, and rows in which a value leaves 2^-750 .. 2^900 (below, a quad
-// double's last limbs would underflow), form every partial derivative as its
-// own product instead (val_direct), in the same kernel.
+// NaN, and rows in which a product of variables or a value (with its
+// coefficient and weight) leaves 2^-750 .. 2^900 (below, a quad double's last
+// limbs would underflow), form every partial derivative and every term of F as
+// its own product instead (val_direct), in the same kernel.
 //
 // A COPY of VW threads (a multiple of 64) evaluates rows at one point:
 //   1. powers x_v^1 .. x_v^emax of every variable into LDS (and 1 / x_v, by
@@ -174,15 +175,6 @@ __device__ __forceinline__ ValLds<L> val_lds(const ValView& S, double* base, boo
   M.zeros = reinterpret_cast<uint8_t*>(z);
   M.flag = reinterpret_cast<int*>(z + (S.max_mon + 8) / 8);
   return M;
-}
-
-// SMALL: the kernels that also take systems whose table holds x alone (apart,
-// since the code costs the others 3 to 9 %)
-template <int L, bool SMALL>
-__device__ __forceinline__ C<L> val_power(const ValView& S, const ValLds<L>& M, int v, int e) {
-  if constexpr (SMALL)
-    if (e > S.tab) return c_pow(val_get<L>(M.tab, v), e);
-  return val_get<L>(M.tab, (e - 1) * M.cols + v);
 }
 
 template <int L>
@@ -371,6 +363,9 @@ __device__ __forceinline__ void val_prefetch(const ValView& S, int p, int w, int
   }
 }
 
+// SMALL (FULL false here): the kernels that also take systems whose table
+// holds x alone (apart, since the code costs the others 3 to 9 %)
+//
 // one factor, x^d of a record; with ZERO a zero variable counts into z and is
 // taken as 1
 template <int L, bool ZERO, bool FULL>
@@ -432,8 +427,11 @@ __device__ __forceinline__ void val_unit(const ValView& S, const ValLds<L>& M, c
     const int t = u.mon + g;
     val_put(M.val, t, V);
     if constexpr (ZERO) M.zeros[t] = uint8_t(min(z, 2));
-    const double mag = val_mag(A);
-    const bool fine = mag >= 0x1p-750 && mag <= 0x1p900 && val_mag(V) <= 0x1p1000 && !val_nan(V);
+    // the value is divided by x_v, so it needs its last limbs as the product
+    // does, unless it is zero by its coefficient or weight
+    const double mag = val_mag(A), vm = val_mag(V);
+    const bool none = val_mag(cf) == 0.0 || (weighted && val_mag(weight) == 0.0);
+    const bool fine = mag >= 0x1p-750 && mag <= 0x1p900 && (vm >= 0x1p-750 || none) && vm <= 0x1p1000 && !val_nan(V);
     if (!fine && !direct) M.flag[1] = 1;
   }
 }
@@ -512,29 +510,49 @@ __device__ __forceinline__ R<NL> val_total(const ValSum<NL>& s) {
   return r;
 }
 
+// r 2^e with the leading limb of r's larger part in [0.5, 1); zeros and what
+// is not finite stay as they are
+template <int L>
+__device__ __forceinline__ void val_norm(C<L>& r, int& e) {
+  const double mag = val_mag(r);
+  if (!(mag > 0.0 && mag <= 0x1.fffffffffffffp1023)) return;
+  const int k = __builtin_amdgcn_frexp_exp(mag);
+  r = bl_ldexp(r, -k);
+  e += k;
+}
+
 // partial derivative of monomial t with respect to column v (exponent d), or
 // for v < 0 its value (d = 1), every factor in turn: the definition, for points
-// the division does not suit
-template <int L, bool SMALL>
+// the division does not suit.  The product is kept as r 2^e, so that no order
+// of the factors leaves the range on the way to a result within it.
+template <int L>
 __device__ C<L> val_direct(const ValView& S, const ValLds<L>& M, const ValBlock& blk, uint32_t t, int v, int d,
-                           bool weighted, const C<L>& weight) {
+                           bool weighted, C<L> weight) {
   uint32_t u = blk.unit0;
   while (u + 1 < blk.unit1 && val_ld(S.unit, u + 1).mon <= t) ++u;
   const ValUnit U = val_ld(S.unit, u);
   const int g = int(t) - int(U.mon);
+  int e = 0;
   C<L> r = val_ld_coef<L>(S.mcoef + size_t(blk.mon0 + t) * width_of(L));
-  if (weighted) r = c_mul(r, weight);
+  val_norm(r, e);
+  if (weighted) {
+    val_norm(weight, e);
+    r = c_mul(r, weight);
+    val_norm(r, e);
+  }
   for (int i = 0; i < int(U.seg); ++i)
     for (int q = 0; q < (1 << U.lgs); ++q) {
       const uint32_t w = val_ld(S.rec, U.base + 64 * i + (g << U.lgs) + q);
-      const int wv = int(w % uint32_t(M.cols)), wd = int(w / uint32_t(M.cols)) + 1;
-      if (wv == S.n) continue;
-      if (wv != v)
-        r = c_mul(r, val_power<L, SMALL>(S, M, wv, wd));
-      else if (wd > 1)
-        r = c_mul(r, val_power<L, SMALL>(S, M, v, wd - 1));
+      const int wv = int(w % uint32_t(M.cols)), wd = int(w / uint32_t(M.cols)) + (wv != v);
+      if (wv == S.n || wd == 0) continue;
+      C<L> x = val_get<L>(M.tab, wv);
+      int ex = 0;
+      val_norm(x, ex);
+      r = c_mul(r, c_pow(x, wd));
+      e += wd * ex;
+      val_norm(r, e);
     }
-  return c_mul_d(r, double(d));
+  return bl_ldexp(c_mul_d(r, double(d)), e);
 }
 
 // Column `col`'s sum over a slice by the calling lane and its Q - 1
@@ -588,14 +606,14 @@ __device__ __forceinline__ C<L> val_column(const ValView& S, const ValLds<L>& M,
 }
 
 // the same by products of all factors
-template <int L, bool SMALL>
+template <int L>
 __device__ __forceinline__ C<L> val_column_direct(const ValView& S, const ValLds<L>& M, const ValBlock& blk, uint32_t e0,
                                                   uint32_t e1, int col, int lane, bool weighted, const C<L>& weight) {
   const uint32_t* ell = S.ell + lane;
   C<L> J = c_zero<L>();
   for (uint32_t i = e0; i < e1; ++i) {
     const uint32_t r = val_ld(ell, 64 * size_t(i)), t = r & 0xffffu;
-    if (t < blk.nmon) J = c_add(J, val_direct<L, SMALL>(S, M, blk, t, col, int(r >> 16), weighted, weight));
+    if (t < blk.nmon) J = c_add(J, val_direct<L>(S, M, blk, t, col, int(r >> 16), weighted, weight));
   }
   for (int m = 1; m < (1 << S.lgQ); m <<= 1) J = c_add(J, shfl_xor_c(J, m));
   return J;
@@ -604,13 +622,13 @@ __device__ __forceinline__ C<L> val_column_direct(const ValView& S, const ValLds
 // F's share of a block by one wavefront, the same in every lane.  Where the
 // row takes direct products, so does F: a value stored with its zero factors
 // left out is not a term of F beside a factor that is out of range.
-template <int L, bool SMALL>
+template <int L>
 __device__ __forceinline__ C<L> val_f(const ValView& S, const ValLds<L>& M, const ValBlock& blk, int lane, bool zero,
                                       bool direct) {
   constexpr int NL = limbs_of(L);
   C<L> f = c_zero<L>();
   if (direct) {
-    for (uint32_t t = lane; t < blk.nmon; t += 64) f = c_add(f, val_direct<L, SMALL>(S, M, blk, t, -1, 1, false, c_one<L>()));
+    for (uint32_t t = lane; t < blk.nmon; t += 64) f = c_add(f, val_direct<L>(S, M, blk, t, -1, 1, false, c_one<L>()));
   } else {
     ValSum<NL> re{}, im{};
     for (uint32_t t = lane; t < blk.nmon; t += 64) {
@@ -663,7 +681,7 @@ __device__ __forceinline__ void val_row(const ValView& S, const ValLds<L>& M, co
     __syncthreads();
     const bool direct = direct0 || val_uniform(M.flag[1]) != 0;
     if (MODE != MODE_ADJ && w == nw - 1) {
-      const C<L> f = val_f<L, SMALL>(S, M, blk, lane, zero, direct);
+      const C<L> f = val_f<L>(S, M, blk, lane, zero, direct);
       F = b == b0 ? f : c_add(F, f);
     }
     if (MODE != MODE_FONLY) {
@@ -679,7 +697,7 @@ __device__ __forceinline__ void val_row(const ValView& S, const ValLds<L>& M, co
         }
         C<L> J;
         if (direct) {
-          J = val_column_direct<L, SMALL>(S, M, blk, pre.e0, pre.e1, pre.col, lane, weighted, weight);
+          J = val_column_direct<L>(S, M, blk, pre.e0, pre.e1, pre.col, lane, weighted, weight);
         } else if (zero) {
           J = val_column<L, true, SMALL>(S, M, blk, pre.e0, pre.e1, pre.col, lane, pre.el);
         } else {

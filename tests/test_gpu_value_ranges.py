@@ -87,6 +87,26 @@ def test_zero_times_nonfinite(pe, L, n, bad):
     assert np.array_equal(ok(J), ok(Jw))
 
 
+# |x|, |coefficient|, as powers of two: the product of four variables is in range, the value is not
+TINY = [(1, -180, -350), (2, -180, -350), (4, -170, -250)]
+
+
+@pytest.mark.parametrize("L,ex,ec", TINY)
+def test_tiny_coefficients(pe, L, ex, ec):
+    """Values that underflow where the derivatives are normal numbers; rows 1 and 2 hold one such monomial and none.
+    J only: the terms of F themselves are not representable."""
+    n, m = 24, 600
+    s = uniform((221, L), L, n, 3, m, lambda rng, p, i: rng.choice(12, size=4, replace=False) + 12 * (i & 1))
+    s.coef[:, :, :m] *= 2.0**ec
+    s.coef[:, :, m + 8] *= 2.0**ec
+    x = V.points((222, L), 1, n, L, False)
+    x[:, :, :, :12] *= 2.0**ex
+    s.coef[:, :, 1:m:2] *= 2.0**(4 * ex - ec)  # the odd monomials of row 0 are as small, by their coefficients
+    _, J = V.evaluate(pe, s, x, False)
+    _, eJ = U.max_errors_rows(s, x[0], np.zeros_like(J[0, :, :, :, 0]), J[0], range(3), parallel=False)
+    assert eJ <= U.tolerance(s), (eJ, U.tolerance(s))
+
+
 def check_adjoint(s, x, v, g, cols):
     exact = O.adjoint_columns(s, x, v, cols)
     Sc = O.abs_sums_columns(s, x, cols)
@@ -94,6 +114,23 @@ def check_adjoint(s, x, v, g, cols):
     for j in cols:
         scale = sum(q * av[p] for p, q in Sc[j].items())
         assert O.rel_error(g[0, :, j], g[1, :, j], exact[j], scale) <= 3 * U.tolerance(s), j
+
+
+@pytest.mark.parametrize("L,ex,ev", TINY)
+def test_tiny_weights(pe, L, ex, ev):
+    """The same through the adjoint's weights."""
+    import torch
+    n, m = 24, 600
+    s = uniform((231, L), L, n, 3, m, lambda rng, p, i: rng.choice(12, size=4, replace=False) + 12 * (p == 2))
+    x = V.points((232, L), 1, n, L, False)
+    x[:, :, :, :12] *= 2.0**ex
+    v = synth.unit_circle_points(synth.rng_for((233, L)), 1, 3, L)
+    v[..., :2] *= 2.0**ev
+    S = pe.System.from_sparse(s)
+    g = S.adjoint(U.to_device(x), U.to_device(v)).cpu().numpy()
+    torch.cuda.synchronize()
+    S.close()
+    check_adjoint(s, x[0], v[0], g[0], [0, 5, 11, 12, 23])
 
 
 @pytest.mark.parametrize("L", [1, 2, 4])
