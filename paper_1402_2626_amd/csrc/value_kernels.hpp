@@ -15,11 +15,13 @@
 // zero factors, and their count decides (no zero: as above; one zero variable
 // of exponent 1: the value is the partial derivative with respect to that
 // variable; otherwise the monomial contributes nothing).  Points with values
-// outside 2^-300 .. 2^300 (2^(900 / emax) for large exponents), infinities or
-// NaN, and rows in which a product of variables or a value (with its
-// coefficient and weight) leaves 2^-750 .. 2^900 (below, a quad double's last
-// limbs would underflow), form every partial derivative and every term of F as
-// its own product instead (val_direct), in the same kernel.
+// outside 2^-300 .. 2^300 (for large exponents 2^(-750 / emax) .. 2^(900 / emax)),
+// infinities or NaN, and rows in which a product of variables or a value (with
+// its coefficient and weight) leaves 2^-750 .. 2^900 (below, a quad double's
+// last limbs would underflow), form every partial derivative and every term of
+// F as its own product instead (val_direct), in the same kernel.  The products
+// on the way to a value are tested where the sizes of the variables allow them
+// to leave the range (val_ranges).
 //
 // A COPY of VW threads (a multiple of 64) evaluates rows at one point:
 //   1. powers x_v^1 .. x_v^emax of every variable into LDS (and 1 / x_v, by
@@ -57,6 +59,7 @@ struct ValView {
   int n, N, emax;
   int tab;  // powers in the table: emax, or 1 (higher ones formed per factor)
   int inv;  // reciprocals behind them, or formed per column
+  int safe;  // no product of a monomial's factors leaves the range while all |x_v| are in 2^-safe .. 2^(safe - 1); 0: none is safe
   int lgQ, slices, max_mon;
   int max_units;
   int lgvw;   // log2 of the threads of a copy
@@ -160,7 +163,7 @@ struct ValLds {
   double* val;    // [max_mon + 1]
   double* sum;    // [n]
   uint8_t* zeros;  // [max_mon]
-  int* flag;      // [0], of the point: 1 a zero variable, 2 direct products; [1], of the row: direct products
+  int* flag;      // [0], of the point: 1 a zero variable, 2 direct products, 4 ranges to be tested; [1], of the row: direct products
   int cols;
 };
 
@@ -249,8 +252,9 @@ __device__ __forceinline__ C<L> val_first_x(const ValView& S, const double* __re
 template <int L>
 __device__ __forceinline__ void val_table(const ValView& S, const ValLds<L>& M, const double* __restrict__ xpt, int lv,
                                           int VW, const C<L>& x0) {
-  const double big = __builtin_ldexp(1.0, min(300, 900 / S.emax)), small = 1.0 / big;
-  int f = 0;
+  const double big = __builtin_ldexp(1.0, min(300, 900 / S.emax)), small = __builtin_ldexp(1.0, -min(300, 750 / S.emax));
+  const double lo = __builtin_ldexp(1.0, -S.safe), hi = __builtin_ldexp(0.5, S.safe);
+  int f = S.safe == 0 ? 4 : 0;
   for (int v = lv; v <= S.n; v += VW) {
     const C<L> x = v == lv ? x0 : (v < S.n ? load_planar<L>(xpt, S.n, v) : c_one<L>());
     C<L> p = x;
@@ -261,8 +265,8 @@ __device__ __forceinline__ void val_table(const ValView& S, const ValLds<L>& M, 
     const double mag = val_mag(x);
     if (mag == 0.0)
       f |= 1;
-    else if (!(mag >= small && mag <= big))
-      f |= 2;
+    else if (!(mag >= lo && mag <= hi))
+      f |= mag >= small && mag <= big ? 4 : 2;
     if (val_nan(x)) f |= 2;
   }
   if (f) atomicOr(M.flag, f);
@@ -436,6 +440,32 @@ __device__ __forceinline__ void val_unit(const ValView& S, const ValLds<L>& M, c
   }
 }
 
+// Whether some product of factors of a unit's monomials, in whatever order,
+// can leave 2^-750 .. 2^900: one that leaves it and comes back has lost its last
+// limbs.  By the sums of the factors' negative and positive exponents, apart
+// from the products so that those keep their registers (tested product by
+// product, a launch of one row per CU took 14.3 us in place of 14.15); only for
+// points whose variables are not near 1 (val_table).
+template <int L, bool FULL>
+__device__ __forceinline__ void val_ranges(const ValView& S, const ValLds<L>& M, const ValUnit& u, int lane) {
+  int lo = 0, hi = 0;
+#pragma unroll 1
+  for (int i = 0; i < int(u.seg); ++i) {
+    const uint32_t r = val_ld(S.rec + u.base + lane, 64 * i);
+    const uint32_t e = FULL ? 0 : r / uint32_t(M.cols);
+    const double mag = val_mag(val_get<L>(M.tab, int(r - e * uint32_t(M.cols))));
+    if (mag == 0.0) continue;
+    const int k = bl_exp(mag) - 1023;  // |factor| in 2^k .. 2^(k + 3/2), of its first power
+    lo += min(k, 0) * int(e + 1);
+    hi += max(2 * k + 3, 0) * int(e + 1);
+  }
+  for (int m = 1; m < 1 << u.lgs; m <<= 1) {
+    lo += __shfl_xor(lo, m);
+    hi += __shfl_xor(hi, m);
+  }
+  if (lo < -750 || hi > 2 * 900) M.flag[1] = 1;
+}
+
 // ------------------------------------------------------------------ column sums
 
 // running sum of d V: the terms go into error-free cascades (double: one
@@ -524,10 +554,12 @@ __device__ __forceinline__ void val_norm(C<L>& r, int& e) {
 // partial derivative of monomial t with respect to column v (exponent d), or
 // for v < 0 its value (d = 1), every factor in turn: the definition, for points
 // the division does not suit.  The product is kept as r 2^e, so that no order
-// of the factors leaves the range on the way to a result within it.
+// of the factors leaves the range on the way to a result within it.  wt: the
+// row's weight v_p (planes N apart), whose conjugate multiplies the product, or
+// null; read here, so that the common path need not keep it.
 template <int L>
 __device__ C<L> val_direct(const ValView& S, const ValLds<L>& M, const ValBlock& blk, uint32_t t, int v, int d,
-                           bool weighted, C<L> weight) {
+                           const double* wt) {
   uint32_t u = blk.unit0;
   while (u + 1 < blk.unit1 && val_ld(S.unit, u + 1).mon <= t) ++u;
   const ValUnit U = val_ld(S.unit, u);
@@ -535,7 +567,13 @@ __device__ C<L> val_direct(const ValView& S, const ValLds<L>& M, const ValBlock&
   int e = 0;
   C<L> r = val_ld_coef<L>(S.mcoef + size_t(blk.mon0 + t) * width_of(L));
   val_norm(r, e);
-  if (weighted) {
+  if (wt) {
+    C<L> weight;
+#pragma unroll
+    for (int l = 0; l < limbs_of(L); ++l) {
+      weight.re.x[l] = val_ld(wt, size_t(l) * S.N);
+      if constexpr (!is_real(L)) weight.im.x[l] = -val_ld(wt, size_t(limbs_of(L) + l) * S.N);
+    }
     val_norm(weight, e);
     r = c_mul(r, weight);
     val_norm(r, e);
@@ -608,12 +646,12 @@ __device__ __forceinline__ C<L> val_column(const ValView& S, const ValLds<L>& M,
 // the same by products of all factors
 template <int L>
 __device__ __forceinline__ C<L> val_column_direct(const ValView& S, const ValLds<L>& M, const ValBlock& blk, uint32_t e0,
-                                                  uint32_t e1, int col, int lane, bool weighted, const C<L>& weight) {
+                                                  uint32_t e1, int col, int lane, const double* wt) {
   const uint32_t* ell = S.ell + lane;
   C<L> J = c_zero<L>();
   for (uint32_t i = e0; i < e1; ++i) {
     const uint32_t r = val_ld(ell, 64 * size_t(i)), t = r & 0xffffu;
-    if (t < blk.nmon) J = c_add(J, val_direct<L>(S, M, blk, t, col, int(r >> 16), weighted, weight));
+    if (t < blk.nmon) J = c_add(J, val_direct<L>(S, M, blk, t, col, int(r >> 16), wt));
   }
   for (int m = 1; m < (1 << S.lgQ); m <<= 1) J = c_add(J, shfl_xor_c(J, m));
   return J;
@@ -627,8 +665,8 @@ __device__ __forceinline__ C<L> val_f(const ValView& S, const ValLds<L>& M, cons
                                       bool direct) {
   constexpr int NL = limbs_of(L);
   C<L> f = c_zero<L>();
-  if (direct) {
-    for (uint32_t t = lane; t < blk.nmon; t += 64) f = c_add(f, val_direct<L>(S, M, blk, t, -1, 1, false, c_one<L>()));
+  if (__builtin_expect(direct, 0)) {
+    for (uint32_t t = lane; t < blk.nmon; t += 64) f = c_add(f, val_direct<L>(S, M, blk, t, -1, 1, nullptr));
   } else {
     ValSum<NL> re{}, im{};
     for (uint32_t t = lane; t < blk.nmon; t += 64) {
@@ -652,7 +690,8 @@ __device__ __forceinline__ C<L> val_f(const ValView& S, const ValLds<L>& M, cons
 // forms the reciprocals.
 template <int L, int MODE, bool SMALL>
 __device__ __forceinline__ void val_row(const ValView& S, const ValLds<L>& M, const OutView& O, int pt, int p, int lv,
-                                        int VW, bool live, bool inv, const C<L>& weight, ValPre<L>& pre) {
+                                        int VW, bool live, bool inv, const C<L>& weight, const double* wt,
+                                        ValPre<L>& pre) {
   const int lane = lv & 63, w = val_uniform(lv >> 6), nw = VW >> 6;
   const uint32_t b0 = S.multi ? val_ld(S.row_block, p) : uint32_t(p), b1 = S.multi ? val_ld(S.row_block, p + 1) : uint32_t(p) + 1;
   constexpr bool weighted = MODE == MODE_ADJ;
@@ -661,6 +700,9 @@ __device__ __forceinline__ void val_row(const ValView& S, const ValLds<L>& M, co
   const bool direct0 = (f0 & 2) != 0, zero = (f0 & 1) != 0 && !direct0;
   for (uint32_t b = b0; b < b1; ++b) {
     const ValBlock blk = b == b0 ? pre.blk : val_block(S, b);
+    if (__builtin_expect((f0 & 6) == 4, 0))
+      for (uint32_t u = blk.unit0 + w; u < blk.unit1; u += nw)
+        val_ranges<L, !SMALL>(S, M, val_unit_of(S, blk, u), lane);
     for (uint32_t u = blk.unit0 + w; u < blk.unit1; u += nw) {
       const bool first = b == b0 && u == blk.unit0 + w;
       if (!first) {
@@ -670,7 +712,7 @@ __device__ __forceinline__ void val_row(const ValView& S, const ValLds<L>& M, co
       if (SMALL && S.tab < S.emax) {
         // the forms with zero counts hold for every point
         val_unit<L, true, false>(S, M, pre.u, lane, pre.r, pre.cf, direct0, weighted, weight);
-      } else if (zero) {
+      } else if (__builtin_expect(zero, 0)) {
         val_unit<L, true, true>(S, M, pre.u, lane, pre.r, pre.cf, direct0, weighted, weight);
       } else {
         val_unit<L, false, true>(S, M, pre.u, lane, pre.r, pre.cf, direct0, weighted, weight);
@@ -696,9 +738,9 @@ __device__ __forceinline__ void val_row(const ValView& S, const ValLds<L>& M, co
           val_entries<L>(S, blk, pre.e0, pre.e1, lane, pre.el);
         }
         C<L> J;
-        if (direct) {
-          J = val_column_direct<L>(S, M, blk, pre.e0, pre.e1, pre.col, lane, weighted, weight);
-        } else if (zero) {
+        if (__builtin_expect(direct, 0)) {
+          J = val_column_direct<L>(S, M, blk, pre.e0, pre.e1, pre.col, lane, wt);
+        } else if (__builtin_expect(zero, 0)) {
           J = val_column<L, true, SMALL>(S, M, blk, pre.e0, pre.e1, pre.col, lane, pre.el);
         } else {
           J = val_column<L, false, SMALL>(S, M, blk, pre.e0, pre.e1, pre.col, lane, pre.el);
@@ -762,7 +804,7 @@ __global__ __launch_bounds__(kValThreads, limbs_of(L) == 4 ? 2 : 4) void val_row
       M.flag[1] = 0;
     }
     __syncthreads();
-    val_row<L, MODE, SMALL>(S, M, O, pt, p, lv, VW, in, r == 0, c_one<L>(), pre);
+    val_row<L, MODE, SMALL>(S, M, O, pt, p, lv, VW, in, r == 0, c_one<L>(), nullptr, pre);
   }
 }
 
@@ -793,7 +835,7 @@ __global__ __launch_bounds__(kValThreads, limbs_of(L) == 4 ? 2 : 4) void val_adj
       M.flag[1] = 0;
     }
     __syncthreads();
-    val_row<L, MODE_ADJ, SMALL>(S, M, O, 0, p, lv, VW, true, p == gi * gsize, weight, pre);
+    val_row<L, MODE_ADJ, SMALL>(S, M, O, 0, p, lv, VW, true, p == gi * gsize, weight, v + pt * v_pt + p, pre);
   }
   double* out = part + size_t(pt * NG + gi) * width_of(L) * S.n;
   for (int c = lv; c < S.n; c += VW) store_planar(out, S.n, c, val_get<L>(M.sum, c));
@@ -858,7 +900,7 @@ __global__ __launch_bounds__(kValThreads, limbs_of(L) == 4 ? 2 : 4) void val_bat
       __syncthreads();
       val_table<L>(S, M, xpt, lv, VW, x0);
       __syncthreads();
-      val_row<L, MODE, SMALL>(S, M, O, pt, p, lv, VW, live, true, c_one<L>(), pre);
+      val_row<L, MODE, SMALL>(S, M, O, pt, p, lv, VW, live, true, c_one<L>(), nullptr, pre);
     }
   }
 }

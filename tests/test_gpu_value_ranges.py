@@ -151,3 +151,20 @@ def test_nonfinite_weight(pe, L, bad):
     assert np.isfinite(g[:, :, 20:]).all()
     v[0, :, :, 2] = 0.0
     check_adjoint(s, x[0], v[0], g, [20, 31, 39])
+
+
+@pytest.mark.parametrize("L", [1, 2, 4])
+@pytest.mark.parametrize("lanes", [1, 2])
+def test_partial_products_out_of_range(pe, L, lanes):
+    """Factors whose product is near 1 while the product of a lane's first four, or of all a lane has, is near 2^-1000."""
+    n, m = 24, 600
+    if lanes == 1:
+        pick = lambda rng, p, i: np.concatenate([rng.choice(12, 4, replace=False), 12 + rng.choice(12, 4, replace=False)])  # noqa: E731
+        lift = np.where(np.arange(n) < 12, 2.0**-250, 2.0**250)
+    else:
+        pick = lambda rng, p, i: np.arange(n)  # noqa: E731
+        lift = np.where(np.arange(n) % 2 == 0, 2.0**-83, 2.0**83)
+    s = uniform((251, L), L, n, 3, m, pick)
+    x = V.points((252, L), 1, n, L, False) * lift
+    F, J = V.evaluate(pe, s, x, False)
+    V.check(s, x[0], F[0], J[0], range(3))
