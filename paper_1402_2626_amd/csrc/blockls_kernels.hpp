@@ -73,6 +73,26 @@ constexpr int kBlRows = 64;     // rows of a chunk: the K of a matrix instructio
 constexpr int kBlBs = 256;      // rows of a back-substitution block
 constexpr int kBlMaxSplit = 4;  // row splits of a contraction
 constexpr int kBlGramSplit = 16;  // and of the Gram matrix's
+// Row splits of a problem's Gram matrix (per panel) and of its contraction with
+// `ncols` real columns in tiles of NT x 16: by the problem's own size, never by
+// how many problems a launch holds, since the partial sums are rounded and the
+// results of a problem are to be the same in every company.  As many as give a
+// single problem two workgroups on every CU; 96 problems of 32 .. 256 rows in a
+// launch would do with fewer (a batched step takes 1.87 ms against 1.78 with
+// splits by the launch), 1 to 64 problems of 128 .. 256 rows lose or gain up to
+// 3 %.
+__host__ __device__ inline int bl_chunks(int N) { return (N + kBlRows - 1) / kBlRows; }
+__host__ __device__ inline int bl_gram_splits(int N) {
+  const int nc = bl_chunks(N);
+  return nc < kBlGramSplit ? nc : kBlGramSplit;
+}
+template <int L>
+__host__ __device__ inline int bl_dot_splits(int N, int ncols) {
+  const int tiles = (ncols + 16 * Bl<L>::NT - 1) / (16 * Bl<L>::NT), nc = bl_chunks(N);
+  const int want = (512 + tiles - 1) / tiles, most = nc < kBlMaxSplit ? nc : kBlMaxSplit;
+  return want < most ? want : most;
+}
+
 constexpr int kExpOne = 1022;   // biased exponent field E of v: |v| < 2^(E - 1022)
 
 // the problems of one launch group; per-slot strides in bytes
@@ -494,8 +514,7 @@ __device__ __forceinline__ void bl_store4(double* dst, int64_t plane, int row, i
 // tiles of 16.  Row ranges are summed by bl_chol_kernel.  S is [split][column]
 // [B] numbers of the factor's level.  grid (4 / NT, splits, slots), 256 threads
 template <int L>
-__global__ __launch_bounds__(256, limbs_of(L) == 4 ? 1 : 2) void bl_gram_kernel(BlView V, int panel, int cur,
-                                                                                int nsplit) {
+__global__ __launch_bounds__(256, limbs_of(L) == 4 ? 1 : 2) void bl_gram_kernel(BlView V, int panel, int cur) {
   using K = Bl<L>;
   constexpr int NL = K::NL, ND = K::ND, NT = K::NT, CX = K::CX;
   extern __shared__ double lds[];
@@ -507,7 +526,7 @@ __global__ __launch_bounds__(256, limbs_of(L) == 4 ? 1 : 2) void bl_gram_kernel(
   const int bcur = min(K::B, p.n - k0);
   const int rc0 = blockIdx.x * NT * 16;
   const int NC = (p.N + kBlRows - 1) / kBlRows;
-  const int ns = min(nsplit, NC), split = blockIdx.y;
+  const int ns = bl_gram_splits(p.N), split = blockIdx.y;
   if (rc0 >= bcur * CX || split >= ns) return;
   const int per = (NC + ns - 1) / ns;
   const int ch0 = split * per, ch1 = min(NC, ch0 + per);
@@ -570,8 +589,7 @@ __host__ __device__ inline size_t bl_gram_lds() {
 // summed by bl_fin_kernel.  S is [split][column][B] numbers.  grid (column
 // tiles, splits, slots), 256 threads
 template <int L>
-__global__ __launch_bounds__(256, limbs_of(L) == 4 ? 1 : 2) void bl_dot_kernel(BlView V, int panel, int cur,
-                                                                               int nsplit) {
+__global__ __launch_bounds__(256, limbs_of(L) == 4 ? 1 : 2) void bl_dot_kernel(BlView V, int panel, int cur) {
   using K = Bl<L>;
   constexpr int NL = K::NL, ND = K::ND, NT = K::NT, CX = K::CX;
   __shared__ bl_v4i dig[NT * ND * 64];
@@ -583,7 +601,7 @@ __global__ __launch_bounds__(256, limbs_of(L) == 4 ? 1 : 2) void bl_dot_kernel(B
   const int ncols = (p.n + 1 - k0) * CX;  // real columns
   const int rc0 = blockIdx.x * NT * 16;
   const int NC = (p.N + kBlRows - 1) / kBlRows;
-  const int ns = min(nsplit, NC), split = blockIdx.y;
+  const int ns = bl_dot_splits<L>(p.N, ncols), split = blockIdx.y;
   if (rc0 >= ncols || split >= ns) return;
   const int per = (NC + ns - 1) / ns;
   const int ch0 = split * per, ch1 = min(NC, ch0 + per);
@@ -766,7 +784,7 @@ __device__ bool bl_mgs_sweep(const BlProb& p, double* Wp, int k0, int bcur, doub
 // E above the square root of the level's roundoff.  One workgroup per
 // problem: it is bound by the chain of B pivots.
 template <int L>
-__global__ __launch_bounds__(BlChol<L>::T) void bl_chol_kernel(BlView V, int panel, int cur, int nsplit) {
+__global__ __launch_bounds__(BlChol<L>::T) void bl_chol_kernel(BlView V, int panel, int cur) {
   using K = Bl<L>;
   constexpr int LC = K::LC, NC_ = limbs_of(LC), WC = K::WC, B = K::B, NL = K::NL;
   constexpr int T = BlChol<L>::T, EPT = BlChol<L>::EPT;
@@ -787,8 +805,7 @@ __global__ __launch_bounds__(BlChol<L>::T) void bl_chol_kernel(BlView V, int pan
   double* frow = norm0 + B;           // [B] numbers (quad double)
   int* ex = reinterpret_cast<int*>(frow + B * WC);  // [B] column exponents
   (void)frow;
-  const int nch = (p.N + kBlRows - 1) / kBlRows;
-  const int ns = min(nsplit, nch);
+  const int ns = bl_gram_splits(p.N);
   const int* ce = bl_at<int>(p, V.oCe) + cur * V.nmax;
   if (tid < B) ex[tid] = tid < bcur ? ce[k0 + tid] - kExpOne : 0;
   // entries in row order, so that whole wavefronts fall idle as rows finish;
@@ -1143,7 +1160,7 @@ __host__ __device__ inline size_t bl_solve_lds() {
 // 2^-58, so its products need no more than double arithmetic.  grid (column
 // groups, slots), 256 threads: B lanes per column
 template <int L>
-__global__ __launch_bounds__(256) void bl_fin_kernel(BlView V, int panel, int cur, int nsplit) {
+__global__ __launch_bounds__(256) void bl_fin_kernel(BlView V, int panel, int cur) {
   using K = Bl<L>;
   constexpr int B = K::B, NL = K::NL, ND = K::ND, NW = K::NW, CX = K::CX, W = K::W, CPW = 256 / B;
   __shared__ double E[B * B * CX];    // [i][j]
@@ -1155,7 +1172,7 @@ __global__ __launch_bounds__(256) void bl_fin_kernel(BlView V, int panel, int cu
   const int bcur = min(B, p.n - k0);
   const int c0 = blockIdx.x * CPW;
   if (k0 + c0 > p.n) return;
-  const int ns = min(nsplit, (p.N + kBlRows - 1) / kBlRows);
+  const int ns = bl_dot_splits<L>(p.N, (p.n + 1 - k0) * CX);
   const int tid = threadIdx.x;
   auto sum = [&](int c, int i) {
     return bl_sum_splits<L>(p.base + V.oS + (size_t(c) * B + i) * W * 8, V.s_split, ns);

@@ -440,22 +440,20 @@ hipError_t launch_blockls(const BlView& V, int slots, int Nm, int nm, hipStream_
   // fit on a CU, and one round of them leaves no tail (double double, n =
   // 2048: 60 us a panel against 68 with three per CU and 74 with one)
   constexpr int kUpdate = limbs_of(L) == 4 ? 256 : 512;
-  // enough workgroups for two on every CU, within the split limits
-  auto splits = [&](int tiles, int most) { return std::max(1, std::min({most, NC, (512 + tiles * slots - 1) / (tiles * slots)})); };
+  // (row splits: each problem has its own, and workgroups beyond them end)
+  const unsigned gs = unsigned(bl_gram_splits(Nm)), ds = unsigned(std::min(NC, kBlMaxSplit));
   for (int panel = 0, k0 = 0; k0 < nm; ++panel, k0 += K::B) {
     const int cur = panel & 1;
     const int real_cols = (nm + 1 - k0) * K::CX;
-    const int gt = 64 / (16 * K::NT), gs = splits(gt, kBlGramSplit);
-    hipLaunchKernelGGL(bl_gram_kernel<L>, dim3(unsigned(gt), unsigned(gs), S), dim3(256), gram_lds, st, V, panel, cur, gs);
-    hipLaunchKernelGGL(bl_chol_kernel<L>, dim3(S), dim3(BlChol<L>::T), chol_lds, st, V, panel, cur, gs);
+    hipLaunchKernelGGL(bl_gram_kernel<L>, dim3(64 / (16 * K::NT), gs, S), dim3(256), gram_lds, st, V, panel, cur);
+    hipLaunchKernelGGL(bl_chol_kernel<L>, dim3(S), dim3(BlChol<L>::T), chol_lds, st, V, panel, cur);
     hipLaunchKernelGGL(bl_solve_kernel<L>, dim3(unsigned(NC * kBlRows / (4 * bl_solve_rows<L>())), S), dim3(256), solve_lds, st, V,
                        panel, cur);
-    const int dt = (real_cols + 16 * K::NT - 1) / (16 * K::NT), ds = splits(dt, kBlMaxSplit);
-    hipLaunchKernelGGL(bl_dot_kernel<L>, dim3(unsigned(dt), unsigned(ds), S), dim3(256), 0, st, V, panel, cur,
-                       ds);
+    const int dt = (real_cols + 16 * K::NT - 1) / (16 * K::NT);
+    hipLaunchKernelGGL(bl_dot_kernel<L>, dim3(unsigned(dt), ds, S), dim3(256), 0, st, V, panel, cur);
     const int cpw = 256 / K::B;
     hipLaunchKernelGGL(bl_fin_kernel<L>, dim3(unsigned((nm + 1 - k0 + cpw - 1) / cpw), S), dim3(256), 0, st, V, panel,
-                       cur, ds);
+                       cur);
     if (k0 + K::B < nm) {
       const int tiles = (real_cols + 15) / 16 - 4;
       const int groups = std::max(1, std::min(tiles, (kUpdate + NC * slots - 1) / (NC * slots)));
