@@ -116,12 +116,21 @@ pe_status pe_system_destroy(pe_system* sys);
 
 /* Sizes of a loaded system: info[0] = level (with PE_REAL if real), [1] = n, [2] = N, [3] = M,
  * [4] = nnz, [5] = largest exponent, [6] = largest monomial size k,
- * [7] = device bytes held, [8] = chunks per workgroup of the evaluation
- * launch, [9] = LDS bytes per evaluation workgroup, [10] = segment length
- * (variables per lane). */
+ * [7] = device bytes held, [8] = chunks per workgroup of the launch shape,
+ * [9] = LDS bytes of a workgroup of that shape, [10] = segment length
+ * (variables per lane).  Of a system that pe_eval evaluates through monomial
+ * values (see pe_system_set_shape), [8] and [9] do not describe pe_eval's
+ * launch. */
 pe_status pe_system_info(const pe_system* sys, int64_t info[11]);
 
-/* Set the evaluation launch shape.  A monomial of k variables is handled by
+/* Set the launch shape of the kernels that work on chunks: pe_eval, the
+ * adjoint and batches of systems that are not evaluated through monomial
+ * values (rows that touch a variable less than twice on average, monomials of
+ * fewer than four variables on average, tables beyond a workgroup's LDS; in
+ * double, real double and real double double also rows of one chunk at the
+ * default segment length), and pe_eval_terms of every system.  Whether a system
+ * is evaluated through values does not depend on the shape.
+ * A monomial of k variables is handled by
  * s lanes (s the smallest power of two with s * segment >= k); the
  * monomials of a row are cut into chunks of 256 lanes, and a workgroup of
  * chunks_per_workgroup * 256 threads works on that many chunks of a row at
@@ -324,8 +333,9 @@ pe_status pe_lstsq(int32_t level, int32_t P, int32_t N, int32_t n, const double*
 /* ------------------------------------------------------------------ tuning
  * Time the candidate launch shapes for this system at P points on the
  * current device and keep the fastest for later pe_eval calls (this call
- * allocates and synchronises).  The choice is recorded in the plan cache
- * file if one is set. */
+ * allocates and synchronises).  A system that pe_eval evaluates through
+ * monomial values (pe_system_set_shape) keeps its shape: pe_eval does not
+ * depend on it.  The choice is recorded in the plan cache file if one is set. */
 pe_status pe_autotune(pe_system* sys, int32_t P, void* stream);
 
 /* Use `path` (NULL to disable) as a plan cache: a text file with one line

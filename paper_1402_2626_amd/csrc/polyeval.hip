@@ -144,8 +144,9 @@ struct pe_system {
   bool use_val = false;      // F and J
   bool use_val_adj = false;  // the adjoint (its column sums take more LDS)
   ValView val{};
-  std::vector<void*> allocs;
-  size_t device_bytes = 0;
+  int default_chunks = -1;  // most chunks of a row at the default segment length (val_suits)
+  std::vector<void*> allocs, val_allocs;  // of the chunks; of the value layout
+  size_t device_bytes = 0, val_bytes = 0;
   // batches that hold a copy of this system's device view; while any is
   // alive the system may not be repacked or destroyed
   mutable std::atomic<int> batch_refs{0};
@@ -216,8 +217,9 @@ hipError_t dispatch_adj(const pe_system* sys, int P, const double* x, const doub
   return hipErrorInvalidValue;
 }
 
+// v to the device, its memory and size noted in allocs and total
 template <typename T>
-pe_status upload(pe_system* sys, const std::vector<T>& v, const T*& dst, hipStream_t st) {
+pe_status upload_to(std::vector<void*>& allocs, size_t& total, const std::vector<T>& v, const T*& dst, hipStream_t st) {
   if (v.empty()) {
     dst = nullptr;
     return PE_OK;
@@ -225,11 +227,16 @@ pe_status upload(pe_system* sys, const std::vector<T>& v, const T*& dst, hipStre
   void* p = nullptr;
   const size_t bytes = v.size() * sizeof(T);
   PE_HIP(hipMalloc(&p, bytes));
-  sys->allocs.push_back(p);
-  sys->device_bytes += bytes;
+  allocs.push_back(p);
+  total += bytes;
   PE_HIP(hipMemcpyAsync(p, v.data(), bytes, hipMemcpyHostToDevice, st));
   dst = static_cast<const T*>(p);
   return PE_OK;
+}
+
+template <typename T>
+pe_status upload(pe_system* sys, const std::vector<T>& v, const T*& dst, hipStream_t st) {
+  return upload_to(sys->allocs, sys->device_bytes, v, dst, st);
 }
 
 // Launch shape for a packed system: G chunks at once (G > 1 needs at least
@@ -303,8 +310,14 @@ int slots_for(int L, int seg) {
   return std::max(kMaxMonomialVars + 1, bytes / (16 * L));
 }
 
-void free_device(pe_system* sys) {
+void free_values(pe_system* sys) {
   sys->use_val = sys->use_val_adj = false;
+  for (void* p : sys->val_allocs) (void)hipFree(p);
+  sys->val_allocs.clear();
+  sys->val_bytes = 0;
+}
+
+void free_device(pe_system* sys) {
   for (void* p : sys->allocs) (void)hipFree(p);
   sys->allocs.clear();
   sys->device_bytes = 0;
@@ -361,7 +374,9 @@ size_t val_lds_limit(const pe_system* sys) { return sys->level == 4 ? val_lds_al
 // chunks besides: their products cost so little that one chunk in registers is
 // ahead when the launch is short (D, n = N = 32, P = 1: 4.9 us against 6.0 in
 // a graph; real D, n = 256, 128 x 16, P = 8: 11.7 against 13.5), while chunks
-// in sequence are not (D, n = 128, 256 x 16, P = 8: 28 us against 18).
+// in sequence are not (D, n = 128, 256 x 16, P = 8: 28 us against 18).  The
+// chunks are those of the default segment length, so that the launch shape does
+// not change the algorithm.
 // Where the table of powers does not fit, x alone does more often: higher
 // powers are then formed factor by factor and reciprocals column by column,
 // and if the sums of several blocks are in the way a block takes a whole row
@@ -378,12 +393,8 @@ bool val_suits(const pe_system* sys, ValPlan& plan) {
   if (H.N == 0 || H.M == 0 || H.n > kTileCols) return false;
   if (H.nnz < 4 * H.M || H.nnz < 2 * int64_t(H.N) * H.n) return false;
   int64_t most = 0;
-  int chunks = 0;
-  for (int p = 0; p < H.N; ++p) {
-    most = std::max(most, sys->in_poly_ptr[p + 1] - sys->in_poly_ptr[p]);
-    chunks = std::max<int>(chunks, H.chunk_ptr[p + 1] - H.chunk_ptr[p]);
-  }
-  if (width_of(sys->code) <= 2 && chunks < 2) return false;
+  for (int p = 0; p < H.N; ++p) most = std::max(most, sys->in_poly_ptr[p + 1] - sys->in_poly_ptr[p]);
+  if (width_of(sys->code) <= 2 && sys->default_chunks < 2) return false;
   if (H.emax > 64) return false;
   const int std_block = val_block_mons(sys->code), row = int(std::min<int64_t>(most, 65534));
   for (const ValPlan p : {ValPlan{H.emax, 1, std_block}, ValPlan{1, 0, std_block}, ValPlan{1, 0, row}}) {
@@ -395,9 +406,28 @@ bool val_suits(const pe_system* sys, ValPlan& plan) {
   return false;
 }
 
+// The packed arrays that the value layout shares with the chunks: monomials
+// come in the same order at every segment length.
+void share_with_values(pe_system* sys) {
+  sys->val.mcoef = sys->view.mcoef;
+  sys->val.row_order = sys->view.row_order;
+}
+
+pe_status upload_value_arrays(pe_system* sys, const PackedValues& PV, hipStream_t hs) {
+  ValView& V = sys->val;
+  auto up = [&](const auto& v, auto& dst) { return upload_to(sys->val_allocs, sys->val_bytes, v, dst, hs); };
+  pe_status e = PE_OK;
+  if ((e = up(PV.block, V.block)) != PE_OK || (e = up(PV.row_block, V.row_block)) != PE_OK ||
+      (e = up(PV.unit, V.unit)) != PE_OK || (e = up(PV.rec, V.rec)) != PE_OK || (e = up(PV.ell, V.ell)) != PE_OK ||
+      (e = up(PV.slice, V.slice)) != PE_OK || (e = up(PV.perm, V.perm)) != PE_OK)
+    return e;
+  PE_HIP(hipStreamSynchronize(hs));
+  return PE_OK;
+}
+
 // Pack and upload the value layout; on success sys->val is complete.
 pe_status upload_values(pe_system* sys, hipStream_t hs) {
-  sys->use_val = sys->use_val_adj = false;
+  free_values(sys);
   ValPlan plan;
   if (!val_suits(sys, plan)) return PE_OK;
   PackedValues PV;
@@ -438,15 +468,9 @@ pe_status upload_values(pe_system* sys, hipStream_t hs) {
   const size_t copy = val_doubles(sys->code, V.n, V.tab + V.inv, V.max_mon, V.multi != 0) * sizeof(double);
   while (vw < kValThreads && size_t(kValThreads / vw) * copy > val_lds_all() / 2) vw *= 2;
   while ((1 << V.lgvw) < vw) ++V.lgvw;
-  V.mcoef = sys->view.mcoef;
-  V.row_order = sys->view.row_order;
-  pe_status e = PE_OK;
-  if ((e = upload(sys, PV.block, V.block, hs)) != PE_OK || (e = upload(sys, PV.row_block, V.row_block, hs)) != PE_OK ||
-      (e = upload(sys, PV.unit, V.unit, hs)) != PE_OK || (e = upload(sys, PV.rec, V.rec, hs)) != PE_OK ||
-      (e = upload(sys, PV.ell, V.ell, hs)) != PE_OK || (e = upload(sys, PV.slice, V.slice, hs)) != PE_OK ||
-      (e = upload(sys, PV.perm, V.perm, hs)) != PE_OK)
-    return e;
-  PE_HIP(hipStreamSynchronize(hs));
+  const pe_status e = upload_value_arrays(sys, PV, hs);
+  if (e != PE_OK) return e;
+  share_with_values(sys);
   sys->use_val = true;
   sys->use_val_adj = val_doubles(sys->code, V.n, V.tab + V.inv, V.max_mon, true) * sizeof(double) <= val_lds_all();
   return PE_OK;
@@ -520,7 +544,15 @@ pe_status pack_and_upload(pe_system* sys, int seg, int force_G, hipStream_t hs) 
   sys->host.occ_orig.shrink_to_fit();
   sys->host.mon_orig.clear();
   sys->host.mon_orig.shrink_to_fit();
-  return upload_values(sys, hs);
+  if (sys->default_chunks < 0) {
+    // the first packing, at the default segment length
+    sys->default_chunks = 0;
+    for (int p = 0; p < P.N; ++p)
+      sys->default_chunks = std::max<int>(sys->default_chunks, P.chunk_ptr[p + 1] - P.chunk_ptr[p]);
+    return upload_values(sys, hs);
+  }
+  share_with_values(sys);
+  return PE_OK;
 }
 
 // ------------------------------------------------------------------ plan cache
@@ -650,6 +682,7 @@ pe_status pe_system_destroy(pe_system* sys) {
   if (!sys) return PE_OK;
   if (sys->batch_refs.load() > 0) return fail(PE_EINVAL, "the system belongs to a live batch; destroy the batch first");
   free_device(sys);
+  free_values(sys);
   if (sys->adj_ws) (void)hipFree(sys->adj_ws);
   delete sys;
   return PE_OK;
@@ -665,7 +698,7 @@ pe_status pe_system_info(const pe_system* sys, int64_t info[11]) {
   info[4] = H.nnz;
   info[5] = H.emax;
   info[6] = H.kmax;
-  info[7] = int64_t(sys->device_bytes);
+  info[7] = int64_t(sys->device_bytes + sys->val_bytes);
   info[8] = sys->plan.G;
   info[9] = int64_t(sys->plan.lds);
   info[10] = sys->plan.seg;
@@ -1608,6 +1641,9 @@ pe_status pe_autotune(pe_system* sys, int32_t P, void* stream) {
   for (int seg : {1, 2, 4, 6, 8, 16})
     for (int G : {1, 2, 4}) {
       if (!shape_compiled(L, seg, G)) continue;
+      // pe_eval of a system evaluated through monomial values is the same
+      // launch at every shape: the present one is kept
+      if (sys->use_val && (seg != best_seg0 || G != best_G0)) continue;
       if (pe_system_set_shape(sys, seg, G, stream) != PE_OK) continue;
       double us = 1e300;
       for (int rep = 0; rep < 3; ++rep) {
