@@ -9,6 +9,7 @@
 #include <cstring>
 #include <fstream>
 #include <mutex>
+#include <new>
 #include <numeric>
 #include <sstream>
 #include <string>
@@ -425,13 +426,19 @@ pe_status upload_value_arrays(pe_system* sys, const PackedValues& PV, hipStream_
   return PE_OK;
 }
 
-// Pack and upload the value layout; on success sys->val is complete.
+// Pack and upload the value layout; on success sys->val is complete.  Without
+// memory for it, on the host or the device, the system is evaluated from its
+// chunks, which are on the device already.
 pe_status upload_values(pe_system* sys, hipStream_t hs) {
   free_values(sys);
   ValPlan plan;
   if (!val_suits(sys, plan)) return PE_OK;
   PackedValues PV;
-  if (!pack_values(stored_input(sys), plan.block, PV)) return PE_OK;
+  try {
+    if (!pack_values(stored_input(sys), plan.block, PV)) return PE_OK;
+  } catch (const std::bad_alloc&) {
+    return PE_OK;
+  }
   ValView& V = sys->val;
   V = ValView{};
   V.n = sys->host.n;
@@ -469,7 +476,15 @@ pe_status upload_values(pe_system* sys, hipStream_t hs) {
   while (vw < kValThreads && size_t(kValThreads / vw) * copy > val_lds_all() / 2) vw *= 2;
   while ((1 << V.lgvw) < vw) ++V.lgvw;
   const pe_status e = upload_value_arrays(sys, PV, hs);
-  if (e != PE_OK) return e;
+  if (e != PE_OK) {
+    (void)hipGetLastError();  // or the next launch would report it
+    free_values(sys);
+    if (e == PE_ENOMEM) {
+      g_last_error.clear();
+      return PE_OK;
+    }
+    return e;
+  }
   share_with_values(sys);
   sys->use_val = true;
   sys->use_val_adj = val_doubles(sys->code, V.n, V.tab + V.inv, V.max_mon, true) * sizeof(double) <= val_lds_all();
