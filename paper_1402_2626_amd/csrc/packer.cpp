@@ -296,6 +296,13 @@ int val_lg_lanes_per_column(int n, int64_t len) {
   return lg;
 }
 
+// A slice is as long as its longest column, 64 lanes wide: a variable that
+// occurs in every monomial of a row of many columns would pad the row to 64 / Q
+// times its entries, in memory and as a chain of that many additions in one
+// wavefront.  More than kValPadding entries per occurrence are refused (1 MB is
+// allowed in any case); sorted columns of similar length take 1.1 to 1.5.
+static constexpr int64_t kValPadding = 4;
+
 bool pack_values(const SysInput& in, int block_mons, PackedValues& out) {
   const int n = in.n_vars, N = in.n_polys;
   if (n > 32768 || block_mons < 1 || block_mons > 65534) return false;
@@ -406,7 +413,7 @@ bool pack_values(const SysInput& in, int block_mons, PackedValues& out) {
         rows += uint32_t(len);
       }
       out.slice.push_back(rows);
-      if (rows > 0xffffffffu / 64) return false;
+      if (rows > 0xffffffffu / 64 || int64_t(rows) * 64 > kValPadding * nnz + (1 << 18)) return false;
       out.ell.resize(size_t(rows) * 64, uint32_t(nm));
       fill.assign(size_t(n), 0);
       const uint32_t* sl = out.slice.data() + blk.slice0;

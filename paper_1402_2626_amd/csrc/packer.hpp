@@ -71,7 +71,8 @@ struct PackedValues {
 int val_lg_lanes_per_column(int n, int64_t len);
 
 // Packs the value layout of a valid system with n <= 32768; blocks of at most
-// `block_mons` monomials (< 65535).  False when an index does not fit.
+// `block_mons` monomials (< 65535).  False when an index does not fit or the
+// column lists would be mostly padding.
 bool pack_values(const SysInput& in, int block_mons, PackedValues& out);
 
 // status codes as in the C ABI
