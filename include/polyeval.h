@@ -262,8 +262,10 @@ pe_status pe_batch_eval(const pe_batch* batch, int32_t points_per_system, const 
  *              256-byte aligned, owned by the caller.
  *   resid_out  device [P][2] doubles: |F(x)|_2 before the step and
  *              |dx|_inf (leading limbs), or NULL.
- * The solve is that of pe_lstsq below; points beyond what 1 GiB of solver
- * workspace holds go through it in groups.
+ * The solve is that of pe_lstsq below (a few unknowns: one wavefront per
+ * point, and a workspace of 16 L n (n + 2) bytes a point beside [J | -F]);
+ * points beyond what 1 GiB of solver workspace holds go through it in groups.
+ * A point's result does not depend on the other points of the call.
  * Requires N >= n (least squares), at most 65535 points, and N <= 4096 for
  * 128 variables or more (fewer variables: two columns of N numbers within a
  * workgroup's LDS, or N <= 4096) (PE_EUNSUPPORTED otherwise).  Enqueues kernels only
@@ -297,7 +299,8 @@ pe_status pe_homotopy_track(const pe_system* sys, int32_t P, double* x_inout, co
                             int32_t corrector_iters, void* workspace, double* resid_out, void* stream);
 
 /* The same for every system of a batch, x in the packed batch layout;
- * resid_out is [S][P][2].  Takes n + 1 <= 1024 and two columns of N numbers
+ * resid_out is [S][P][2].  A batch of systems with a few unknowns each takes
+ * the one-wavefront solve, any other the panels for all its systems.  Takes n + 1 <= 1024 and two columns of N numbers
  * within one workgroup's LDS (PE_EUNSUPPORTED otherwise). */
 size_t pe_batch_newton_workspace_bytes(const pe_batch* batch, int32_t P);
 pe_status pe_batch_newton_step(const pe_batch* batch, int32_t P, double* x_inout, void* workspace,
@@ -305,7 +308,8 @@ pe_status pe_batch_newton_step(const pe_batch* batch, int32_t P, double* x_inout
 
 /* ------------------------------------------------------------------ least squares
  * Solve A x = b in the least-squares sense by Gram-Schmidt on the augmented
- * matrix [A b] = [Q q][R y; 0 z] (Sec. 3, Fig. 4, eq. (2)): right-looking, in
+ * matrix [A b] = [Q q][R y; 0 z] (Sec. 3, Fig. 4, eq. (2)): for a few unknowns
+ * column by column in one wavefront per problem, otherwise right-looking, in
  * panels of 32 (complex) or 64 (real) columns.  A panel is orthonormalised
  * through its Gram matrix (column by column where that is too ill-
  * conditioned) and its projector is taken off the columns behind it; the

@@ -26,6 +26,7 @@ template hipError_t launch_rhs_shift<PE_LEVEL>(double*, int64_t, int64_t, int64_
                                                double, hipStream_t);
 #elif PE_KIND == 4
 template hipError_t launch_blockls<PE_LEVEL>(const BlView&, int, int, int, hipStream_t);
+template hipError_t launch_small_solve<PE_LEVEL>(const BlView&, int, int, hipStream_t);
 #elif PE_KIND == 5
 template hipError_t launch_val_rows<PE_LEVEL>(const ValView&, int, const double*, const OutView&, int, hipStream_t);
 #if PE_LEVEL < 8

@@ -10,6 +10,7 @@
 #include "blockls_kernels.hpp"
 #include "eval_kernels.hpp"
 #include "newton_kernels.hpp"
+#include "smallls_kernels.hpp"
 #include "value_kernels.hpp"
 
 namespace pe {
@@ -108,6 +109,10 @@ constexpr int kLsMaxRows = 4096;  // N limit of the solve beyond 127 unknowns
 
 template <int L>
 hipError_t launch_blockls(const BlView& V, int slots, int Nm, int nm, hipStream_t st);
+
+// The same for small problems (smallls_kernels.hpp), nm < kSmallCols.
+template <int L>
+hipError_t launch_small_solve(const BlView& V, int slots, int Nm, hipStream_t st);
 
 #ifdef PE_LAUNCH_DEFINITIONS
 
@@ -417,6 +422,15 @@ hipError_t launch_rhs_shift(double* W, int64_t w_pt, int64_t plane, int64_t ld, 
   const int64_t tot = int64_t(P) * N;
   hipLaunchKernelGGL(rhs_shift_kernel<L>, dim3(unsigned((tot + 255) / 256)), dim3(256), 0, st, W, w_pt, plane, ld, N, n,
                      P, c, wF, wc);
+  return hipGetLastError();
+}
+
+template <int L>
+hipError_t launch_small_solve(const BlView& V, int slots, int Nm, hipStream_t st) {
+  const size_t lds = small_lds<L>(Nm);
+  const hipError_t e = allow_lds(small_solve_kernel<L>, lds);
+  if (e != hipSuccess) return e;
+  hipLaunchKernelGGL(small_solve_kernel<L>, dim3(unsigned(slots)), dim3(64), lds, st, V);
   return hipGetLastError();
 }
 

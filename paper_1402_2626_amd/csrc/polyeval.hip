@@ -994,46 +994,77 @@ bool newton_large(const pe_system* sys) {
 constexpr size_t kSolveBytes = size_t(1) << 30;
 constexpr int kSolveSlots = 32768;
 
-void bl_layout_for(int code, int N, int n, BlView& V) {
+// Whether a problem of N rows and n unknowns is solved by one wavefront
+// (smallls_kernels.hpp) rather than in panels: up to so many row-unknown
+// products, by the level.  By the size alone, so that a problem has the same
+// bits at every number of points; the wavefront's chain grows with it, the
+// panels' time hardly below 64 rows but with every problem.  A Gauss-Newton step
+// at 1 and at 2048 points, wavefront / panels in us: DD n = 8 51/66 and 145/709,
+// n = 12 88/70 and 252/787, n = 16 137/75 and 381/911; D n = 20 85/65 and 344/677;
+// QD n = 6 202/120 and 633/2961; real DD n = 20 113/80 and 306/991; real D n = 24
+// 100/72 and 269/744; real QD n = 10 200/119 and 636/3116.
+constexpr int small_products(int code) {
+  return code == 1 ? 400 : code == 2 ? 150 : code == 4 ? 36 : code == (PE_REAL | 1) ? 600 : code == (PE_REAL | 2) ? 400 : 100;
+}
+
+bool small_solve(int code, int N, int n) { return int64_t(N) * n <= small_products(code) && n < kSmallCols; }
+
+// keep: the matrix is the caller's (pe_lstsq)
+template <int L>
+void solve_layout_t(int N, int n, bool small, bool keep, BlView& V) {
+  if (small)
+    small_layout<L>(N, n, keep, V);
+  else
+    bl_layout<L>(N, n, V);
+}
+
+void solve_layout(int code, int N, int n, bool small, bool keep, BlView& V) {
   switch (code) {
-    case 1: return bl_layout<1>(N, n, V);
-    case 2: return bl_layout<2>(N, n, V);
-    case 4: return bl_layout<4>(N, n, V);
-    case PE_REAL | 1: return bl_layout<PE_REAL | 1>(N, n, V);
-    case PE_REAL | 2: return bl_layout<PE_REAL | 2>(N, n, V);
-    case PE_REAL | 4: return bl_layout<PE_REAL | 4>(N, n, V);
+    case 1: return solve_layout_t<1>(N, n, small, keep, V);
+    case 2: return solve_layout_t<2>(N, n, small, keep, V);
+    case 4: return solve_layout_t<4>(N, n, small, keep, V);
+    case PE_REAL | 1: return solve_layout_t<PE_REAL | 1>(N, n, small, keep, V);
+    case PE_REAL | 2: return solve_layout_t<PE_REAL | 2>(N, n, small, keep, V);
+    case PE_REAL | 4: return solve_layout_t<PE_REAL | 4>(N, n, small, keep, V);
   }
 }
 
-size_t solve_bytes(int code, int N, int n, int64_t total) {
+size_t solve_bytes(int code, int N, int n, int64_t total, bool small, bool keep) {
   BlView V{};
-  bl_layout_for(code, N, n, V);
+  solve_layout(code, N, n, small, keep, V);
   const int64_t fit = std::max<int64_t>(1, int64_t(kSolveBytes / V.slot));
   return V.slot * size_t(std::min<int64_t>({total, fit, int64_t(kSolveSlots)}));
 }
 
-hipError_t dispatch_solve(int code, const BlView& V, int slots, int N, int n, hipStream_t st) {
+template <int L>
+hipError_t dispatch_solve_t(const BlView& V, int slots, int N, int n, bool small, hipStream_t st) {
+  return small ? launch_small_solve<L>(V, slots, N, st) : launch_blockls<L>(V, slots, N, n, st);
+}
+
+hipError_t dispatch_solve(int code, const BlView& V, int slots, int N, int n, bool small, hipStream_t st) {
   switch (code) {
-    case 1: return launch_blockls<1>(V, slots, N, n, st);
-    case 2: return launch_blockls<2>(V, slots, N, n, st);
-    case 4: return launch_blockls<4>(V, slots, N, n, st);
-    case PE_REAL | 1: return launch_blockls<PE_REAL | 1>(V, slots, N, n, st);
-    case PE_REAL | 2: return launch_blockls<PE_REAL | 2>(V, slots, N, n, st);
-    case PE_REAL | 4: return launch_blockls<PE_REAL | 4>(V, slots, N, n, st);
+    case 1: return dispatch_solve_t<1>(V, slots, N, n, small, st);
+    case 2: return dispatch_solve_t<2>(V, slots, N, n, small, st);
+    case 4: return dispatch_solve_t<4>(V, slots, N, n, small, st);
+    case PE_REAL | 1: return dispatch_solve_t<PE_REAL | 1>(V, slots, N, n, small, st);
+    case PE_REAL | 2: return dispatch_solve_t<PE_REAL | 2>(V, slots, N, n, small, st);
+    case PE_REAL | 4: return dispatch_solve_t<PE_REAL | 4>(V, slots, N, n, small, st);
   }
   return hipErrorInvalidValue;
 }
 
-// P problems of one size in groups of as many slots as `bytes` hold
-hipError_t solve_uniform(int code, int P, int N, int n, BlView V, size_t bytes, hipStream_t st) {
-  bl_layout_for(code, N, n, V);
+// P problems of one size in groups of as many slots as solve_bytes holds
+hipError_t solve_uniform(int code, int P, int N, int n, BlView V, hipStream_t st) {
+  const bool small = small_solve(code, N, n), keep = !V.add;
+  const size_t bytes = solve_bytes(code, N, n, P, small, keep);
+  solve_layout(code, N, n, small, keep, V);
   V.desc = nullptr;
   V.N = N;
   V.n = n;
   const int slots = int(std::min<size_t>({bytes / V.slot, size_t(P), size_t(kSolveSlots)}));
   for (int q = 0; q < P; q += slots) {
     V.q0 = q;
-    const hipError_t e = dispatch_solve(code, V, std::min(slots, P - q), N, n, st);
+    const hipError_t e = dispatch_solve(code, V, std::min(slots, P - q), N, n, small, st);
     if (e != hipSuccess) return e;
   }
   return hipSuccess;
@@ -1059,7 +1090,8 @@ size_t pe_newton_workspace_bytes(const pe_system* sys, int32_t P) {
   if (!sys || P < 0) return 0;
   const int W = width_of(sys->code), N = sys->view.N, n = sys->view.n;
   // [J | -F] row-major as the evaluation writes it, then the solver's slots
-  return align256(size_t(P) * W * N * (n + 1) * sizeof(double)) + solve_bytes(sys->code, N, n, P);
+  return align256(size_t(P) * W * N * (n + 1) * sizeof(double)) +
+         solve_bytes(sys->code, N, n, P, small_solve(sys->code, N, n), false);
 }
 
 }  // extern "C"
@@ -1119,7 +1151,7 @@ pe_status newton_step_impl(const pe_system* sys, int32_t P, double* x_inout, con
   V.add = 1;
   V.resid = resid_out;
   V.ws = base + front;
-  e = solve_uniform(code, P, N, n, V, solve_bytes(code, N, n, P), hs);
+  e = solve_uniform(code, P, N, n, V, hs);
   if (e != hipSuccess) return fail(PE_EDEVICE, std::string("newton solve launch: ") + hipGetErrorString(e));
   return PE_OK;
 }
@@ -1170,7 +1202,7 @@ static bool valid_level(int level) {
 
 size_t pe_lstsq_workspace_bytes(int32_t level, int32_t P, int32_t N, int32_t n) {
   if (!valid_level(level) || P < 0 || N < 1 || n < 1) return 0;
-  return solve_bytes(level, N, n, P);
+  return solve_bytes(level, N, n, P, small_solve(level, N, n), true);
 }
 
 pe_status pe_lstsq(int32_t level, int32_t P, int32_t N, int32_t n, const double* Ab, double* x, double* resid_out,
@@ -1196,8 +1228,7 @@ pe_status pe_lstsq(int32_t level, int32_t P, int32_t N, int32_t n, const double*
   V.Rout = R_out;
   V.Qout = Q_out;
   V.ws = static_cast<char*>(workspace);
-  const hipError_t e =
-      solve_uniform(level, P, N, n, V, solve_bytes(level, N, n, P), static_cast<hipStream_t>(stream));
+  const hipError_t e = solve_uniform(level, P, N, n, V, static_cast<hipStream_t>(stream));
   if (e != hipSuccess) return fail(PE_EDEVICE, std::string("least-squares launch: ") + hipGetErrorString(e));
   return PE_OK;
 }
@@ -1235,6 +1266,7 @@ struct pe_batch {
   int maxN = 0;
   bool any_multi = false;  // a system has a row of two or more chunks
   bool any_small = false;  // a system evaluated by values has a table of x alone
+  bool small_solve = true;  // every system's Gauss-Newton step is a small solve (one launch takes them all)
   std::vector<const pe_system*> systems;
   std::vector<int64_t> x_off, F_off, J_off;  // per point, doubles, [S+1]
   std::vector<BatchNewtonDesc> ndesc;        // per point offsets of the Newton workspace
@@ -1493,6 +1525,7 @@ pe_status pe_batch_create(pe_batch** out, int32_t S, const pe_system* const* sys
   for (int i = S - 1; i >= 0; --i) {
     b->left_N[i] = std::max(b->left_N[i + 1], systems[order[i]]->view.N);
     b->left_n[i] = std::max(b->left_n[i + 1], systems[order[i]]->view.n);
+    b->small_solve = b->small_solve && small_solve(systems[order[i]]->code, systems[order[i]]->view.N, systems[order[i]]->view.n);
   }
   hipStream_t hs = static_cast<hipStream_t>(stream);
   pe_status e = PE_OK;
@@ -1563,7 +1596,8 @@ pe_status pe_batch_eval(const pe_batch* b, int32_t P, const double* x, double* F
 size_t pe_batch_newton_workspace_bytes(const pe_batch* b, int32_t P) {
   if (!b || P < 0) return 0;
   // [J | -F] of every system-point, then the solver's slots
-  return align256(size_t(P) * b->w_total * 8) + solve_bytes(b->level, b->left_N[0], b->left_n[0], int64_t(b->S) * P);
+  return align256(size_t(P) * b->w_total * 8) +
+         solve_bytes(b->level, b->left_N[0], b->left_n[0], int64_t(b->S) * P, b->small_solve, false);
 }
 
 pe_status pe_batch_newton_step(const pe_batch* b, int32_t P, double* x_inout, void* workspace, double* resid_out,
@@ -1593,7 +1627,7 @@ pe_status pe_batch_newton_step(const pe_batch* b, int32_t P, double* x_inout, vo
   // groups of system-points in decreasing size, as many at a time as the
   // slots of that size fit in the workspace
   const int64_t total = int64_t(b->S) * P;
-  const size_t bytes = solve_bytes(b->level, b->left_N[0], b->left_n[0], total);
+  const size_t bytes = solve_bytes(b->level, b->left_N[0], b->left_n[0], total, b->small_solve, false);
   BlView V{};
   V.desc = b->d_ndesc;
   V.order = b->d_order;
@@ -1605,10 +1639,10 @@ pe_status pe_batch_newton_step(const pe_batch* b, int32_t P, double* x_inout, vo
   V.ws = base + align256(size_t(P) * b->w_total * 8);
   for (int64_t q = 0; q < total && e == hipSuccess;) {
     const int Nm = b->left_N[q / P], nm = b->left_n[q / P];
-    bl_layout_for(b->level, Nm, nm, V);
+    solve_layout(b->level, Nm, nm, b->small_solve, false, V);
     V.q0 = int(q);
     const int slots = int(std::min<int64_t>({int64_t(bytes / V.slot), total - q, int64_t(kSolveSlots)}));
-    e = dispatch_solve(b->level, V, slots, Nm, nm, hs);
+    e = dispatch_solve(b->level, V, slots, Nm, nm, b->small_solve, hs);
     q += slots;
   }
   if (e != hipSuccess) return fail(PE_EDEVICE, std::string("batch newton solve: ") + hipGetErrorString(e));
