@@ -120,7 +120,7 @@ struct BlView {
 
 struct BlMisc {
   double rmax;   // largest |r_ii| so far
-  int flag;      // 1: a pivot was numerically zero, the problem is done
+  int flag;      // panel + 1 in which a pivot was numerically zero, and the problem done; 0: none
   int mgs;       // 1: the current panel was orthogonalised by plain MGS
 };
 
@@ -871,7 +871,7 @@ __global__ __launch_bounds__(BlChol<L>::T) void bl_chol_kernel(BlView V, int pan
     }
   }
   if (nonfinite) {
-    if (tid == 0) misc->flag = 1;
+    if (tid == 0) misc->flag = panel + 1;
     return;
   }
   __syncthreads();
@@ -899,7 +899,7 @@ __global__ __launch_bounds__(BlChol<L>::T) void bl_chol_kernel(BlView V, int pan
       if (!(r > thresh * rmax)) singular = true;
     }
     if (singular) {
-      if (tid == 0) misc->flag = 1;
+      if (tid == 0) misc->flag = panel + 1;
       return;
     }
     for (int idx = tid; idx < B * B; idx += T) {
@@ -940,7 +940,7 @@ __global__ __launch_bounds__(BlChol<L>::T) void bl_chol_kernel(BlView V, int pan
   __syncthreads();
   double rmin = 1.0;
   if (!bl_mgs_sweep<L>(p, Wp, k0, bcur, Rp, thresh, &rmax, true, norm0, &rmin)) {
-    if (tid == 0) misc->flag = 1;
+    if (tid == 0) misc->flag = panel + 1;
     return;
   }
   if (rmin < (NL == 1 ? 0x1p-20 : (NL == 2 ? 0x1p-40 : 0x1p-44))) {
@@ -1598,8 +1598,9 @@ __global__ __launch_bounds__(256) void bl_finish_kernel(BlView V) {
 }
 
 // R (row-major [P][components][n][n + 1], zeros below the diagonal) and
-// Q = X (I - F) ([P][components][N][n]).  A group of lanes takes a row of a
-// panel of Q.  grid (blocks, slots), 256 threads
+// Q = X (I - F) ([P][components][N][n]); zeros from the panel of a zero pivot
+// on, which has neither.  A group of lanes takes a row of a panel of Q.  grid
+// (blocks, slots), 256 threads
 template <int L>
 __global__ __launch_bounds__(256) void bl_export_kernel(BlView V) {
   using K = Bl<L>;
@@ -1609,10 +1610,12 @@ __global__ __launch_bounds__(256) void bl_export_kernel(BlView V) {
   const int64_t pt = V.q0 + blockIdx.y;
   const int ncol = p.n + 1;
   const int64_t rplane = int64_t(ncol) * p.n;
+  const int flag = bl_at<BlMisc>(p, V.oMisc)->flag;
+  const int done = flag ? (flag - 1) * B : p.n;
   if (V.Rout && idx < rplane) {
     const int i = int(idx / ncol), j = int(idx - int64_t(i) * ncol);
     const C<L> r =
-        i <= j ? load_planar<L>(bl_at<double>(p, V.oR) + int64_t(j) * p.n, rplane, i) : c_zero<L>();
+        i <= j && i < done ? load_planar<L>(bl_at<double>(p, V.oR) + int64_t(j) * p.n, rplane, i) : c_zero<L>();
     store_planar(V.Rout + pt * (int64_t(K::W) * rplane), rplane, idx, r);
   }
   if (V.Qout && idx < int64_t(p.N) * p.n) {
@@ -1620,6 +1623,10 @@ __global__ __launch_bounds__(256) void bl_export_kernel(BlView V) {
     const int i = int(idx / p.n), c = int(idx - int64_t(i) * p.n);
     const int k0 = c / B * B, cc = c - k0;
     const int64_t plane = int64_t(ncol) * p.N;
+    if (c >= done) {
+      store_planar(V.Qout + pt * (int64_t(K::W) * p.N * p.n), int64_t(p.N) * p.n, idx, c_zero<L>());
+      return;
+    }
     const double* X = bl_at<double>(p, V.oW) + i;
     const double* F = bl_at<double>(p, V.oF) + size_t(c / B) * B * B * CX;
     double fr = 0.0, fi = 0.0;
