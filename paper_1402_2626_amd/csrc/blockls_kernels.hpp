@@ -112,7 +112,7 @@ struct BlView {
   char* ws;
   size_t slot;        // bytes of a slot
   // byte offsets inside a slot
-  size_t oW, oR, oInv, oY, oU, oRp, oF, oS, oXD, oXU, oXr, oSD, oSe, oCe, oMisc;
+  size_t oW, oR, oInv, oY, oU, oRp, oF, oS, oXD, oXU, oXr, oSD, oSe, oCe, oMisc, oPiv;
   size_t s_split;     // bytes of one split's contraction output
   size_t g_split;     // and of one split's Gram matrix
   int nmax;           // stride of the two column-exponent arrays
@@ -121,7 +121,15 @@ struct BlView {
 struct BlMisc {
   double rmax;   // largest |r_ii| so far
   int flag;      // panel + 1 in which a pivot was numerically zero, and the problem done; 0: none
-  int mgs;       // 1: the current panel was orthogonalised by plain MGS
+  int mgs;       // 1: the current panel is orthogonalised by plain MGS
+  int ticket;    // its next column
+};
+
+// columns of a panel under plain MGS, per sweep: 0 open, 1 orthonormal, 2 given up
+struct BlPivots {
+  int state[2][64];
+  double rmax[64];  // largest |r_ii| so far
+  double loss[64];  // bound of |q_i^H q_c| for i < c
 };
 
 // Offsets of a slot's regions for problems of at most N rows and n unknowns
@@ -129,7 +137,8 @@ struct BlMisc {
 // by columns, R [components][n + 1][n] by columns (column n is y = Q^H b),
 // 1 / r_jj, y, the panel's U and D^1/2 U, F of every panel, S per row split,
 // the digits of X in two orders with its row exponents, the digits of T with
-// its column exponents, two sets of column exponents, the state.
+// its column exponents, two sets of column exponents, the state, the pivots of
+// a panel under plain MGS.
 template <int L>
 inline void bl_layout(int N, int n, BlView& V) {
   using K = Bl<L>;
@@ -160,6 +169,7 @@ inline void bl_layout(int N, int n, BlView& V) {
   V.oSe = take(size_t(n + 1) * 4);
   V.oCe = take(size_t(n + 1) * 2 * 4);
   V.oMisc = take(sizeof(BlMisc));
+  V.oPiv = take(sizeof(BlPivots));
   V.slot = off;
 }
 
@@ -702,87 +712,18 @@ __device__ __forceinline__ R<NLV> bl_recip(const R<NLV>& a) {
   }
 }
 
-// squared norm of a wavefront's rows of a column summed over the wavefront
-template <int NLV>
-__device__ __forceinline__ R<NLV> bl_wave_sum(R<NLV> s) {
-#pragma unroll
-  for (int m = 1; m < 64; m <<= 1) {
-    R<NLV> o;
-#pragma unroll
-    for (int l = 0; l < NLV; ++l) o.x[l] = __shfl_xor(s.x[l], m);
-    s = r_add(s, o);
-  }
-  return s;
-}
-
-// One sweep of modified Gram-Schmidt over the panel's columns in W by one
-// workgroup: each wavefront takes columns of its own, its lanes the rows.
-// Rr[i * B + j] gets R; the columns become orthonormal.  `rmin` is the
-// smallest ratio of a pivot to its column's norm before the sweep.  Returns
-// false when a pivot is numerically zero against *rmax (first sweep only).
-template <int L>
-__device__ bool bl_mgs_sweep(const BlProb& p, double* Wp, int k0, int bcur, double* Rr, double thresh, double* rmax,
-                             bool check, double* norm0, double* rmin) {
-  using K = Bl<L>;
-  constexpr int NL = K::NL;
-  const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6, nwave = BlChol<L>::T / 64;
-  const int64_t plane = int64_t(p.n + 1) * p.N;
-  auto norm2 = [&](int c) {
-    R<NL> s = r_zero<NL>();
-    for (int i = lane; i < p.N; i += 64) s = r_add(s, c_norm2(load_planar<L>(Wp + int64_t(c) * p.N, plane, i)));
-    return bl_wave_sum<NL>(s);
-  };
-  for (int j = wave; j < bcur; j += nwave) {
-    const R<NL> s = norm2(k0 + j);
-    if (lane == 0) norm0[j] = sqrt(s.x[0]);
-  }
-  __syncthreads();
-  for (int k = 0; k < bcur; ++k) {
-    // every wavefront sums the pivot's norm itself (the same value in each)
-    const R<NL> r = r_sqrt(norm2(k0 + k));
-    if (check) {
-      *rmax = fmax(*rmax, r.x[0]);
-      if (!(r.x[0] > thresh * *rmax)) return false;  // uniform
-    }
-    *rmin = fmin(*rmin, r.x[0] / norm0[k]);
-    const R<NL> ir = r_recip(r);
-    __syncthreads();
-    for (int i = threadIdx.x; i < p.N; i += BlChol<L>::T) {
-      double* c = Wp + int64_t(k0 + k) * p.N;
-      store_planar(c, plane, i, c_mul_r(load_planar<L>(c, plane, i), ir));
-    }
-    if (threadIdx.x == 0) store_aos(Rr + (size_t(k) * K::B + k) * K::W, c_from_r<L>(r));
-    __syncthreads();
-    const double* q = Wp + int64_t(k0 + k) * p.N;
-    for (int j = k + 1 + wave; j < bcur; j += nwave) {
-      double* a = Wp + int64_t(k0 + j) * p.N;
-      C<L> d = c_zero<L>();
-      for (int i = lane; i < p.N; i += 64)
-        d = c_add(d, c_mul_conj_a(load_planar<L>(q, plane, i), load_planar<L>(a, plane, i)));
-#pragma unroll
-      for (int m = 1; m < 64; m <<= 1) d = c_add(d, shfl_xor_c(d, m));
-      const C<L> nd = c_neg(d);
-      for (int i = lane; i < p.N; i += 64)
-        store_planar(a, plane, i, c_add(load_planar<L>(a, plane, i), c_mul(nd, load_planar<L>(q, plane, i))));
-      if (lane == 0) store_aos(Rr + (size_t(k) * K::B + j) * K::W, d);
-    }
-    __syncthreads();
-  }
-  return true;
-}
-
 // Factor of the panel's Gram matrix G (of the columns scaled by their
 // exponents): G = U^H D U, U unit upper triangular.  A thread keeps entries
 // of the upper triangle in registers; a row is published in LDS when the
 // pivots above it are done, and step k's threads subtract
 // conj(g_ki) g_kj / d_k, every thread forming the reciprocal of the pivot
 // itself, so that a step has one barrier (quad double: the row over its pivot
-// once, and two).  Square roots wait for the end.  A pivot below kPivot of its column's squared norm would leave
-// E = X^H X - I too large for its first order (E is about u_C / pivot
-// ratio, u_C the unit roundoff of the factor's level): then the panel is
-// orthogonalised by modified Gram-Schmidt here, again if one sweep leaves
-// E above the square root of the level's roundoff.  One workgroup per
-// problem: it is bound by the chain of B pivots.
+// once, and two).  Square roots wait for the end.  A pivot below kPivot of its
+// column's squared norm would leave E = X^H X - I too large for its first order
+// (E is about u_C / pivot ratio, u_C the unit roundoff of the factor's level):
+// then the panel is left to plain modified Gram-Schmidt (bl_mgs_panel, in the
+// next kernel).  One workgroup per problem: it is bound by the chain of B
+// pivots.
 template <int L>
 __global__ __launch_bounds__(BlChol<L>::T) void bl_chol_kernel(BlView V, int panel, int cur) {
   using K = Bl<L>;
@@ -801,8 +742,7 @@ __global__ __launch_bounds__(BlChol<L>::T) void bl_chol_kernel(BlView V, int pan
   double* g0 = G + size_t(B) * B * WC;  // [B] diagonal before the factorisation
   double* dinv = g0 + B;              // [B][NC_] 1 / d
   double* sq = dinv + B * NC_;        // [B][NC_] sqrt(d)
-  double* norm0 = sq + B * NC_;       // [B]
-  double* frow = norm0 + B;           // [B] numbers (quad double)
+  double* frow = sq + B * NC_;        // [B] numbers (quad double)
   int* ex = reinterpret_cast<int*>(frow + B * WC);  // [B] column exponents
   (void)frow;
   const int ns = bl_gram_splits(p.N);
@@ -930,44 +870,24 @@ __global__ __launch_bounds__(BlChol<L>::T) void bl_chol_kernel(BlView V, int pan
     }
     return;
   }
-  // modified Gram-Schmidt on the panel itself
-  double* Wp = bl_at<double>(p, V.oW);
+  // too ill-conditioned: modified Gram-Schmidt, column by column
   for (int idx = tid; idx < B * B; idx += T) {
     store_aos(Rp + size_t(idx) * K::W, c_zero<L>());
     store_aos(U + size_t(idx) * K::W, c_zero<L>());
   }
   if (tid < B) rexp[tid] = 0;
-  __syncthreads();
-  double rmin = 1.0;
-  if (!bl_mgs_sweep<L>(p, Wp, k0, bcur, Rp, thresh, &rmax, true, norm0, &rmin)) {
-    if (tid == 0) misc->flag = panel + 1;
-    return;
-  }
-  if (rmin < (NL == 1 ? 0x1p-20 : (NL == 2 ? 0x1p-40 : 0x1p-44))) {
-    // again: R = R2 R1 (R2 into U's place, then the product)
-    double unused = 1.0;
-    bl_mgs_sweep<L>(p, Wp, k0, bcur, U, 0.0, &unused, false, norm0, &unused);
-    __syncthreads();
-    // entry (i, j) = sum over m = i .. j of R2[i][m] R1[m][j]: a thread owns a
-    // column and goes down it, since entry (i, j) needs R1[m][j] for m >= i only
-    for (int j = tid; j < bcur; j += T)
-      for (int i = 0; i <= j; ++i) {
-        C<L> s = c_zero<L>();
-        for (int m = i; m <= j; ++m)
-          s = c_add(s, c_mul(load_aos<L>(U + (size_t(i) * B + m) * K::W), load_aos<L>(Rp + (size_t(m) * B + j) * K::W)));
-        store_aos(Rp + (size_t(i) * B + j) * K::W, s);
-      }
-  }
+  BlPivots* piv = bl_at<BlPivots>(p, V.oPiv);
+  if (tid < 128) piv->state[tid >> 6][tid & 63] = 0;
   if (tid == 0) {
-    misc->rmax = rmax;
     misc->mgs = 1;
+    misc->ticket = 0;
   }
 }
 
 template <int L>
 __host__ __device__ inline size_t bl_chol_lds() {
   using K = Bl<L>;
-  return (size_t(K::B) * K::B * K::WC + K::B * (2 + 2 * limbs_of(K::LC) + K::WC)) * sizeof(double) + K::B * sizeof(int);
+  return (size_t(K::B) * K::B * K::WC + K::B * (1 + 2 * limbs_of(K::LC) + K::WC)) * sizeof(double) + K::B * sizeof(int);
 }
 
 // ------------------------------------------------------------------ X = A U^-1 D^-1/2
@@ -995,13 +915,192 @@ __device__ __forceinline__ double bl_readlane(double v, int lane) {
 }
 
 template <int L>
+__host__ __device__ inline size_t bl_solve_lds() {
+  using K = Bl<L>;
+  return (size_t(K::B) * K::B * (is_real(L) ? K::NL : 4 * K::NL) + 4 * bl_solve_rows<L>() * 64 * K::NL) * sizeof(double) + 4 * bl_solve_rows<L>() * sizeof(int);
+}
+
+// ------------------------------------------------------------------ plain MGS
+
+__device__ __forceinline__ int bl_load_state(const int* s) {
+  return __hip_atomic_load(s, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+}
+
+// State of column c once it is no longer open, the same in all 256 threads, with
+// the column's memory visible to them.  Bounded: a wait of some seconds gives
+// the panel up.
+__device__ __forceinline__ int bl_await(const int* state, int* sh) {
+  __syncthreads();  // the word is free
+  if (threadIdx.x == 0) {
+    int s = 0;
+    for (int n = 0; n < (1 << 21) && (s = bl_load_state(state)) == 0; ++n) __builtin_amdgcn_s_sleep(8);
+    *sh = s == 0 ? 2 : s;
+  }
+  __syncthreads();
+  __threadfence();
+  return *sh;
+}
+
+// sum of a number over 256 threads, in a fixed order; red: 4 numbers
+template <int L>
+__device__ __forceinline__ C<L> bl_wg_sum(C<L> v, double* red) {
+#pragma unroll 1
+  for (int m = 1; m < 64; m <<= 1) v = c_add(v, shfl_xor_c(v, m));
+  __syncthreads();  // the numbers are free
+  if ((threadIdx.x & 63) == 0) store_aos(red + (threadIdx.x >> 6) * width_of(L), v);
+  __syncthreads();
+  C<L> s = load_aos<L>(red);
+  for (int q = 1; q < 4; ++q) s = c_add(s, load_aos<L>(red + q * width_of(L)));
+  return s;
+}
+
+// Column j of the panel in one sweep: off with the columns before it as they
+// become orthonormal, in order, then normalised; column j of the sweep's R into
+// Rr.  The column is kept in LDS (rows from `cap` on in its place in W).  The
+// first sweep tests the pivot and bounds what is left of the columns before it
+// (piv->loss).  Returns false when the panel is given up (a zero pivot).
+template <int L>
+__device__ bool bl_mgs_column(const BlProb& p, const BlMisc* misc, BlPivots* piv, int sweep, double* Wp, double* Rr,
+                              int k0, int j, double* red, int* sh, double* la, int cap) {
+  using K = Bl<L>;
+  constexpr int NL = K::NL;
+  const int tid = threadIdx.x;
+  const int64_t plane = int64_t(p.n + 1) * p.N;
+  double* col = Wp + int64_t(k0 + j) * p.N;
+  // a thread only ever touches its own rows (the address space is spelled out:
+  // the compiler would join the two sides in flat accesses)
+  auto* const lc = (__attribute__((address_space(3))) double*)la;
+  auto get = [&](int i) {
+    if (i >= cap) return load_planar<L>(col, plane, i);
+    C<L> v;
+#pragma unroll
+    for (int l = 0; l < NL; ++l) {
+      v.re.x[l] = lc[l * cap + i];
+      if constexpr (!is_real(L)) v.im.x[l] = lc[(NL + l) * cap + i];
+    }
+    return v;
+  };
+  auto put = [&](int i, const C<L>& v) {
+    if (i >= cap) return store_planar(col, plane, i, v);
+#pragma unroll
+    for (int l = 0; l < NL; ++l) {
+      lc[l * cap + i] = v.re.x[l];
+      if constexpr (!is_real(L)) lc[(NL + l) * cap + i] = v.im.x[l];
+    }
+  };
+  C<L> s = c_zero<L>();
+  for (int i = tid; i < p.N; i += 256) {
+    const C<L> v = load_planar<L>(col, plane, i);
+    s.re = r_add(s.re, c_norm2(v));
+    put(i, v);
+  }
+  s = bl_wg_sum<L>(s, red);
+  const double size = r_sqrt(s.re).x[0];
+  double lost = 0.0;
+  for (int c = 0; c < j; ++c) {
+    if (bl_await(piv->state[sweep] + c, sh) == 2) return false;
+    const double* q = Wp + int64_t(k0 + c) * p.N;
+    C<L> d = c_zero<L>();
+    for (int i = tid; i < p.N; i += 256) d = c_add(d, c_mul_conj_a(load_planar<L>(q, plane, i), get(i)));
+    d = bl_wg_sum<L>(d, red);
+    const C<L> nd = c_neg(d);
+    s = c_zero<L>();
+    for (int i = tid; i < p.N; i += 256) {
+      const C<L> v = c_add(get(i), c_mul(nd, load_planar<L>(q, plane, i)));
+      put(i, v);
+      if (c + 1 == j) s.re = r_add(s.re, c_norm2(v));
+    }
+    if (c + 1 == j) s = bl_wg_sum<L>(s, red);
+    lost += piv->loss[c] * (fabs(d.re.x[0]) + fabs(im_lead(d)));
+    if (tid == 0) store_aos(Rr + (size_t(c) * K::B + j) * K::W, d);
+  }
+  const R<NL> r = r_sqrt(s.re);
+  if (sweep == 0) {
+    const double rmax = fmax(j == 0 ? misc->rmax : piv->rmax[j - 1], r.x[0]);
+    if (!(r.x[0] > double(p.n) * level_unit<L>() * rmax)) return false;
+    if (tid == 0) {
+      piv->rmax[j] = rmax;
+      piv->loss[j] = (lost + level_unit<L>() * size) / r.x[0];
+    }
+  } else if (!(r.x[0] > 0.0)) {
+    return false;
+  }
+  const R<NL> ir = r_recip(r);
+  for (int i = tid; i < p.N; i += 256) store_planar(col, plane, i, c_mul_r(get(i), ir));
+  if (tid == 0) store_aos(Rr + (size_t(j) * K::B + j) * K::W, c_from_r<L>(r));
+  return true;
+}
+
+// A panel that is too ill-conditioned for its Gram matrix, by plain modified
+// Gram-Schmidt: the workgroups of bl_solve_kernel (256 threads each) take its
+// columns by ticket, each subtracts the columns before its own as they are
+// published and publishes its own.  A workgroup only ever waits for columns with
+// smaller tickets, whose workgroups are running, so it makes progress however
+// many of them fit on the chip.  A second sweep where the first leaves too much
+// of a column in another one: E's first order has to do, so the loss has to be
+// below 2^-33, 2^-64 or 2^-162, whose square and whose product with double's
+// roundoff are below the level's.  R = R2 R1 then.  False: the panel was given
+// up.  Bound by the chain of pivots (a wait, two passes over a column, its
+// publication): 17 us each at 2048 rows in complex double double, 7 at 256,
+// where one workgroup for the panel took 90 and 12.
+template <int L>
+__device__ bool bl_mgs_panel(const BlView& V, const BlProb& p, BlMisc* misc, int panel, int bcur, double* lds) {
+  using K = Bl<L>;
+  constexpr double kLoss = K::NL == 1 ? 0x1p-33 : (K::NL == 2 ? 0x1p-64 : 0x1p-162);
+  const int k0 = panel * K::B, tid = threadIdx.x;
+  BlPivots* piv = bl_at<BlPivots>(p, V.oPiv);
+  double* Wp = bl_at<double>(p, V.oW);
+  double* R1 = bl_at<double>(p, V.oRp);
+  double* R2 = bl_at<double>(p, V.oU);
+  double* red = lds;
+  int* sh = reinterpret_cast<int*>(red + 4 * width_of(L));
+  double* la = red + 4 * width_of(L) + 2;
+  const int cap = min(p.N, int((bl_solve_lds<L>() / 8 - 4 * width_of(L) - 2) / width_of(L)));
+  int j;  // a ticket taken in one sweep may be one of the next
+  auto take = [&]() {
+    __syncthreads();
+    if (tid == 0) *sh = atomicAdd(&misc->ticket, 1);
+    __syncthreads();
+    j = *sh;
+  };
+  take();
+  for (int sweep = 0; sweep < 2; ++sweep) {
+    for (; j < (sweep + 1) * bcur; take()) {
+      const int c = j - sweep * bcur;
+      const bool ok = bl_mgs_column<L>(p, misc, piv, sweep, Wp, sweep ? R2 : R1, k0, c, red, sh, la, cap);
+      if (tid == 0) {
+        if (!ok) misc->flag = panel + 1;
+        else if (sweep == 0 && c + 1 == bcur) misc->rmax = piv->rmax[c];
+      }
+      __threadfence();
+      __syncthreads();
+      if (tid == 0)
+        __hip_atomic_store(piv->state[sweep] + c, ok ? 1 : 2, __ATOMIC_RELEASE, __HIP_MEMORY_SCOPE_AGENT);
+      if (ok && sweep == 1) {
+        // entry (i, c) = sum over m = i .. c of R2[i][m] R1[m][c]
+        C<L> s = c_zero<L>();
+        for (int m = tid; m <= c; ++m)
+          s = c_add(s, c_mul(load_aos<L>(R2 + (size_t(tid) * K::B + m) * K::W), load_aos<L>(R1 + (size_t(m) * K::B + c) * K::W)));
+        __syncthreads();
+        if (tid <= c) store_aos(R1 + (size_t(tid) * K::B + c) * K::W, s);
+      }
+    }
+    if (bl_await(piv->state[sweep] + bcur - 1, sh) == 2) return false;
+    bool again = false;
+    for (int c = 0; c < bcur; ++c) again = again || !(piv->loss[c] <= kLoss);
+    if (!again) break;
+  }
+  return true;
+}
+
+template <int L>
 __global__ __launch_bounds__(256) void bl_solve_kernel(BlView V, int panel, int cur) {
   using K = Bl<L>;
   constexpr int B = K::B, NL = K::NL, ND = K::ND, CX = K::CX, NR = bl_solve_rows<L>(), RPW = 4 * NR;
   using RL = R<NL>;
   extern __shared__ double lds[];
   const BlProb p = bl_prob<L>(V, blockIdx.y);
-  const BlMisc* misc = bl_at<BlMisc>(p, V.oMisc);
+  BlMisc* misc = bl_at<BlMisc>(p, V.oMisc);
   const int k0 = panel * B, r0 = blockIdx.x * RPW;
   const int NC = (p.N + kBlRows - 1) / kBlRows;
   if (k0 >= p.n || r0 >= NC * kBlRows) return;
@@ -1017,31 +1116,38 @@ __global__ __launch_bounds__(256) void bl_solve_kernel(BlView V, int panel, int 
   const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
   const int j = lane % B, comp = lane / B;
   RL a[NR];
+  auto load_rows = [&]() {
 #pragma unroll
-  for (int r = 0; r < NR; ++r) {
-    const int row = r0 + wave * NR + r;
-    const bool live = row < p.N && j < bcur;
+    for (int r = 0; r < NR; ++r) {
+      const int row = r0 + wave * NR + r;
+      const bool live = row < p.N && j < bcur;
 #pragma unroll
-    for (int l = 0; l < NL; ++l)
-      a[r].x[l] = live ? Wp[(comp * NL + l) * plane + int64_t(k0 + j) * p.N + row] : 0.0;
-  }
-      // entry (i, j) of plane k at [i][k][j]: the lanes of a row read consecutive
-      // words; planes: real limbs, imaginary limbs, their negatives, real limbs
-      // again, so that a lane's two factors sit at fixed offsets
+      for (int l = 0; l < NL; ++l)
+        a[r].x[l] = live ? Wp[(comp * NL + l) * plane + int64_t(k0 + j) * p.N + row] : 0.0;
+    }
+  };
+  load_rows();
+  // entry (i, j) of plane k at [i][k][j]: the lanes of a row read consecutive
+  // words; planes: real limbs, imaginary limbs, their negatives, real limbs
+  // again, so that a lane's two factors sit at fixed offsets
 #pragma unroll 16
-      for (int q = 0; q < B * B * K::W / 256; ++q) {
-        const int idx = tid + q * 256, k = idx % K::W, ij = idx / K::W;
-        const double u = U[idx];
-        double* at = Us + size_t(ij / B) * UP * B + ij % B;
-        if constexpr (is_real(L)) {
-          at[k * B] = u;
-        } else {
-          at[k * B] = u;
-          at[(k + 2 * NL) * B] = k < NL ? u : -u;
-        }
-      }
+  for (int q = 0; q < B * B * K::W / 256; ++q) {
+    const int idx = tid + q * 256, k = idx % K::W, ij = idx / K::W;
+    const double u = U[idx];
+    double* at = Us + size_t(ij / B) * UP * B + ij % B;
+    if constexpr (is_real(L)) {
+      at[k * B] = u;
+    } else {
+      at[k * B] = u;
+      at[(k + 2 * NL) * B] = k < NL ? u : -u;
+    }
+  }
   if (flag) return;
-  if (!mgs) {
+  if (__builtin_expect(mgs, 0)) {
+    if (!bl_mgs_panel<L>(V, p, misc, panel, bcur, lds)) return;
+    load_rows();
+    __syncthreads();  // the words of the waits are free
+  } else {
     const double* is = U + size_t(B) * B * K::W;
     RL inv;
 #pragma unroll
@@ -1142,12 +1248,6 @@ __global__ __launch_bounds__(256) void bl_solve_kernel(BlView V, int panel, int 
     }
     bl_put4<NL, ND>(v, ev, dst, 1024);
   }
-}
-
-template <int L>
-__host__ __device__ inline size_t bl_solve_lds() {
-  using K = Bl<L>;
-  return (size_t(K::B) * K::B * (is_real(L) ? K::NL : 4 * K::NL) + 4 * bl_solve_rows<L>() * 64 * K::NL) * sizeof(double) + 4 * bl_solve_rows<L>() * sizeof(int);
 }
 
 // ------------------------------------------------------------------ R and T
