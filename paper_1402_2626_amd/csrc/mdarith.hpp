@@ -497,6 +497,84 @@ PE_HD C<4> c_mul<4>(const C<4>& a, const C<4>& b) {
   return C<4>{qd_dot2(a.re, b.re, r_neg(a.im), b.im), qd_dot2(a.re, b.im, a.im, b.re)};
 }
 
+// The same two products with the parts of order 3 joined by TwoSums whose errors
+// go into a fifth component: half the error (mean 0.145 u^4 against 0.29 for
+// the sum of two products of operands in [1/2, 3/2], 0.07 against 0.14 for one)
+// for a tenth more operations.
+PE_HD R<4> r_mul_fine(const R<4>& a, const R<4>& b) {
+  double p0, q0, p1, q1, p2, q2, p3, q3, p4, q4, p5, q5;
+  two_prod(a.x[0], b.x[0], p0, q0);
+  two_prod(a.x[0], b.x[1], p1, q1);
+  two_prod(a.x[1], b.x[0], p2, q2);
+  two_prod(a.x[0], b.x[2], p3, q3);
+  two_prod(a.x[1], b.x[1], p4, q4);
+  two_prod(a.x[2], b.x[0], p5, q5);
+  double o3 = PE_FMA(a.x[0], b.x[3], PE_FMA(a.x[1], b.x[2], PE_FMA(a.x[2], b.x[1], a.x[3] * b.x[0])));
+  double s1, e_a, e_b;
+  two_sum(p1, p2, s1, e_a);
+  two_sum(s1, q0, s1, e_b);
+  double s2, f0, f1, f2, f3, f4, f5;
+  two_sum(p3, p4, s2, f0);
+  two_sum(s2, p5, s2, f1);
+  two_sum(s2, q1, s2, f2);
+  two_sum(s2, q2, s2, f3);
+  two_sum(s2, e_a, s2, f4);
+  two_sum(s2, e_b, s2, f5);
+  double s3, h0, h1;
+  two_sum(o3, q3 + q4 + q5, s3, h0);
+  two_sum(s3, (f0 + f1) + (f2 + f3) + (f4 + f5), s3, h1);
+  return renorm5(p0, s1, s2, s3, h0 + h1);
+}
+
+PE_HD R<4> qd_dot2_fine(const R<4>& a, const R<4>& b, const R<4>& c, const R<4>& d) {
+  double p0a, q0a, p0c, q0c, s0, e0;
+  two_prod(a.x[0], b.x[0], p0a, q0a);
+  two_prod(c.x[0], d.x[0], p0c, q0c);
+  two_sum(p0a, p0c, s0, e0);
+  double p1[4], q1[4];
+  two_prod(a.x[0], b.x[1], p1[0], q1[0]);
+  two_prod(a.x[1], b.x[0], p1[1], q1[1]);
+  two_prod(c.x[0], d.x[1], p1[2], q1[2]);
+  two_prod(c.x[1], d.x[0], p1[3], q1[3]);
+  double f[6], s1;
+  two_sum(p1[0], p1[1], s1, f[0]);
+  two_sum(s1, p1[2], s1, f[1]);
+  two_sum(s1, p1[3], s1, f[2]);
+  two_sum(s1, q0a, s1, f[3]);
+  two_sum(s1, q0c, s1, f[4]);
+  two_sum(s1, e0, s1, f[5]);
+  double p2[6], q2[6];
+  two_prod(a.x[0], b.x[2], p2[0], q2[0]);
+  two_prod(a.x[1], b.x[1], p2[1], q2[1]);
+  two_prod(a.x[2], b.x[0], p2[2], q2[2]);
+  two_prod(c.x[0], d.x[2], p2[3], q2[3]);
+  two_prod(c.x[1], d.x[1], p2[4], q2[4]);
+  two_prod(c.x[2], d.x[0], p2[5], q2[5]);
+  double s2 = p2[0], g = 0.0, e;
+#pragma unroll
+  for (int i = 1; i < 6; ++i) {
+    two_sum(s2, p2[i], s2, e);
+    g += e;
+  }
+#pragma unroll
+  for (int i = 0; i < 4; ++i) {
+    two_sum(s2, q1[i], s2, e);
+    g += e;
+  }
+#pragma unroll
+  for (int i = 0; i < 6; ++i) {
+    two_sum(s2, f[i], s2, e);
+    g += e;
+  }
+  const double oa = PE_FMA(a.x[0], b.x[3], PE_FMA(a.x[1], b.x[2], PE_FMA(a.x[2], b.x[1], a.x[3] * b.x[0])));
+  const double oc = PE_FMA(c.x[0], d.x[3], PE_FMA(c.x[1], d.x[2], PE_FMA(c.x[2], d.x[1], c.x[3] * d.x[0])));
+  double s3, h0, h1, h2;
+  two_sum(oa, oc, s3, h0);
+  two_sum(s3, (q2[0] + q2[1]) + (q2[2] + q2[3]) + (q2[4] + q2[5]), s3, h1);
+  two_sum(s3, g, s3, h2);
+  return renorm5(s0, s1, s2, s3, h0 + (h1 + h2));
+}
+
 // ------------------------------------------------------------------ operation counts
 // FP64 operations per call of each primitive as written above (an FMA counts
 // once here; flop counts with FMA = 2 are derived from the FMA share).
