@@ -447,14 +447,14 @@ pe_status upload_values(pe_system* sys, hipStream_t hs) {
   V.tab = plan.tab;
   V.inv = plan.inv;
   // products of up to `degree` factors (counted with their exponents) of
-  // modulus 2^-safe .. 2^(safe - 1/2) stay within 2^-700 .. 2^700
+  // modulus 2^-safe .. 2^safe stay within 2^-350 .. 2^350
   int64_t degree = 1;
   for (int64_t t = 0; t < sys->host.M; ++t) {
     int64_t d = 0;
     for (int64_t o = sys->in_mon_ptr[t]; o < sys->in_mon_ptr[t + 1]; ++o) d += sys->in_exp[o];
     degree = std::max(degree, d);
   }
-  V.safe = int(std::min<int64_t>(300, 700 / degree));
+  V.safe = int(std::min<int64_t>(300, 350 / degree));
   V.lgQ = PV.lgQ;
   V.slices = PV.slices;
   V.max_mon = PV.max_mon;

@@ -59,7 +59,7 @@ struct ValView {
   int n, N, emax;
   int tab;  // powers in the table: emax, or 1 (higher ones formed per factor)
   int inv;  // reciprocals behind them, or formed per column
-  int safe;  // no product of a monomial's factors leaves the range while all |x_v| are in 2^-safe .. 2^(safe - 1); 0: none is safe
+  int safe;  // monomials of variables within 2^-safe .. 2^safe stay within 2^-350 .. 2^350, whatever the order of the factors
   int lgQ, slices, max_mon;
   int max_units;
   int lgvw;   // log2 of the threads of a copy
@@ -109,11 +109,11 @@ __device__ __forceinline__ C<L> val_ld_coef(const double* p) {
 
 // doubles of a copy's LDS: [`blocks` (powers, reciprocals) of n + 1 numbers][max_mon + 1
 // values][n column sums when rows have several blocks or the sums run over
-// rows][zero counts, bytes][2 flags]
+// rows][zero counts, bytes][4 flags]
 template <int L>
 __host__ __device__ inline size_t val_copy_doubles(int n, int blocks, int max_mon, bool sums) {
   const size_t d =
-      size_t(width_of(L)) * (size_t(blocks) * (n + 1) + max_mon + 1 + (sums ? n : 0)) + size_t(max_mon + 8) / 8 + 1;
+      size_t(width_of(L)) * (size_t(blocks) * (n + 1) + max_mon + 1 + (sums ? n : 0)) + size_t(max_mon + 8) / 8 + 2;
   return (d + 1) & ~size_t(1);  // 16-byte words
 }
 
@@ -163,7 +163,7 @@ struct ValLds {
   double* val;    // [max_mon + 1]
   double* sum;    // [n]
   uint8_t* zeros;  // [max_mon]
-  int* flag;      // [0], of the point: 1 a zero variable, 2 direct products, 4 ranges to be tested; [1], of the row: direct products
+  int* flag;      // [0], of the point: 1 a zero variable, 2 direct products; [1], of the row: direct products; [2], of the point: val_far
   int cols;
 };
 
@@ -292,7 +292,7 @@ __device__ __forceinline__ void val_table(const ValView& S, const ValLds<L>& M, 
                                           int VW, const C<L>& x0) {
   const double big = __builtin_ldexp(1.0, min(300, 900 / S.emax)), small = __builtin_ldexp(1.0, -min(300, 750 / S.emax));
   const double lo = __builtin_ldexp(1.0, -S.safe), hi = __builtin_ldexp(0.5, S.safe);
-  int f = S.safe == 0 ? 4 : 0;
+  int f = 0;
   for (int v = lv; v <= S.n; v += VW) {
     const C<L> x = v == lv ? x0 : (v < S.n ? load_planar<L>(xpt, S.n, v) : c_one<L>());
     C<L> p = x;
@@ -303,8 +303,13 @@ __device__ __forceinline__ void val_table(const ValView& S, const ValLds<L>& M, 
     const double mag = val_mag(x);
     if (mag == 0.0)
       f |= 1;
-    else if (!(mag >= lo && mag <= hi))
-      f |= mag >= small && mag <= big ? 4 : 2;
+    else if (__builtin_expect(!(mag >= lo && mag <= hi), 0)) {
+      const int k = bl_exp(mag) - 1023;  // |x| in 2^k .. 2^(k + 3/2)
+      if (!(mag >= small && mag <= big))
+        f |= 2;
+      else
+        atomicAdd(M.flag + 2, max(max(-k, k + 2) - S.safe, 0));
+    }
     if (val_nan(x)) f |= 2;
   }
   if (f) atomicOr(M.flag, f);
@@ -478,12 +483,17 @@ __device__ __forceinline__ void val_unit(const ValView& S, const ValLds<L>& M, c
   }
 }
 
+// Whether the variables' sizes let a product of some factors of a monomial leave
+// the range: flag[2] is by how many binary orders they are beyond 2^-safe ..
+// 2^safe in all, a factor takes that up to emax times, and 400 orders are left.
+__device__ __forceinline__ bool val_far(const ValView& S, int far) { return far > 400 / S.emax; }
+
 // Whether some product of factors of a unit's monomials, in whatever order,
 // can leave 2^-750 .. 2^900: one that leaves it and comes back has lost its last
 // limbs.  By the sums of the factors' negative and positive exponents, apart
 // from the products so that those keep their registers (tested product by
 // product, a launch of one row per CU took 14.3 us in place of 14.15); only for
-// points whose variables are not near 1 (val_table).
+// points whose variables are far from 1 (val_far).
 template <int L, bool FULL>
 __device__ __forceinline__ void val_ranges(const ValView& S, const ValLds<L>& M, const ValUnit& u, int lane) {
   int lo = 0, hi = 0;
@@ -745,7 +755,7 @@ __device__ __forceinline__ void val_row(const ValView& S, const ValLds<L>& M, co
   const bool direct0 = (f0 & 2) != 0, zero = (f0 & 1) != 0 && !direct0;
   for (uint32_t b = b0; b < b1; ++b) {
     const ValBlock blk = b == b0 ? pre.blk : val_block(S, b);
-    if (__builtin_expect((f0 & 6) == 4, 0))
+    if (__builtin_expect(!direct0 && val_far(S, val_uniform(M.flag[2])), 0))
       for (uint32_t u = blk.unit0 + w; u < blk.unit1; u += nw)
         val_ranges<L, !SMALL>(S, M, val_unit_of(S, blk, u), lane);
     for (uint32_t u = blk.unit0 + w; u < blk.unit1; u += nw) {
@@ -842,7 +852,7 @@ __global__ __launch_bounds__(kValThreads, limbs_of(L) == 4 ? 2 : 4) void val_row
     ValPre<L> pre;
     val_prefetch<L, MODE>(S, p, w, lv & 63, pre);
     if (r == 0) {
-      if (lv == 0) M.flag[0] = M.flag[1] = 0;
+      if (lv == 0) M.flag[0] = M.flag[1] = M.flag[2] = 0;
       __syncthreads();
       val_table<L>(S, M, x + pt * x_pt, lv, VW, x0);
     } else if (lv == 0) {
@@ -872,7 +882,7 @@ __global__ __launch_bounds__(kValThreads, limbs_of(L) == 4 ? 2 : 4) void val_adj
     val_prefetch<L, MODE_ADJ>(S, p, w, lv & 63, pre);
     const C<L> weight = c_conj(load_planar<L>(v + pt * v_pt, S.N, p));
     if (p == gi * gsize) {
-      if (lv == 0) M.flag[0] = M.flag[1] = 0;
+      if (lv == 0) M.flag[0] = M.flag[1] = M.flag[2] = 0;
       __syncthreads();
       val_table<L>(S, M, x + pt * x_pt, lv, VW, x0);
       for (int c = lv; c < S.n; c += VW) val_put(M.sum, c, c_zero<L>());
@@ -941,7 +951,7 @@ __global__ __launch_bounds__(kValThreads, limbs_of(L) == 4 ? 2 : 4) void val_bat
       const C<L> x0 = val_first_x<L>(S, xpt, lv);
       ValPre<L> pre;
       val_prefetch<L, MODE>(S, p, val_uniform(lv >> 6), lv & 63, pre);
-      if (lv == 0) M.flag[0] = M.flag[1] = 0;
+      if (lv == 0) M.flag[0] = M.flag[1] = M.flag[2] = 0;
       __syncthreads();
       val_table<L>(S, M, xpt, lv, VW, x0);
       __syncthreads();
