@@ -591,11 +591,12 @@ __device__ __forceinline__ R<NL> val_total(const ValSum<NL>& s) {
   return r;
 }
 
-// r 2^e with the leading limb of r's larger part in [0.5, 1); zeros and what
-// is not finite stay as they are
+// r 2^e with the leading limb of r's larger part in 2^-128 .. 2^128; zeros and
+// what is not finite stay as they are
 template <int L>
 __device__ __forceinline__ void val_norm(C<L>& r, int& e) {
   const double mag = val_mag(r);
+  if (mag >= 0x1p-128 && mag <= 0x1p128) return;
   if (!(mag > 0.0 && mag <= 0x1.fffffffffffffp1023)) return;
   const int k = __builtin_amdgcn_frexp_exp(mag);
   r = bl_ldexp(r, -k);
@@ -605,9 +606,13 @@ __device__ __forceinline__ void val_norm(C<L>& r, int& e) {
 // partial derivative of monomial t with respect to column v (exponent d), or
 // for v < 0 its value (d = 1), every factor in turn: the definition, for points
 // the division does not suit.  The product is kept as r 2^e, so that no order
-// of the factors leaves the range on the way to a result within it.  wt: the
-// row's weight v_p (planes N apart), whose conjugate multiplies the product, or
-// null; read here, so that the common path need not keep it.
+// of the factors leaves the range on the way to a result within it.  Powers come
+// from the table where they are in range there (a NaN among 512 polynomials of
+// 256 monomials of 32 variables up to the third power, quad double: 3.2 ms; each
+// formed here: 10.0; among 256 x 256 x 16 up to the fourth, double double: 0.15
+// and 0.24).  wt: the row's weight v_p (planes N apart), whose conjugate
+// multiplies the product, or null; read here, so that the common path need not
+// keep it.
 template <int L>
 __device__ C<L> val_direct(const ValView& S, const ValLds<L>& M, const ValBlock& blk, uint32_t t, int v, int d,
                            const double* wt) {
@@ -631,14 +636,25 @@ __device__ C<L> val_direct(const ValView& S, const ValLds<L>& M, const ValBlock&
   }
   for (int i = 0; i < int(U.seg); ++i)
     for (int q = 0; q < (1 << U.lgs); ++q) {
-      const uint32_t w = val_ld(S.rec, U.base + 64 * i + (g << U.lgs) + q);
-      const int wv = int(w % uint32_t(M.cols)), wd = int(w / uint32_t(M.cols)) + (wv != v);
+      const int w = int(val_ld(S.rec, U.base + 64 * i + (g << U.lgs) + q));
+      const int wv = w % M.cols, wd = w / M.cols + (wv != v);
       if (wv == S.n || wd == 0) continue;
-      C<L> x = val_get<L>(M.tab, wv);
+      C<L> x = val_get<L>(M.tab, (min(wd, S.tab) - 1) * M.cols + wv);
       int ex = 0;
+      if (wd > 1 && !(wd <= S.tab && val_mag(x) >= 0x1p-750 && val_mag(x) <= 0x1p900)) {
+        // x^wd is not in the table, or out of range there
+        x = val_get<L>(M.tab, wv);
+        const double mag = val_mag(x);
+        if (mag > 0.0 && mag <= 0x1.fffffffffffffp1023) {
+          ex = __builtin_amdgcn_frexp_exp(mag);
+          x = bl_ldexp(x, -ex);
+          ex *= wd;
+        }
+        x = c_pow(x, wd);
+      }
       val_norm(x, ex);
-      r = c_mul(r, c_pow(x, wd));
-      e += wd * ex;
+      r = c_mul(r, x);
+      e += ex;
       val_norm(r, e);
     }
   return bl_ldexp(c_mul_d(r, double(d)), e);
