@@ -46,11 +46,11 @@ BATCH_COUNT, BATCH_POINTS = 4096, 8
 # of known size) and FP64 instruction counts.  They hold for the kernel
 # sources they were taken with: the bench reports them only while the
 # sources match.  Every counted workload is an evaluation, so the digest
-# covers the evaluation kernels' sources, their arithmetic, packing, planning
-# and launchers (the least-squares and Gauss-Newton kernels are not among
-# them).
+# covers the evaluation kernels' sources and what they include (number helpers
+# and the reciprocal are in the headers of the solve), their arithmetic,
+# packing, planning and launchers.
 COUNTERS_DIR = os.path.join(ROOT, "profiles")
-KERNEL_SOURCES = ["eval_kernels.hpp", "value_kernels.hpp", "mdarith.hpp", "layout.hpp", "polyeval.hip", "packer.cpp", "packer.hpp",
+KERNEL_SOURCES = ["eval_kernels.hpp", "value_kernels.hpp", "blockls_kernels.hpp", "newton_kernels.hpp", "mdarith.hpp", "layout.hpp", "polyeval.hip", "packer.cpp", "packer.hpp",
                   "launch.hpp", "instances.hip"]
 
 

@@ -7,12 +7,13 @@
 //   1. bl_gram_kernel: the Gram matrix of the panel;
 //   2. bl_chol_kernel: its factor U^H D U, one workgroup per problem, so that
 //      the serial chain of a panel is B small steps in LDS instead of B inner
-//      products over all rows and B launches;
+//      products over all rows and B launches (the method of the Cholesky
+//      factor of A^H A, with what it leaves corrected below);
 //   3. bl_solve_kernel: X = A U^-1 D^-1/2 by forward substitution, row by row
 //      (backward stable in each row), X overwriting the panel;
 //   4. bl_dot_kernel: S = X^H [X | trailing columns].  E = X^H X - I is
-//      what the factor's rounding left (at most about 2^-58 in double double,
-//      see bl_chol_kernel), and its first order is folded into everything
+//      what rounding left (bounds per level at bl_fin_kernel), and its
+//      first order is folded into everything
 //      that follows: Q = X (I - F), R = (I + F) D^1/2 U, F the upper
 //      triangle of E with half its diagonal, so that Q^H Q = I + O(E^2);
 //   5. bl_fin_kernel: the rows of R, and T = (I - E) S;
@@ -20,9 +21,10 @@
 // The trailing columns see the exact projector of the panel's span, panels in
 // order: the right-looking sweep of Fig. 4 with its columns in blocks.  A
 // panel too ill-conditioned for its Gram matrix is orthogonalised by plain
-// modified Gram-Schmidt inside bl_chol_kernel instead (repeated where one
+// modified Gram-Schmidt in step 3 instead (bl_mgs_panel; repeated where one
 // sweep would leave E too large), so every matrix the one-column-at-a-time
-// algorithm takes is taken.
+// algorithm takes is taken.  Problems of a few unknowns are one wavefront's
+// work (smallls_kernels.hpp).
 //
 // Contractions.  A multi-double is cut into ND signed base-256 digits
 // (fixed point against a power of two: the column's largest entry for the
@@ -39,9 +41,12 @@
 // 544 int8 multiply-adds, of which the matrix cores do 2.5e15 a second.
 // Against the column-by-column sweep that this replaces (a launch and two
 // workgroup reductions per pivot, FP64 throughout) a Gauss-Newton step went
-// from 2.08 to 0.75 ms (complex double double, n = 256), 53.5 to 14.7 ms
-// (n = 2048), 35.0 to 7.7 ms (real quad double, n = 1016), and the batched
-// step over 96 system-points of n = 32 .. 256 from 39.9 to 2.2 ms.
+// from 2.08 to 0.73 ms (complex double double, n = 256), 53.6 to 12.6 ms
+// (n = 2048), 35.1 to 6.5 ms (real quad double, n = 1016), and the batched
+// step over 96 system-points of n = 32 .. 256 from 39.8 to 1.9 ms.  Where all
+// panels are too ill-conditioned (columns that agree to 1e-8 or better) the
+// sweep is ahead: 1.3 to 1.8 times in double double at 1e-8, 2.3 to 3.3 at
+// 1e-13, 2.7 to 4 in double.
 #pragma once
 #include <hip/hip_runtime.h>
 
@@ -1256,8 +1261,14 @@ __global__ __launch_bounds__(256) void bl_solve_kernel(BlView V, int panel, int 
 // in digits ([tile][digit][16 real columns][64] bytes, real column 2 c
 // holding (Tr, -Ti) and 2 c + 1 (Ti, Tr) of the B pairs, so that the update
 // is one real product); the exponents of the next panel's columns cleared.
-// For the panel's own columns R = (I + F) D^1/2 U instead.  E is at most
-// 2^-58, so its products need no more than double arithmetic.  grid (column
+// For the panel's own columns R = (I + F) D^1/2 U instead.  E is about u_C over
+// the smallest pivot ratio from the Gram matrix (double double 2^-104 / 2^-46 =
+// 2^-58, quad double 2^-160; double, factored in double double, has the rounding
+// of X itself, 2^-53 over the root of 2^-26, as its largest part, 2^-35 with a
+// panel's 32 columns) and below bl_mgs_panel's kLoss from modified Gram-Schmidt
+// (2^-33, 2^-64, 2^-162).  E^2 and E times double's roundoff are below the
+// level's roundoff (2^-53, 2^-104, 2^-206) in each case, so its first order
+// does and its products need no more than double arithmetic.  grid (column
 // groups, slots), 256 threads: B lanes per column
 template <int L>
 __global__ __launch_bounds__(256) void bl_fin_kernel(BlView V, int panel, int cur) {
@@ -1636,7 +1647,7 @@ __global__ __launch_bounds__(kBlBsThreads) void bl_bs_diag_kernel(BlView V, int 
 }
 
 // y[0, s) -= R[0:s, s:e] x[s:e] for the block `stage` just solved: eight
-// lanes per row, their columns added pairwise.  grid (row blocks of 32,
+// lanes per row, their sums added in order.  grid (row blocks of 32,
 // slots), 256 threads
 template <int L>
 __global__ __launch_bounds__(256) void bl_bs_update_kernel(BlView V, int stage) {

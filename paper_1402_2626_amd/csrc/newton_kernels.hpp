@@ -1,6 +1,7 @@
 // Gauss-Newton step on the device (Sec. 4): number helpers of the solve, the
 // sizes of a batched step, and the right-hand side of the Newton homotopy.
-// The least-squares solve itself is in blockls_kernels.hpp.
+// The least-squares solve itself is in blockls_kernels.hpp and, for a few
+// unknowns, smallls_kernels.hpp.
 #pragma once
 #include <hip/hip_runtime.h>
 

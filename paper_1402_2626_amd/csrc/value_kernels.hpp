@@ -40,10 +40,10 @@
 //
 // A launch that fills the chip is bound by FP64 and address issue (LDS active
 // a third of the time), one row per CU by the chain launch, loads, table,
-// products, sums.  Reverse sweep -> this: DD n = 256, 256 x 16: 14.9 -> 13.2 us
+// products, sums.  Reverse sweep -> this: DD n = 256, 256 x 16: 14.9 -> 14.0 us
 // at one point, 343 -> 178 us at 64 points of 128 x 16; QD n = 512, 256 x 32:
-// 546 -> 131 us; cyclic 192-roots in DD, whose longest rows are 192 monomials
-// of 191 variables: 130 -> 44 us; a batch of 24 DD systems: 818 -> 373 us.
+// 546 -> 146 us; cyclic 192-roots in DD, whose longest rows are 192 monomials
+// of 191 variables: 130 -> 45 us; a batch of 24 DD systems: 818 -> 375 us.
 #pragma once
 #include <hip/hip_runtime.h>
 
