@@ -168,3 +168,16 @@ def test_partial_products_out_of_range(pe, L, lanes):
     x = V.points((252, L), 1, n, L, False) * lift
     F, J = V.evaluate(pe, s, x, False)
     V.check(s, x[0], F[0], J[0], range(3))
+
+
+@pytest.mark.parametrize("L", [1, 2, 4])
+@pytest.mark.parametrize("lift", [0, 1, 3])
+def test_long_products(pe, L, lift):
+    """Products of 600 variables (quad double, which takes fewer: 200) of modulus 1 or by halves 2^-lift and 2^lift
+    (2^-3lift, 2^3lift): on the way they reach 2^(-300 lift)."""
+    n, m = 600 if L < 4 else 200, 2
+    lift *= 600 // n
+    s = uniform((261, L), L, n, 1, m, lambda rng, p, i: np.arange(n))
+    x = V.points((262, L, lift), 1, n, L, False) * np.where(np.arange(n) < n // 2, 2.0**-lift, 2.0**lift)
+    F, J = V.evaluate(pe, s, x, False)
+    V.check(s, x[0], F[0], J[0], range(1))
